@@ -177,9 +177,13 @@ struct StepArgs {
   int32_t max_splits;
   uint32_t key0, key1;
   double dt;
-  int32_t kernel;  // FP32 schedule: 0 lane-per-particle windows, 1 / 2 wave
-                   // pools of 128 / 256 particles
+  int32_t kernel;  // schedule: 0 lane-per-particle windows, 1 / 2 / 3 wave pools
+                   // of 128 / 256 / 128 particles
   int32_t idle;    // wave pools: idle lanes that trigger a partial split pass
+  int32_t refill;  // wave pools: lanes without a particle that end a window of
+                   // groups while there are particles for them
+  uint32_t pool_cap;  // and the particles a wave holds at a time (a multiple of
+                      // 16, at most the pool's home slots)
   uint32_t n0_offset;  // batched launches: steps taken earlier in the call
   int32_t obs_lds;     // streamed-histogram bins privatised in LDS (0: global)
   int32_t probe;       // autotuning probe: the same kernels under probe names
@@ -204,6 +208,7 @@ constexpr int64_t kMaxParticles = 0xFFFFFFFFll - 0xFFFFFll;  // 2^32 - 2^20
 constexpr uint32_t kMaxPersistBlocks = 2048;
 constexpr uint32_t kDrainMax = 1024;
 constexpr uint32_t kLdsDrainMax = 1u << 20;
+constexpr int32_t kMaxGroups = 64;  // Philox groups of a window at most
 
 // Batched form: one work item per (set, tile of particles).  The wave-pool
 // kernel reads only the set (its waves claim the set's particles from the

@@ -86,6 +86,55 @@ __device__ __forceinline__ void fresh_keys(uint32_t &k0, uint32_t &k1) {
   if constexpr (sizeof(real) == 8) asm volatile("" : "+s"(k0), "+s"(k1));
 }
 
+// Main-stream Philox with the particle's share computed once.  The counter
+// (p, g, 0, tag) differs between a particle's groups only in its second
+// word, and its third word is zero, so of the first three rounds' six
+// products three depend on the particle alone: those of round one (p and
+// zero), one of round two (of a word that holds p and the tag) and one of
+// round three.  A lane keeps the four words that later rounds read from them
+// and a call takes 16 products instead of 20 (19 after the compiler has
+// folded the zero).
+struct MainCtr {
+  uint32_t lo1, lo2, hi3, lo3;
+};
+__device__ __forceinline__ MainCtr main_ctr(uint32_t pid, uint32_t tag, uint32_t k0,
+                                            uint32_t k1) {
+  const uint64_t p1 = (uint64_t)0xD2511F53u * (uint64_t)pid;
+  const uint32_t c2 = xor3((uint32_t)(p1 >> 32), tag, k1);
+  const uint64_t p2 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
+  const uint32_t c0 = (uint32_t)(p2 >> 32) ^ (k0 + 0x9E3779B9u);
+  const uint64_t p3 = (uint64_t)0xD2511F53u * (uint64_t)c0;
+  return {(uint32_t)p1, (uint32_t)p2, (uint32_t)(p3 >> 32), (uint32_t)p3};
+}
+__device__ __forceinline__ U4 philox_main(const MainCtr &m, uint32_t g, uint32_t k0,
+                                          uint32_t k1) {
+  uint32_t c0 = g ^ k0;  // round one
+  k0 += 0x9E3779B9u;
+  k1 += 0xBB67AE85u;
+  const uint64_t p2 = (uint64_t)0xD2511F53u * (uint64_t)c0;  // round two
+  uint32_t c2 = xor3((uint32_t)(p2 >> 32), m.lo1, k1);
+  k0 += 0x9E3779B9u;
+  k1 += 0xBB67AE85u;
+  const uint64_t p3 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;  // round three
+  c0 = xor3((uint32_t)(p3 >> 32), m.lo2, k0);
+  c2 = xor3(m.hi3, (uint32_t)p2, k1);
+  uint32_t c1 = (uint32_t)p3, c3 = m.lo3;
+#pragma unroll
+  for (int r = 3; r < 10; ++r) {
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+    const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
+    const uint32_t t0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+    const uint32_t t2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+    c1 = (uint32_t)p1;
+    c3 = (uint32_t)p0;
+    c0 = t0;
+    c2 = t2;
+  }
+  return {c0, c1, c2, c3};
+}
+
 // Sine and cosine of t in [0, 2 pi) (the Box-Muller angle, t = 2 pi u with
 // u in (0, 1)): the argument is reduced by quarter turns, r = t - q pi/2
 // with pi/2 in two parts (Cody and Waite); for q <= 4 the first step
@@ -472,14 +521,17 @@ struct ObsSink {
   const EdgeRec64 *e64;
 };
 
-template <typename P>
-__device__ __forceinline__ void observe(const P &q, const SetDev &S, const ObsSink &o) {
-  const EdgeRec64 &r = o.e64[q.e];
-  const int32_t idx = q.e * S.obs_nb + bin_of(q.pos64(r.L), r.span, S.obs_nb);
+__device__ __forceinline__ void observe_at(int32_t e, double x, const SetDev &S,
+                                           const ObsSink &o) {
+  const int32_t idx = e * S.obs_nb + bin_of(x, o.e64[e].span, S.obs_nb);
   if (o.lds)
     atomicAdd(&o.lds[idx], 1u);
   else
     atomicAdd((unsigned long long *)&S.obs[idx], 1ull);
+}
+template <typename P>
+__device__ __forceinline__ void observe(const P &q, const SetDev &S, const ObsSink &o) {
+  observe_at(q.e, q.pos64(o.e64[q.e].L), S, o);
 }
 
 template <typename T, int N>
@@ -645,8 +697,8 @@ struct Particle64 {
   // the local coordinate t = x K / L - j.
   __device__ __forceinline__ const TabRec64 &interval(double at, double &t) const {
     const double s = at * R.inv_h;
-    double j = floor(s);
-    j = j < 0.0 ? 0.0 : (j > (double)(R.tab_k - 1) ? (double)(R.tab_k - 1) : j);
+    // (also a row of the edge for a lane that has run past its vertex)
+    const double j = fmin(fmax(floor(s), 0.0), (double)(R.tab_k - 1));
     t = s - j;
     return G.tab64[R.tab0 + (int32_t)j];
   }
@@ -699,20 +751,6 @@ struct Particle64 {
       return true;
     }
     return false;
-  }
-
-  // The same first sub-step as straight-line code (the wave pools): applied
-  // only where `active`; returns whether the proposal stays inside the edge
-  // (a step that starts on a Wentzell vertex never does: it is parked for
-  // its visit).  The normal is already folded where the step starts on a
-  // vertex (prep_window).
-  __device__ __forceinline__ bool fast_pred(double w, bool active) {
-    const double mu = drift(x);
-    const double g = diffusion(x) * sqdt;
-    const double xt = fma(g, w, fma(mu, dtv, x));
-    const bool in = (xt > 0.0) & (xt < R.L) & !on_wentzell();
-    x = (active & in) ? xt : x;
-    return in;
   }
 
   double dtv;
@@ -792,6 +830,10 @@ struct Particle64 {
       ++nhit;
       t.hits++;
       const VtxBlk vb = G.vtx[v];
+      // (drawn while the vertex block loads, for a removed particle too)
+      uint32_t k0 = A.key0, k1 = A.key1;
+      fresh_keys<double>(k0, k1);
+      const U4 hd = philox(pid, step, (uint32_t)H.k, S.tag, k0, k1);
       // a Wentzell vertex: the visit this hit starts, its overshoot being
       // how far past the vertex the proposal went
       double h_move = h, owed = 0.0;
@@ -806,9 +848,6 @@ struct Particle64 {
         die(v, step, S);
         return true;
       }
-      uint32_t k0 = A.key0, k1 = A.key1;
-      fresh_keys<double>(k0, k1);
-      const U4 hd = philox(pid, step, (uint32_t)H.k, S.tag, k0, k1);
       const SlotPick sp = pick_slot(G, vb, hd.x);
       e = eo_edge(sp.eo);
       R = G.e64[e];
@@ -976,8 +1015,7 @@ struct Particle32 {
   // at x = L) and the local coordinate t.
   __device__ __forceinline__ const TabRec32 &interval(float x, float &t) const {
     const float s = x * inv_h;
-    float j = floorf(s);
-    j = j < 0.0f ? 0.0f : (j > (float)(tab_k - 1) ? (float)(tab_k - 1) : j);
+    const float j = fminf(fmaxf(floorf(s), 0.0f), (float)(tab_k - 1));
     t = s - j;
     return G.tab32[tab0 + (int32_t)j];
   }
@@ -1119,21 +1157,6 @@ struct Particle32 {
     return false;
   }
 
-  // First sub-step as straight-line code: applied only where `active`;
-  // returns whether the proposal stays inside the edge.  No y = 0 check:
-  // y is positive after every step that stays inside an edge, so only a
-  // group's first active step can start on a vertex, and the caller passes
-  // at_vertex(w) for it.
-  __device__ __forceinline__ bool fast_pred(float w, bool active) {
-    float err;
-    const float yt = propose(w, err);
-    const bool in = (yt > 0.0f) & (yt < R.L) & !on_wentzell();
-    const bool upd = active & in;
-    y = upd ? yt : y;
-    yl = upd ? err : yl;
-    return in;
-  }
-
   // One vertex crossing of a step whose current sub-step proposal (normal
   // h.w over the remaining time h.hh + h.hl; the step's first sub-step when
   // h.k == 0) reached a vertex: crossing time, edge draw, and the next
@@ -1251,6 +1274,8 @@ struct Particle32 {
       ++nhit;
       t.hits++;
       const VtxBlk vb = G.vtx[v];
+      // (drawn while the vertex block loads, for a removed particle too)
+      const U4 hd = philox(pid, step, (uint32_t)h.k, S.tag, A.key0, A.key1);
       // a Wentzell vertex: the visit this hit starts, with the proposal's
       // overshoot past the vertex
       double hm = 0.0, owed = 0.0;
@@ -1264,7 +1289,6 @@ struct Particle32 {
         die(v, step, S);
         return true;
       }
-      const U4 hd = philox(pid, step, (uint32_t)h.k, S.tag, A.key0, A.key1);
       const SlotPick sp = pick_slot(G, vb, hd.x);
       e = eo_edge(sp.eo);
       R = load_edge32(G.e32, e);
@@ -1465,11 +1489,11 @@ __global__ __launch_bounds__(kBlock) void k_batch(const GraphDev *graphs,
 }
 
 // ------------------------------------------------ FP32 wave-pool kernel --
-// Each wave owns PW particles (128 or 256): 64 ride in the lanes, the others
-// wait in the wave's private LDS home slots.  A lane runs its particle's
-// first sub-steps for one window (one or two main-stream Philox groups,
-// four or eight steps) per iteration; a particle whose sub-step reaches a
-// vertex is parked: its state
+// Each wave owns PW particles (128 or 256; fewer where the set is small): 64
+// ride in the lanes, the others wait in the wave's private LDS home slots.
+// The lanes run their particles' first sub-steps in groups of four (one
+// main-stream Philox block) until enough of them wait for another particle;
+// a particle whose sub-step reaches a vertex is parked: its state
 // goes to its home slot and its slot id onto the wave's split queue, and the
 // lane takes a ready particle instead.  When 64 particles are parked (or
 // lanes would idle), one split pass takes them with every lane busy and
@@ -1514,7 +1538,7 @@ struct PoolLds32 : PoolTrace<TRACE, PW> {
   float hl[PW];
   int32_t last[PW]; // last slot drawn in the parked step
   uint32_t pid[PW];   // particle held by each home slot
-  uint8_t k[PW];    // crossings so far in the parked step
+  uint8_t k[PW];    // crossings so far in the parked step, else 0
   uint8_t ready[PW];
   uint8_t split[PW];
   uint8_t freeq[PW];  // home slots without a particle
@@ -1537,6 +1561,16 @@ struct PoolLds64 : PoolTrace<TRACE, PW> {
   uint8_t split[PW];
   uint8_t freeq[PW];
 };
+
+// The lanes of the wave where c holds, and whether a lane is in a mask.  The
+// wave pools keep their lane masks as 64-bit values, combined in the scalar
+// unit: a ballot of a plain comparison is the comparison, whereas a
+// combination of conditions, and HIP's __ballot of an int, go through a
+// vector register and a second comparison.
+__device__ __forceinline__ uint64_t ballot(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+__device__ __forceinline__ bool in_mask(uint64_t m) {
+  return __builtin_amdgcn_inverse_ballot_w64(m);
+}
 
 __device__ __forceinline__ uint32_t lane_rank(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
@@ -1757,6 +1791,201 @@ __device__ __forceinline__ void pool_particle(Particle64<TRACE, LDS, GEN> &q, co
                                   A.dt, sqrt(A.dt)};
 }
 
+// A lane's particle while it runs first sub-steps: what a window of steps
+// needs, in registers, and no more.  Pos is the part that a step changes;
+//   propose(p, w)   the position a first sub-step from p reaches;
+//   inside(p)       the lanes where it lies strictly inside the edge;
+//   fold(p, w)      the normal of a step from p as it enters the proposal
+//                   (a particle on a vertex moves into its edge);
+//   on_vertex(p)    the lanes where p is an end of the edge;
+//   visits(p)       the step from p starts with a Wentzell visit (GEN);
+//   reanchor(p, c)  the nearer reference end, where c (FP32).
+struct Pos32 {
+  float y, yl;
+};
+struct Pos64 {
+  double x;
+};
+__device__ __forceinline__ Pos32 pick(bool c, const Pos32 &a, const Pos32 &b) {
+  return {c ? a.y : b.y, c ? a.yl : b.yl};
+}
+__device__ __forceinline__ Pos64 pick(bool c, const Pos64 &a, const Pos64 &b) {
+  return {c ? a.x : b.x};
+}
+
+// FP32.  Affine coefficients: the first sub-step is y + (fma(gs, w, fma(cd,
+// y, ad)) + yl) with per-frame constants; adf is ad of the other reference
+// end and the sign of gs is the end itself (negative: the terminal one), so
+// a change of end is four selects.  GEN evaluates the coefficients at y.
+template <bool TRACE, bool LDS, int GEN>
+struct Lane32 {
+  using real = float;
+  using Pos = Pos32;
+  using Q = Particle32<TRACE, LDS, GEN>;
+  Pos32 p;
+  int32_t e;
+  float L, cd, ad, adf, gs;
+  Q q;  // GEN only
+
+  __device__ __forceinline__ void init(const GView &G, uint32_t *s_exit, const StepArgs &A) {
+    pool_particle(q, G, s_exit, A);
+    p = {0.0f, 0.0f};
+    e = 0;
+    L = cd = ad = adf = gs = 0.0f;
+  }
+  template <class Pool>
+  __device__ __forceinline__ void load(const Pool &P, uint32_t s, const GView &G) {
+    p = {P.y[s], P.yl[s]};
+    if constexpr (GEN) {
+      pool_load(q, P, s);
+      e = q.e;
+      L = q.R.L;
+    } else {
+      const uint32_t ef = P.ef[s];
+      e = (int32_t)(ef & kEdgeMask);
+      const EdgeRec32 r = G.e32[e];
+      const bool side = (ef & kSideBit) != 0u;
+      const float d0 = r.a * q.dt, d1 = -r.aL * q.dt, g0 = r.sigma * q.sqdt;
+      L = r.L;
+      cd = r.c * q.dt;
+      ad = side ? d1 : d0;
+      adf = side ? d0 : d1;
+      gs = side ? -g0 : g0;
+    }
+  }
+  __device__ __forceinline__ uint32_t side() const {
+    if constexpr (GEN) return q.side;
+    return __float_as_uint(gs) >> 31;
+  }
+  __device__ __forceinline__ uint32_t state() const {
+    return (uint32_t)e | (side() ? kSideBit : 0u);
+  }
+  __device__ __forceinline__ Pos32 propose(const Pos32 &a, float w) {
+    float s;
+    if constexpr (GEN) {
+      const float sg = q.fsigma(a.y) * q.sqdt;
+      s = fmaf(q.side ? -sg : sg, w, q.fdrift(a.y) * q.dt) + a.yl;
+    } else {
+      s = fmaf(gs, w, fmaf(cd, a.y, ad)) + a.yl;
+    }
+    const float yt = a.y + s;  // Fast2Sum, as Particle32::add_comp
+    return {yt, s - (yt - a.y)};
+  }
+  __device__ __forceinline__ uint64_t inside(const Pos32 &a) const {
+    return ballot(a.y > 0.0f) & ballot(a.y < L);
+  }
+  __device__ __forceinline__ uint64_t on_vertex(const Pos32 &a) const {
+    return ballot(a.y == 0.0f);
+  }
+  __device__ __forceinline__ float fold(const Pos32 &, float w) const {
+    return copysignf(fabsf(w), GEN ? q.gs : gs);
+  }
+  __device__ __forceinline__ bool visits(const Pos32 &a) const {
+    if constexpr (GEN != kGenFull) return false;
+    return a.y <= 0.0f && ((uint32_t)(q.side ? q.R.vterm : q.R.vinit) & kWentzellEnd);
+  }
+  // y > L - y exactly when y > L/2: L - y is exact from L/2 on (Sterbenz)
+  // and no smaller than L/2, so than y, below.
+  __device__ __forceinline__ void reanchor(Pos32 &a, bool c) {
+    if constexpr (GEN) {
+      q.y = a.y;
+      q.yl = a.yl;
+      q.reanchor_if(c);
+      a = {q.y, q.yl};
+    } else {
+      const float t = L - a.y;
+      const bool flip = c & (a.y > t);
+      a = {flip ? t : a.y, flip ? -a.yl : a.yl};
+      gs = flip ? -gs : gs;
+      const float o = ad;
+      ad = flip ? adf : ad;
+      adf = flip ? o : adf;
+    }
+  }
+  template <class Pool>
+  __device__ __forceinline__ void store(Pool &P, uint32_t s, const Pos32 &a) const {
+    P.ef[s] = state();
+    P.y[s] = a.y;
+    P.yl[s] = a.yl;
+  }
+  __device__ __forceinline__ void write(const SetDev &S, uint32_t pid, const Pos32 &a,
+                                        uint32_t state) const {
+    S.ef[pid] = state;
+    S.y32[pid] = make_float2(a.y, a.yl);
+  }
+  // position from the initial vertex in FP64, as the histogram reads it
+  __device__ static double pos64(const Pos32 &a, uint32_t side, double L) {
+    const double v = (double)a.y + (double)a.yl;
+    return side ? L - v : v;
+  }
+};
+
+// FP64: positions from the initial vertex, no reference end to change.
+template <bool TRACE, bool LDS, int GEN>
+struct Lane64 {
+  using real = double;
+  using Pos = Pos64;
+  using Q = Particle64<TRACE, LDS, GEN>;
+  Pos64 p;
+  int32_t e;
+  double L, a0, c0, gd;  // affine: drift a0 + c0 x, sigma sqrt(dt)
+  Q q;                   // its dt; GEN: the edge record too
+
+  __device__ __forceinline__ void init(const GView &G, uint32_t *s_exit, const StepArgs &A) {
+    pool_particle(q, G, s_exit, A);
+    p = {0.0};
+    e = 0;
+    L = a0 = c0 = gd = 0.0;
+  }
+  template <class Pool>
+  __device__ __forceinline__ void load(const Pool &P, uint32_t s, const GView &G) {
+    p = {P.x[s]};
+    e = (int32_t)(P.ef[s] & kEdgeMask);
+    if constexpr (GEN) {
+      q.R = G.e64[e];
+      L = q.R.L;
+    } else {
+      const EdgeRec64 &r = G.e64[e];
+      L = r.L;
+      a0 = r.a;
+      c0 = r.c;
+      gd = r.sigma * q.sqdt;
+    }
+  }
+  __device__ __forceinline__ uint32_t side() const { return 0u; }
+  __device__ __forceinline__ uint32_t state() const { return (uint32_t)e; }
+  __device__ __forceinline__ Pos64 propose(const Pos64 &a, double w) const {
+    if constexpr (GEN)
+      return {fma(q.diffusion(a.x) * q.sqdt, w, fma(q.drift(a.x), q.dtv, a.x))};
+    return {fma(gd, w, fma(fma(c0, a.x, a0), q.dtv, a.x))};
+  }
+  __device__ __forceinline__ uint64_t inside(const Pos64 &a) const {
+    return ballot(a.x > 0.0) & ballot(a.x < L);
+  }
+  __device__ __forceinline__ uint64_t on_vertex(const Pos64 &a) const {
+    return ballot(a.x == 0.0) | ballot(a.x == L);
+  }
+  __device__ __forceinline__ double fold(const Pos64 &a, double w) const {
+    return a.x == 0.0 ? fabs(w) : -fabs(w);
+  }
+  __device__ __forceinline__ bool visits(const Pos64 &a) const {
+    if constexpr (GEN != kGenFull) return false;
+    return (a.x <= 0.0 && ((uint32_t)q.R.vinit & kWentzellEnd)) ||
+           (a.x >= L && ((uint32_t)q.R.vterm & kWentzellEnd));
+  }
+  __device__ __forceinline__ void reanchor(Pos64 &, bool) {}
+  template <class Pool>
+  __device__ __forceinline__ void store(Pool &P, uint32_t s, const Pos64 &a) const {
+    P.x[s] = a.x;  // the edge in the home slot is unchanged
+  }
+  __device__ __forceinline__ void write(const SetDev &S, uint32_t pid, const Pos64 &a,
+                                        uint32_t state) const {
+    S.ef[pid] = state;
+    S.x64[pid] = a.x;
+  }
+  __device__ static double pos64(const Pos64 &a, uint32_t, double) { return a.x; }
+};
+
 // Adds a lane's tallies to the block's 64-bit totals and clears them.
 __device__ __forceinline__ void drain_tally(Tally &t, unsigned long long *s_tot) {
   if (t.trunc) atomicAdd(&s_tot[0], (unsigned long long)t.trunc);
@@ -1781,15 +2010,15 @@ __device__ __forceinline__ void drain_lds(uint32_t *lds, uint64_t *glob, int32_t
 // lanes' 32-bit tallies into the block's 64-bit totals every A.drain (at
 // most kDrainMax = 1024) iterations of its pool loop, and the block's u32
 // LDS exit and snapshot counters into the set's 64-bit ones every
-// A.drain_lds (at most kLdsDrainMax = 2^20).  Bounds: one iteration
-// finishes at most two particles on a lane (its own, and the one of its
-// split-pass slot), each adding at most 2^20 steps (a launch's cap), plus
-// at most one crossing, so 1024 iterations add at most 2^31 + 1024 to a
-// tally.  Between two drains of an LDS counter (by any wave), each of the
-// block's four waves runs fewer than A.drain_lds iterations, each adding at
-// most 64 exit records and 64 x 9 snapshots (one per step of a window of at
-// most 8 steps, and one per split-pass lane): below 4 x 2^20 x 576 < 2^32
-// per counter.  The LDS drains are rare because each is a round of
+// A.drain_lds (at most kLdsDrainMax = 2^20) groups of steps and split
+// passes.  Bounds: one iteration finishes at most two particles on a lane
+// (its own, and the one of its split-pass slot), each adding at most 2^20
+// steps (a launch's cap), plus at most one crossing, so 1024 iterations add
+// at most 2^31 + 1024 to a tally.  Between two drains of an LDS counter (by
+// any wave), each of the block's four waves runs fewer than A.drain_lds +
+// kMaxGroups + 1 groups and passes, each adding at most 64 x 4 snapshots, or
+// 64 exit records and 64 snapshots: below 4 (2^20 + 65) x 256 < 2^31 per
+// counter.  The LDS drains are rare because each is a round of
 // device-scope atomics on the set's counters, which go past the XCD's L2.
 
 // Where a wave's particles come from: the set's counter.  The grid stays
@@ -1806,25 +2035,30 @@ __device__ __forceinline__ void drain_lds(uint32_t *lds, uint64_t *glob, int32_t
 // the host bounds the reservation so that the counter cannot wrap.
 // Q: the particle type (Particle32 or Particle64, each with its pool type
 // in LDS).
-template <bool TRACE, bool LDS, bool OBS, int PW, int NG, int GEN, class Q, class Pool>
+template <bool TRACE, bool LDS, bool OBS, int PW, int GEN, class Ln, class Pool>
 __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
                          const StepArgs &A, Pool &P, uint32_t *s_exit, Tally &t,
                          unsigned long long *s_tot, int32_t nnz, const ObsSink &sink) {
-  using real = typename Q::real;
+  using Q = typename Ln::Q;
+  using Pos = typename Ln::Pos;
+  using real = typename Ln::real;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t n_end = S.n0 + A.nsteps;
-  Q q;
-  pool_particle(q, G, s_exit, A);
-  bool has = false;
-  uint32_t slot = 0, n = 0, pid = 0;  // the lane's home slot, next step, particle
+  const uint32_t g_last = (n_end - 1u) >> 2, part = n_end & 3u;
+  Ln ln;
+  ln.init(G, s_exit, A);
+  MainCtr ctr{0u, 0u, 0u, 0u};
+  uint64_t m_has = 0ull;             // lanes with a particle
+  uint32_t slot = 0, g = 0, jb = 0;  // the lane's home slot, next group, first step in it
   uint32_t snap = 0;  // next snapshot count of the lane's particle
   // Ready, split and free queues: FIFO rings over the pool's slot ids, with
   // wave-uniform head and tail counters.  FIFO keeps the particles of a pool
   // advancing together, so a launch ends without a long tail of stragglers.
   constexpr uint32_t K = (uint32_t)PW;
   uint32_t r_head = 0, r_tail = 0, s_head = 0, s_tail = 0;
-  uint32_t f_head = 0, f_tail = K;
-  for (uint32_t i = lane; i < K; i += 64u) P.freeq[i] = (uint8_t)i;
+  uint32_t f_head = 0, f_tail = A.pool_cap;
+  for (uint32_t i = lane; i < A.pool_cap; i += 64u) P.freeq[i] = (uint8_t)i;
+  const int32_t lanes = min((int32_t)A.pool_cap, 64);  // lanes that a full pool keeps busy
   const uint32_t lim = S.n;
   bool exhausted = false;   // the reservation is used up and the set has run out
   bool last_chunk = false;  // the set ran out with the current reservation
@@ -1837,7 +2071,7 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
       iter = 0;
       drain_tally(t, s_tot);
     }
-    if (++iter_lds >= A.drain_lds) {
+    if (iter_lds >= A.drain_lds) {
       iter_lds = 0;
       if (LDS) drain_lds(s_exit, S.exit_cnt, nnz);
       if (OBS && sink.lds) drain_lds(sink.lds, S.obs, A.obs_lds);
@@ -1874,11 +2108,12 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
       const uint32_t hs = mine ? P.freeq[(f_head + lane) % K] : 0u;
       const bool ok = pool_claim<TRACE, PW, GEN>(G, S, n_edges, id, P, hs, mine && id < lim);
       f_head += want;
-      const uint64_t m_ok = __ballot(ok);
-      const uint64_t m_back = __ballot(mine & !ok);
+      const uint64_t m_ok = ballot(ok);
+      const uint64_t m_back = ballot(mine & !ok);
       if (ok) {
         P.n[hs] = S.n0;
         P.pid[hs] = id;
+        P.k[hs] = 0;
         if constexpr (TRACE) {
           P.hits[hs] = S.hits[id];
           P.hash[hs] = S.seqhash[id];
@@ -1893,91 +2128,182 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
     }
     // lanes without a particle take ready ones
     {
-      const uint64_t m_empty = __ballot(!has);
       const uint32_t ready_cnt = r_tail - r_head;
-      if (!has) {
-        const uint32_t r = lane_rank(m_empty);
-        if (r < ready_cnt) {
+      const uint32_t r = lane_rank(~m_has);
+      const uint64_t m_take = ~m_has & ballot(r < ready_cnt);
+      if (m_take != 0ull) {
+        if (in_mask(m_take)) {
           slot = P.ready[(r_head + r) % K];
-          n = P.n[slot];
-          pid = P.pid[slot];
-          pool_load(q, P, slot);
-          has = true;
+          const uint32_t n = P.n[slot];
+          ln.load(P, slot, G);
+          ctr = main_ctr(P.pid[slot], S.tag, A.key0, A.key1);
+          g = n >> 2;
+          jb = n & 3u;
           if (OBS) snap = next_snapshot(n, S);
         }
+        r_head += (uint32_t)__popcll(m_take);
+        m_has |= m_take;
       }
-      r_head += min((uint32_t)__popcll(m_empty), ready_cnt);
     }
     bool do_split = false;
-    if (__ballot(has) == 0ull) {
+    if (m_has == 0ull) {
       if (s_tail == s_head) {
         if (exhausted) break;
         continue;  // every particle claimed so far was dead: claim more
       }
       do_split = true;
     } else {
-      // A window of NG Philox groups of first sub-steps, starting at the
-      // group that holds the lane's next step (so a particle resumed after
-      // a split skips at most three steps of it).  Every lane runs the same
-      // straight-line code; a lane without a particle has no active step.
-      constexpr uint32_t NW = 4u * NG;
-      const uint32_t base = n & ~3u;
-      real W[NW];
-#pragma unroll
-      for (uint32_t g = 0; g < (uint32_t)NG; ++g) {
+      // Groups of four first sub-steps (one main-stream Philox block) until
+      // enough lanes wait for another particle.  Every lane runs the same
+      // straight-line code from the positions H[0] to H[4], past a vertex
+      // too; the lane masks of the proposals that stayed inside tell
+      // afterwards where a lane stopped, so a step carries no select, and a
+      // lane's state is taken back from H only if some lane of the wave
+      // stopped.  The first group after a pickup may start inside (jb > 0).
+      //
+      // Bound by VALU issue: a group of 64 lanes takes 97 VALU instructions
+      // without a hit (16 of them 64-bit products at half rate, 8
+      // transcendentals at a quarter), 24 a step, where windows of eight steps with a
+      // select per step took 39; what a hit adds (parking, the refill and
+      // its shorter first group, the split pass) is about 700 lane slots.
+      // FP32, 1000 steps of 3e7 particles on the vascular network (0.35 %
+      // hits a step) 23.0 -> 19.3 ms, 2000 steps of 1e7 on the 64-edge star
+      // 21.1 -> 20.4 ms (2.1 % hits), 30.7 -> 30.7 (7.1 %); FP64, 1e7 on the
+      // network 19.9 -> 18.9 ms.  More waves change nothing (five a SIMD run
+      // the network as fast as seven).
+      // How many lanes without a particle end the window: A.refill if there
+      // is (or can be claimed) a particle for them; as many as would fill a
+      // split pass, or leave A.idle lanes idle while particles are parked.
+      // (Only parking and finishing empty a lane, so no more than the newly
+      // empty lanes have joined the split queue.)
+      const int32_t ready0 = (int32_t)(r_tail - r_head), split0 = (int32_t)(s_tail - s_head);
+      const int32_t empty0 = lanes - (int32_t)__popcll(m_has);
+      const bool more = ready0 > 0 || (!exhausted && f_tail - f_head >= (uint32_t)kClaimMin);
+      const int32_t full = lanes - split0 + empty0;
+      const int32_t leave = min(min(more ? A.refill : ready0 + A.idle, full), lanes);
+      bool fresh = true;
+      int32_t groups = 0;
+      for (;;) {
         uint32_t k0 = A.key0, k1 = A.key1;
         fresh_keys<real>(k0, k1);
-        const U4 o = philox(pid, (base >> 2) + g, 0u, S.tag, k0, k1);
-        Q::box_muller(o.x, o.y, W[4 * g + 0], W[4 * g + 1]);
-        Q::box_muller(o.z, o.w, W[4 * g + 2], W[4 * g + 3]);
-      }
-      const uint32_t jb = n & 3u;  // = n - base
-      const uint32_t je = has ? min(NW, n_end - base) : 0u;
-      q.prep_window(W, jb, has);
-      int32_t pj = -1;
-      real wp = 0;
-      bool go = true;  // no vertex reached yet in this window
+        const U4 o = philox_main(ctr, g, k0, k1);
+        real W[4];
+        Q::box_muller(o.x, o.y, W[0], W[1]);
+        Q::box_muller(o.z, o.w, W[2], W[3]);
+        Pos H[5];
+        H[0] = ln.p;
+        uint64_t m_visit = 0ull;
+        if (fresh) {
+          const uint64_t m_fold = m_has & ln.on_vertex(ln.p);
+          if (m_fold != 0ull) {
+            if (in_mask(m_fold)) {
 #pragma unroll
-      for (uint32_t j = 0; j < NW; ++j) {
-        const bool act = (j >= jb) & (j < je) & go;
-        const bool in = q.fast_pred(W[j], act);
-        const bool hit = act & !in;
-        pj = hit ? (int32_t)j : pj;
-        wp = hit ? W[j] : wp;
-        go = go & !hit;
-        // a completed group's last step re-anchors
-        if ((j & 3u) == 3u) q.reanchor_if(act & in);
-        if (OBS && (act & in)) {
-          const uint32_t done = base + j + 1u;
-          if (done == snap) {
-            observe(q, S, sink);
-            snap = next_snapshot(done, S);
+              for (uint32_t j = 0; j < 4; ++j) W[j] = jb == j ? ln.fold(ln.p, W[j]) : W[j];
+            }
+          }
+          if constexpr (GEN == kGenFull) m_visit = ballot(ln.visits(ln.p));
+        }
+        uint64_t in[4];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          H[j + 1] = ln.propose(H[j], W[j]);
+          in[j] = ln.inside(H[j + 1]);
+          if (GEN == kGenFull && fresh) in[j] &= ~m_visit;
+          if (j < 3 && fresh) {
+            const uint64_t m_skip = ballot(jb > j);
+            H[j + 1] = pick(in_mask(m_skip), H[0], H[j + 1]);
+            in[j] |= m_skip;
           }
         }
+        // the launch's last group may end inside (part = 1 .. 3 steps of it)
+        const uint64_t m_last = ballot(g == g_last);
+        if (part) {
+          if (part < 2u) in[1] |= m_last;
+          if (part < 3u) in[2] |= m_last;
+          in[3] |= m_last;
+        }
+        const uint64_t stay = in[0] & in[1] & in[2] & in[3];
+        const uint64_t m_park = m_has & ~stay;
+        const uint64_t m_fin = m_has & stay & m_last;
+        // snapshots of the group's steps: the lanes that completed step m - 1
+        // and are at the snapshot count after it (after the fourth step, with
+        // the new reference end)
+        auto snapshot = [&](uint32_t m, uint64_t completed, const Pos &a) {
+          const uint64_t due = completed & ballot(snap == 4u * g + m);
+          if (due != 0ull) {
+            if (in_mask(due)) {
+              observe_at(ln.e, Ln::pos64(a, ln.side(), sink.e64[ln.e].L), S, sink);
+              snap = next_snapshot(snap, S);
+            }
+          }
+        };
+        const bool any_snap = OBS && (m_has & ballot(snap - 4u * g - 1u < 4u)) != 0ull;
+        if (OBS && any_snap) {
+          uint64_t c = m_has;
+#pragma unroll
+          for (uint32_t m = 1; m < 4; ++m) {
+            c &= in[m - 1];
+            if (part != 0u && m > part) c &= ~m_last;
+            snapshot(m, c, H[m]);
+          }
+        }
+        if (m_park != 0ull) {
+          // back to where the lane stopped: step j from H[j] with normal W[j]
+          if (in_mask(m_park)) {
+            uint32_t j = in_mask(in[2]) ? 3u : 2u;
+            Pos a = pick(in_mask(in[2]), H[3], H[2]);
+            real w = in_mask(in[2]) ? W[3] : W[2];
+            j = in_mask(in[1]) ? j : 1u;
+            a = pick(in_mask(in[1]), a, H[1]);
+            w = in_mask(in[1]) ? w : W[1];
+            j = in_mask(in[0]) ? j : 0u;
+            a = pick(in_mask(in[0]), a, H[0]);
+            w = in_mask(in[0]) ? w : W[0];
+            ln.store(P, slot, a);
+            P.n[slot] = 4u * g + j;
+            P.w[slot] = w;
+            P.split[(s_tail + lane_rank(m_park)) % K] = (uint8_t)slot;
+          }
+          s_tail += (uint32_t)__popcll(m_park);
+        }
+        ln.p = H[4];
+        if (part) {
+          const bool cut = in_mask(m_fin);
+          ln.p = pick(cut, pick(part == 1u, H[1], pick(part == 2u, H[2], H[3])), ln.p);
+          ln.reanchor(ln.p, !cut);
+        } else {
+          ln.reanchor(ln.p, true);
+        }
+        if (OBS && any_snap) snapshot(4u, m_has & stay & (part ? ~m_last : ~0ull), ln.p);
+        if (m_fin != 0ull) {
+          if (in_mask(m_fin)) {
+            const uint32_t id = P.pid[slot];
+            ln.write(S, id, ln.p, ln.state());
+            if constexpr (TRACE) {
+              S.seqhash[id] = P.hash[slot];
+              S.hits[id] = P.hits[slot];
+            }
+            t.steps += A.nsteps;
+            t.sub += A.nsteps;
+            P.freeq[(f_tail + lane_rank(m_fin)) % K] = (uint8_t)slot;
+          }
+          f_tail += (uint32_t)__popcll(m_fin);
+        }
+        m_has &= stay & ~m_last;
+        ++g;
+        jb = 0;
+        fresh = false;
+        ++groups;
+        wave_lds_fence();
+        if (lanes - (int32_t)__popcll(m_has) >= leave || groups == kMaxGroups) break;
       }
-      const bool parked = pj >= 0;
-      n = parked ? base + (uint32_t)pj : (has ? base + je : n);
-      const bool done_now = has & !parked & (n == n_end);
-      if (done_now) pool_finish(q, S, A, pid, t);
-      const uint64_t m_done = __ballot(done_now);
-      if (done_now) P.freeq[(f_tail + lane_rank(m_done)) % K] = (uint8_t)slot;
-      f_tail += (uint32_t)__popcll(m_done);
-      const uint64_t m_park = __ballot(parked);
-      if (parked) {
-        pool_store(q, P, slot, n);
-        P.w[slot] = wp;
-        P.k[slot] = 0;  // fresh: the whole step left, no slot drawn yet
-        P.split[(s_tail + lane_rank(m_park)) % K] = (uint8_t)slot;
-      }
-      s_tail += (uint32_t)__popcll(m_park);
-      has = has & !parked & !done_now;
-      wave_lds_fence();
-      const uint32_t empty = (uint32_t)__popcll(__ballot(!has));
-      const uint32_t ready_cnt = r_tail - r_head, split_cnt = s_tail - s_head;
-      const uint32_t idle = empty > ready_cnt ? empty - ready_cnt : 0u;
-      do_split = split_cnt >= 64u || (split_cnt > 0u && idle >= (uint32_t)A.idle);
+      const int32_t split_cnt = (int32_t)(s_tail - s_head);
+      const int32_t idle = lanes - (int32_t)__popcll(m_has) - (int32_t)(r_tail - r_head);
+      do_split = split_cnt >= lanes || (split_cnt > 0 && idle >= A.idle);
+      iter_lds += (uint32_t)groups;
     }
     if (do_split) {
+      ++iter_lds;
       // Up to 64 parked particles, one per lane, one crossing each.  The
       // lanes' own particles stay in registers meanwhile.
       const uint32_t B = min(s_tail - s_head, 64u);
@@ -2010,17 +2336,18 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
             freed = true;
           } else {
             pool_store(q2, P, s2, n2);
+            P.k[s2] = 0;
             back = true;
           }
         }
       }
-      const uint64_t m_freed = __ballot(freed);
+      const uint64_t m_freed = ballot(freed);
       if (freed) P.freeq[(f_tail + lane_rank(m_freed)) % K] = (uint8_t)s2;
       f_tail += (uint32_t)__popcll(m_freed);
-      const uint64_t m_again = __ballot(again);
+      const uint64_t m_again = ballot(again);
       if (again) P.split[(s_tail + lane_rank(m_again)) % K] = (uint8_t)s2;
       s_tail += (uint32_t)__popcll(m_again);
-      const uint64_t m_back = __ballot(back);
+      const uint64_t m_back = ballot(back);
       if (back) P.ready[(r_tail + lane_rank(m_back)) % K] = (uint8_t)s2;
       r_tail += (uint32_t)__popcll(m_back);
       wave_lds_fence();
@@ -2035,12 +2362,12 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
 template <int PW, bool FP64, bool TRACE>
 using PoolLds = std::conditional_t<FP64, PoolLds64<TRACE, PW>, PoolLds32<TRACE, PW>>;
 
-template <bool FP64, bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int NG, int GEN>
+template <bool FP64, bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN>
 __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
                                            const StepArgs &A, unsigned long long *s_tot,
                                            char *smem) {
   using Pool = PoolLds<PW, FP64, TRACE>;
-  using Q = std::conditional_t<FP64, Particle64<TRACE, LDS, GEN>, Particle32<TRACE, LDS, GEN>>;
+  using Ln = std::conditional_t<FP64, Lane64<TRACE, LDS, GEN>, Lane32<TRACE, LDS, GEN>>;
   uint32_t *s_exit = (uint32_t *)smem;
   if (threadIdx.x < 4) s_tot[threadIdx.x] = 0;
   if (LDS)
@@ -2058,24 +2385,24 @@ __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
   __syncthreads();
   Tally t{0, 0, 0, 0};
   const uint32_t wave = threadIdx.x >> 6;
-  run_pool<TRACE, LDS, OBS, PW, NG, GEN, Q>(view, G.E, S, A, pools[wave], s_exit, t, s_tot,
-                                            G.nnz, o);
+  run_pool<TRACE, LDS, OBS, PW, GEN, Ln>(view, G.E, S, A, pools[wave], s_exit, t, s_tot,
+                                         G.nnz, o);
   flush(S, t, s_tot, s_exit, G.nnz, LDS);
   if (OBS && A.obs_lds) flush_obs(S, o.lds, A.obs_lds);
 }
 
 #ifndef MG_POOL_WAVES_PER_EU
-#define MG_POOL_WAVES_PER_EU 7
+#define MG_POOL_WAVES_PER_EU 6
 #endif
 
 // GEN (cubic coefficients) is instantiated for pools of 128 with two
 // Philox groups per window only.
-template <bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int NG, int GEN = 0>
+template <bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN = 0>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL_WAVES_PER_EU)))
 void k_pool32(GraphDev G, SetDev S, StepArgs A) {
   extern __shared__ uint4 smem4[];
   __shared__ unsigned long long s_tot[4];
-  pool_block<false, TRACE, LDS, STAGED, OBS, PW, NG, GEN>(G, S, A, s_tot, (char *)smem4);
+  pool_block<false, TRACE, LDS, STAGED, OBS, PW, GEN>(G, S, A, s_tot, (char *)smem4);
 }
 
 // FP64 wave pools: the same schedule over FP64 particles (pools of 128,
@@ -2089,7 +2416,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL6
 void k_pool64(GraphDev G, SetDev S, StepArgs A) {
   extern __shared__ uint4 smem4[];
   __shared__ unsigned long long s_tot[4];
-  pool_block<true, TRACE, LDS, STAGED, OBS, kPoolSmall, 2, GEN>(G, S, A, s_tot, (char *)smem4);
+  pool_block<true, TRACE, LDS, STAGED, OBS, kPoolSmall, GEN>(G, S, A, s_tot, (char *)smem4);
 }
 
 // Batched form of the wave pools: a resident grid whose blocks take work
@@ -2100,7 +2427,7 @@ void k_pool64(GraphDev G, SetDev S, StepArgs A) {
 // run out.  An item of a set that has run out is passed over at the cost
 // of one load.  Both counters are cleared by k_batch_reset before each
 // launch.
-template <bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int NG, int GEN = 0>
+template <bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN = 0>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL_WAVES_PER_EU)))
 void k_pool32_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem *items,
                     StepArgs A) {
@@ -2127,7 +2454,7 @@ void k_pool32_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem 
     SetDev S = sets[set];
     S.n0 += A.n0_offset;  // steps already taken by earlier launches of this call
     const GraphDev G = graphs[set];
-    pool_block<false, TRACE, LDS, STAGED, OBS, PW, NG, GEN>(G, S, A, s_tot, (char *)smem4);
+    pool_block<false, TRACE, LDS, STAGED, OBS, PW, GEN>(G, S, A, s_tot, (char *)smem4);
   }
 }
 
@@ -2159,7 +2486,7 @@ void k_pool64_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem 
     SetDev S = sets[set];
     S.n0 += A.n0_offset;
     const GraphDev G = graphs[set];
-    pool_block<true, TRACE, LDS, STAGED, OBS, kPoolSmall, 2, GEN>(G, S, A, s_tot,
+    pool_block<true, TRACE, LDS, STAGED, OBS, kPoolSmall, GEN>(G, S, A, s_tot,
                                                                   (char *)smem4);
   }
 }
@@ -2175,12 +2502,12 @@ __global__ void k_batch_reset(const SetDev *sets, int32_t n_sets, uint32_t *clai
 
 // Autotuning probes: the FP32 step kernels under names of their own, so a
 // profile tells the probes apart from the launches they tune.
-template <bool LDS, bool STAGED, int PW, int NG>
+template <bool LDS, bool STAGED, int PW>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL_WAVES_PER_EU)))
 void k_pool32_probe(GraphDev G, SetDev S, StepArgs A) {
   extern __shared__ uint4 smem4[];
   __shared__ unsigned long long s_tot[4];
-  pool_block<false, false, LDS, STAGED, false, PW, NG, false>(G, S, A, s_tot, (char *)smem4);
+  pool_block<false, false, LDS, STAGED, false, PW, 0>(G, S, A, s_tot, (char *)smem4);
 }
 
 template <bool LDS, bool STAGED>
@@ -2448,17 +2775,13 @@ void with_gen(int32_t level, F &&f) {
     f(std::integral_constant<int, 0>{});
 }
 
-// Shape of an FP32 wave-pool schedule (StepArgs::kernel 1, 2, 3): particles
-// per wave and Philox groups per phase-A window.
+// Particles per wave of an FP32 wave-pool schedule (StepArgs::kernel 1, 2, 3).
 template <typename F>
 void with_pool(int32_t kernel, F &&f) {
-  using I = std::integral_constant<int, 1>;
   if (kernel == 2)
-    f(std::integral_constant<int, kPoolLarge>{}, I{});
-  else if (kernel == 3)
-    f(std::integral_constant<int, kPoolSmall>{}, std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, kPoolLarge>{});
   else
-    f(std::integral_constant<int, kPoolSmall>{}, I{});
+    f(std::integral_constant<int, kPoolSmall>{});
 }
 
 // LDS layout of a step block, shared by the host launchers and the
@@ -2496,6 +2819,51 @@ LdsPlan plan_lds(int32_t nnz, int32_t stage, size_t pools, const SetDev *obs_set
   return p;
 }
 
+// Compute units of the current device, looked up once.
+uint32_t device_cus() {
+  static std::mutex mu;
+  static int cus[kMaxDevices] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
+  std::lock_guard<std::mutex> lock(mu);
+  if (cus[dev] <= 0 &&
+      (hipDeviceGetAttribute(&cus[dev], hipDeviceAttributeMultiprocessorCount, dev) !=
+           hipSuccess ||
+       cus[dev] <= 0))
+    cus[dev] = 256;
+  return (uint32_t)cus[dev];
+}
+
+// Particles that a wave of a pool launch holds at a time, and the blocks
+// that the set then fills.  A full pool (two particles per lane) pays once
+// the set fills the chip's waves; below that a launch takes as long as one
+// wave needs for its share, so the set is spread over more waves: 16 or 32
+// particles each while that leaves at most one wave per SIMD, 64 (a particle
+// per lane) while it leaves at most two.  1000 steps, us, at 128 / 64 / 32 /
+// 16 particles a wave: 1e4 particles on the 3-edge star in FP64 1076 / 710 /
+// 669 / 658, on the 64-edge star in FP32 930 / 716 / 699 / 655; 3e4 (1114 /
+// 788 / 735 / 900, 939 / 729 / 711 / 735); 1e5 (1144 / 1006 / 1452 / 2090,
+// 964 / 822 / 1078 / 1465); 3e5 (1986 / 1914 / 3135 / -, 1266 / 1298 / 2065
+// / -).  The lanes that stand idle before a refill or a partial split pass
+// shrink with the pool.
+uint32_t set_pool(StepArgs &a, uint32_t n, int32_t pool) {
+  const uint32_t simds = 4u * device_cus();
+  uint32_t cap = (uint32_t)pool;
+  if (n <= 16u * simds)
+    cap = 16;
+  else if (n <= 32u * simds)
+    cap = 32;
+  else if (n <= 2u * 64u * simds)
+    cap = 64;
+  const int32_t lanes = (int32_t)std::min<uint32_t>(cap, 64u);
+  a.pool_cap = cap;
+  a.idle = std::max(1, a.idle * lanes / 64);
+  a.refill = std::max(1, a.refill * lanes / 64);
+  if (cap < (uint32_t)pool) a.claim_chunk = std::min(a.claim_chunk, cap);
+  const uint32_t per_block = cap * kWavesPerBlock;
+  return (n + per_block - 1) / per_block;
+}
+
 template <bool FP64, bool TRACE>
 hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                          hipStream_t st) {
@@ -2508,7 +2876,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                                   sizeof(PoolLds64<TRACE, kPoolSmall>) * kWavesPerBlock, &s,
                                   g.E);
       a.obs_lds = lp.obs_lds;
-      const uint32_t need = (s.n + kPoolSmall * kWavesPerBlock - 1) / (kPoolSmall * kWavesPerBlock);
+      const uint32_t need = set_pool(a, s.n, kPoolSmall);
       hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(64), 0, st, s.work);
       with_gen(g.gen, [&](auto Gn) {
         constexpr int gn = decltype(Gn)::value;
@@ -2525,25 +2893,25 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
     }
   }
   if (!FP64 && a.kernel >= 1 && (!g.gen || a.kernel == 3)) {
-    with_pool(a.kernel, [&](auto PWc, auto NGc) {
-      constexpr int PW = decltype(PWc)::value, NG = decltype(NGc)::value;
+    with_pool(a.kernel, [&](auto PWc) {
+      constexpr int PW = decltype(PWc)::value;
       const int32_t stage = g.stage_bytes32;
       const LdsPlan lp = plan_lds(g.nnz, stage, sizeof(PoolLds32<TRACE, PW>) * kWavesPerBlock,
                                   &s, g.E);
       a.obs_lds = lp.obs_lds;
-      const uint32_t need = (s.n + PW * kWavesPerBlock - 1) / (PW * kWavesPerBlock);
+      const uint32_t need = set_pool(a, s.n, PW);
       hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(64), 0, st, s.work);
       if (!TRACE && !obs && a.probe) {
         with_flags([&](auto L, auto T) {
           const void *f =
-              (const void *)k_pool32_probe<decltype(L)::value, decltype(T)::value, PW, NG>;
-          hipLaunchKernelGGL((k_pool32_probe<decltype(L)::value, decltype(T)::value, PW, NG>),
+              (const void *)k_pool32_probe<decltype(L)::value, decltype(T)::value, PW>;
+          hipLaunchKernelGGL((k_pool32_probe<decltype(L)::value, decltype(T)::value, PW>),
                              dim3(resident_blocks(f, lp.shm, need)), dim3(kBlock), lp.shm, st,
                              g, s, a);
         }, lp.lds_exit, lp.staged);
         return;
       }
-      if constexpr (PW == kPoolSmall && NG == 2) {
+      if constexpr (PW == kPoolSmall) {
         if (g.gen) {
           with_gen(g.gen, [&](auto Gn) {
             constexpr int gn = decltype(Gn)::value;
@@ -2551,9 +2919,9 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
               with_flags([&](auto L, auto T, auto O) {
                 const void *f =
                     (const void *)k_pool32<TRACE, decltype(L)::value, decltype(T)::value,
-                                           decltype(O)::value, PW, NG, gn>;
+                                           decltype(O)::value, PW, gn>;
                 hipLaunchKernelGGL((k_pool32<TRACE, decltype(L)::value, decltype(T)::value,
-                                             decltype(O)::value, PW, NG, gn>),
+                                             decltype(O)::value, PW, gn>),
                                    dim3(resident_blocks(f, lp.shm, need)), dim3(kBlock),
                                    lp.shm, st, g, s, a);
               }, lp.lds_exit, lp.staged, obs);
@@ -2563,9 +2931,9 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
       }
       with_flags([&](auto L, auto T, auto O) {
         const void *f = (const void *)k_pool32<TRACE, decltype(L)::value, decltype(T)::value,
-                                               decltype(O)::value, PW, NG>;
+                                               decltype(O)::value, PW>;
         hipLaunchKernelGGL((k_pool32<TRACE, decltype(L)::value, decltype(T)::value,
-                                     decltype(O)::value, PW, NG>),
+                                     decltype(O)::value, PW>),
                            dim3(resident_blocks(f, lp.shm, need)), dim3(kBlock), lp.shm, st,
                            g, s, a);
       }, lp.lds_exit, lp.staged, obs);
@@ -2605,8 +2973,8 @@ KernelLaunch batch_launch_t(int32_t n_items, int32_t max_nnz, int32_t max_stage,
   // FP32: the wave pools of the set's schedule (only pools of 128 with
   // 8-step windows for the general levels); FP64: its wave pools
   const bool pools = FP64 ? a.kernel == 3 : (a.kernel >= 1 && (!gen || a.kernel == 3));
-  with_pool(a.kernel, [&](auto PWc, auto NGc) {
-    constexpr int PW = decltype(PWc)::value, NG = decltype(NGc)::value;
+  with_pool(a.kernel, [&](auto PWc) {
+    constexpr int PW = decltype(PWc)::value;
     const size_t pool_bytes = FP64 ? sizeof(PoolLds64<TRACE, kPoolSmall>) * kWavesPerBlock
                                    : sizeof(PoolLds32<TRACE, PW>) * kWavesPerBlock;
     const LdsPlan lp = plan_lds(max_nnz, max_stage, pools ? pool_bytes : 0, nullptr, 0);
@@ -2619,9 +2987,9 @@ KernelLaunch batch_launch_t(int32_t n_items, int32_t max_nnz, int32_t max_stage,
           if constexpr (FP64) {
             k.func = (const void *)k_pool64_batch<TRACE, l, t, o, gn>;
           } else {
-            k.func = (const void *)k_pool32_batch<TRACE, l, t, o, PW, NG>;
-            if constexpr (PW == kPoolSmall && NG == 2 && gn != 0)
-              k.func = (const void *)k_pool32_batch<TRACE, l, t, o, PW, NG, gn>;
+            k.func = (const void *)k_pool32_batch<TRACE, l, t, o, PW>;
+            if constexpr (PW == kPoolSmall && gn != 0)
+              k.func = (const void *)k_pool32_batch<TRACE, l, t, o, PW, gn>;
           }
           // a resident grid takes the items from the batch's counter
           k.persistent = true;
