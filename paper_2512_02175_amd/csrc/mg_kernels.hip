@@ -41,6 +41,8 @@ constexpr int kWindowGroups32 = MG_WINDOW_GROUPS32;
 constexpr int kWindowGroups64 = MG_WINDOW_GROUPS64;
 constexpr uint64_t kFnvPrime = 0x100000001b3ull;
 
+#include "mg_bm64.inc"
+
 struct U4 {
   uint32_t x, y, z, w;
 };
@@ -135,61 +137,6 @@ __device__ __forceinline__ U4 philox_main(const MainCtr &m, uint32_t g, uint32_t
   return {c0, c1, c2, c3};
 }
 
-// Sine and cosine of t in [0, 2 pi) (the Box-Muller angle, t = 2 pi u with
-// u in (0, 1)): the argument is reduced by quarter turns, r = t - q pi/2
-// with pi/2 in two parts (Cody and Waite); for q <= 4 the first step
-// fma(-q, hi, t) is exact, so r carries the error of the second alone.
-// On |r| <= pi/4, sin r = r + r^3 P(r^2) and cos r = 1 - r^2/2 + r^4 C(r^2)
-// with P of degree 5 and C of degree 5, minimax polynomials for the
-// relative error of sine and cosine (Remez exchange; the fit is
-// minimax_fit.py beside this file): their approximation errors are below
-// 2^-57 and 2^-63 of the value, and Horner's rule with fused multiply-adds
-// keeps the result within one ulp of glibc's sin and cos on 2e7 angles
-// (the general library routine handles any argument and costs several
-// times as much).  The quadrant then picks and signs the two.
-__device__ __forceinline__ void sincos_small(double t, double &s_out, double &c_out) {
-  const double q = rint(t * 0.6366197723675814);
-  double r = fma(-q, 1.5707963267948966, t);
-  r = fma(-q, 6.123233995736766e-17, r);
-  const double x2 = r * r;
-  double ps = 1.5896230157095365e-10;  // P, highest degree first
-  ps = fma(ps, x2, -2.5050747762851854e-08);
-  ps = fma(ps, x2, 2.755731362138572e-06);
-  ps = fma(ps, x2, -0.0001984126982958954);
-  ps = fma(ps, x2, 0.008333333333322118);
-  ps = fma(ps, x2, -0.1666666666666663);
-  const double sn = fma(r * x2, ps, r);
-  double pc = -1.1358536524507801e-11;  // C, highest degree first
-  pc = fma(pc, x2, 2.087570084203873e-09);
-  pc = fma(pc, x2, -2.7557314179297243e-07);
-  pc = fma(pc, x2, 2.4801587288851707e-05);
-  pc = fma(pc, x2, -0.0013888888888873056);
-  pc = fma(pc, x2, 0.041666666666666595);
-  pc = fma(pc, x2, -0.5);
-  const double cs = fma(pc, x2, 1.0);
-  const int iq = (int)q & 3;
-  const bool swap = iq & 1;
-  const double a = swap ? cs : sn, b = swap ? sn : cs;
-  s_out = (iq >= 2) ? -a : a;
-  c_out = (iq == 1 || iq == 2) ? -b : b;
-}
-
-// Quotient n / d for d in [1, 4) and |n| < 1, where no range scaling,
-// overflow or special value can arise: the hardware reciprocal estimate
-// refined by two Newton-Raphson steps, the product, and one correction by
-// the residual (Markstein's sequence).  These are the device library's
-// division steps without its operand scaling and special-value fix-up,
-// which leave such operands unchanged, so the quotient is the library's.
-__device__ __forceinline__ double div_unit(double n, double d) {
-  double r = __builtin_amdgcn_rcp(d);
-  double e = fma(-d, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-d, r, 1.0);
-  r = fma(r, e, r);
-  const double q = n * r;
-  return fma(fma(-d, q, n), r, q);
-}
-
 // Square root of x in [2^-767, 2^1023) (normal, positive, finite): the
 // hardware reciprocal square root y refined in Markstein's coupled form
 // (g ~ sqrt(x) and h ~ 1/(2 sqrt(x)) updated together, then two residual
@@ -210,62 +157,100 @@ __device__ __forceinline__ double sqrt_normal(double x) {
   return fma(d, h, g);
 }
 
-// Natural logarithm of a Box-Muller uniform u in (0, 1) (no zero, infinite
-// or negative arguments reach it): u = 2^e m with m in [sqrt(1/2), sqrt(2))
-// shifted down by at most 3e-7 of itself (the split is decided on the high
-// word of the mantissa),
-// f = m - 1 (exact), s = f / (2 + f) (div_unit), and log(1 + f) = 2 atanh(s) written as
-// f - (f^2/2 - s (f^2/2 + R)), R = 2 atanh(s)/s - 2 = 2 z/3 + 2 z^2/5 + ...
-// in z = s^2 <= 0.0295, here z Q(z) with Q the degree-6 minimax polynomial
-// for R (Remez exchange; minimax_fit.py beside this file), whose error is
-// below 2^-59 of log(1 + f); e ln 2 with ln 2 in two parts (its first 32
-// bits, exact times e, and the rest).  Within 0.80 ulp of the exact value
-// on 2e7 draws of (a + 1/2) 2^-32 (the general library routine, with its
-// extended-precision steps, costs about twice as many FP64 operations).
-__device__ __forceinline__ double log_unit(double u) {
-  // exponent and mantissa from the bits: adding 2^20 (1 - sqrt(1/2)) to the
-  // high word carries into the exponent exactly when the mantissa's high
-  // word is at least sqrt 2's, which picks m in [sqrt(1/2), sqrt(2)) with
-  // integer operations alone (u is normal and positive)
-  const uint64_t bits = (uint64_t)__double_as_longlong(u);
-  const uint32_t hx = (uint32_t)(bits >> 32) + 0x00095f62u;
-  const int e = (int)(hx >> 20) - 0x3ff;
-  const double m = __longlong_as_double(
-      (long long)(((uint64_t)((hx & 0x000fffffu) + 0x3fe6a09eu) << 32) | (bits & 0xffffffffull)));
-  const double f = m - 1.0;
-  const double s = div_unit(f, 2.0 + f);
-  const double z = s * s;
-  double r = 0.1479594963458122;  // Q, highest degree first
-  r = fma(r, z, 0.15314050559867082);
-  r = fma(r, z, 0.18183564325758253);
-  r = fma(r, z, 0.22222198573192972);
-  r = fma(r, z, 0.2857142874238752);
-  r = fma(r, z, 0.3999999999941468);
-  r = fma(r, z, 0.6666666666666734);
-  r = r * z;
-  const double hfsq = 0.5 * f * f;
-  const double de = (double)e;
-  return fma(de, 0.6931471803691238, f - (hfsq - fma(s, hfsq + r, de * 1.9082149292705877e-10)));
+// The tables of the FP64 Box-Muller in a block's LDS: {c, -2 log(1/c)} by the
+// mantissa's interval; {cos a, sin a} and a by the 128th of a turn.
+struct alignas(16) BmLds {
+  double2 lg[128];
+  double2 cs[129];
+  double a[129];
+};
+__device__ __forceinline__ void stage_bm(BmLds *t) {
+  for (int32_t i = threadIdx.x; i < 129; i += blockDim.x) {
+    if (i < 128) t->lg[i] = make_double2(kLogTab[i][0], kLogTab[i][1]);
+    t->cs[i] = make_double2(kTurnTab[i][0], kTurnTab[i][1]);
+    t->a[i] = kTurnTab[i][2];
+  }
 }
 
-// Box-Muller in FP64: R = sqrt(-2 ln u1), angle 2 pi u2, u = (bits + 1/2) 2^-32.
-__device__ __forceinline__ void box_muller64(uint32_t a, uint32_t b, double &wc,
+// -2 ln u of the Box-Muller uniform u = (a + 1/2) 2^-32: u = 2^k m with m in
+// [45/64, 45/32), m's interval of 128 gives c ~ 1/m, z = m c - 1 (one
+// rounding) lies in [-2^-8, 2^-7), and -2 ln u = -2 (k ln 2 + ln(1/c)) - 2
+// log1p(z), with log1p(z) = z + z^2 q(z), q the degree-5 minimax polynomial
+// (error below 2^-59 of log1p; minimax_fit.py beside this file) and ln 2 in
+// two parts, whose first, times k, adds to the table's constant exactly.  c =
+// 1 and no constant in the two intervals at 1, so the relative error stays
+// small where the logarithm vanishes: within 0.82 ulp (0.29 ulp rms) on 4e6
+// draws.  14 FP64 operations and a table read; the series of atanh with a
+// division that it replaces took 30 (0.80 ulp, 0.30 rms).
+__device__ __forceinline__ double neg2log_unit(uint32_t a, const BmLds *t) {
+  const uint64_t bits = (uint64_t)__double_as_longlong(fma((double)a, 0x1p-32, 0x1p-33));
+  const uint32_t h = (uint32_t)(bits >> 32), d = h - 0x3fe68000u;
+  const double2 lg = t->lg[(d >> 13) & 127u];
+  const double k = (double)((int32_t)d >> 20);
+  const double m = __longlong_as_double(
+      (long long)(((uint64_t)(h - (d & 0xfff00000u)) << 32) | (bits & 0xffffffffull)));
+  const double z = fma(m, lg.x, -1.0);
+  double q = 0.13996369133691272;  // highest degree first
+  q = fma(q, z, -0.16665110133186214);
+  q = fma(q, z, 0.20000004212836844);
+  q = fma(q, z, -0.2500000003871666);
+  q = fma(q, z, 0.3333333333332643);
+  q = fma(q, z, -0.4999999999999981);
+  double r = fma(z * z, q, z);
+  r = fma(k, 1.9082149292705877e-10, r);
+  return fma(-2.0, r, fma(k, -1.3862943607382476, lg.y));
+}
+
+// Cosine and sine of the Box-Muller angle t = 2 pi u, u = (b + 1/2) 2^-32,
+// rounded to FP64 as it stands: the nearest 128th of a turn comes from the
+// integer; the table has an angle a close to it whose cosine and sine are
+// doubles to within 2^-62 (Gal's accurate tables), x = t - a is exact, and
+// the addition theorem takes sin x = x + x^3 s(x^2) and cos x - 1 = x^2
+// c(x^2), minimax polynomials of degree 2 (errors below 2^-64 for |x| <=
+// pi/128).  The results are rounded almost correctly.  17 FP64 operations
+// and two table reads where quarter turns and polynomials of degree 5 took
+// 23 and eight selects.
+__device__ __forceinline__ void sincos_turn(uint32_t b, const BmLds *t, double &s_out,
+                                            double &c_out) {
+  const uint32_t i = ((b >> 24) + 1u) >> 1;  // 0 .. 128
+  const double2 cs = t->cs[i];
+  const double x = kTwoPi * fma((double)b, 0x1p-32, 0x1p-33) - t->a[i];
+  const double x2 = x * x;
+  double p = -0.0001984095097329375;  // s, highest degree first
+  p = fma(p, x2, 0.008333333332219878);
+  p = fma(p, x2, -0.16666666666666655);
+  const double sx = fma(x * x2, p, x);
+  double c = -0.0013888601908199634;  // c, highest degree first
+  c = fma(c, x2, 0.0416666666566456);
+  c = fma(c, x2, -0.499999999999999);
+  c = c * x2;
+  c_out = cs.x + fma(-cs.y, sx, cs.x * c);
+  s_out = cs.y + fma(cs.x, sx, cs.y * c);
+}
+
+// Box-Muller in FP64: R = sqrt(-2 ln u1), angle 2 pi u2, u = (bits + 1/2)
+// 2^-32.  Against exact values on 6e6 draws a normal is off by 2.434e-16 rms
+// and 2.80e-15 at most, nearly all of it the rounding of the angle (2.459e-16
+// and 2.87e-15 with a series for the logarithm and polynomials on a quarter
+// turn; 2.429e-16 and 2.80e-15 with glibc's functions, whose normals it
+// equals in 97 % of draws, against 82 %).  In place of those the 64-edge
+// star takes 24.5 ms instead of 30.1 for 2000 steps of 4e6 particles at dt
+// 1e-2, 18.0 instead of 22.2 at 1e-3, and the vascular network 14.7 instead
+// of 18.9 for 1000 steps of 1e7: a group of four steps 190 VALU instructions
+// instead of 232, at the price of six LDS reads per lane.
+__device__ __forceinline__ void box_muller64(uint32_t a, uint32_t b, const BmLds *t, double &wc,
                                              double &ws) {
-  const double u1 = ((double)a + 0.5) * 0x1p-32;
-  const double u2 = ((double)b + 0.5) * 0x1p-32;
-  const double r = sqrt_normal(-2.0 * log_unit(u1));
+  const double r = sqrt_normal(neg2log_unit(a, t));
   double s, c;
-  sincos_small(kTwoPi * u2, s, c);
+  sincos_turn(b, t, s, c);
   wc = r * c;
   ws = r * s;
 }
 
-__device__ __forceinline__ double box_muller64_cos(uint32_t a, uint32_t b) {
-  const double u1 = ((double)a + 0.5) * 0x1p-32;
-  const double u2 = ((double)b + 0.5) * 0x1p-32;
+__device__ __forceinline__ double box_muller64_cos(uint32_t a, uint32_t b, const BmLds *t) {
   double s, c;
-  sincos_small(kTwoPi * u2, s, c);
-  return sqrt_normal(-2.0 * log_unit(u1)) * c;
+  sincos_turn(b, t, s, c);
+  return sqrt_normal(neg2log_unit(a, t)) * c;
 }
 
 // Box-Muller in FP32 on the transcendental unit: v_log_f32 is log2 and
@@ -434,10 +419,11 @@ struct GView {
   const WzRec *wz;        // global Wentzell table
   const TabRec64 *tab64;  // global tabulated-coefficient intervals
   const TabRec32 *tab32;
+  const BmLds *bm;        // FP64: the Box-Muller tables in LDS
 };
 
 __device__ __forceinline__ GView global_view(const GraphDev &G) {
-  return {G.vtx, G.slots, G.guide, G.e32, G.e64, G.e64, G.wz, G.tab64, G.tab32};
+  return {G.vtx, G.slots, G.guide, G.e32, G.e64, G.e64, G.wz, G.tab64, G.tab32, nullptr};
 }
 
 struct SlotPick {
@@ -578,8 +564,8 @@ __device__ __forceinline__ void step_loop(P &q, const SetDev &S, const StepArgs 
       uint32_t k0 = A.key0, k1 = A.key1;
       fresh_keys<typename P::real>(k0, k1);
       const U4 o = philox(pid, (base >> 2) + g, 0u, S.tag, k0, k1);
-      P::box_muller(o.x, o.y, W[4 * g + 0], W[4 * g + 1]);
-      P::box_muller(o.z, o.w, W[4 * g + 2], W[4 * g + 3]);
+      P::box_muller(o.x, o.y, q.G.bm, W[4 * g + 0], W[4 * g + 1]);
+      P::box_muller(o.z, o.w, q.G.bm, W[4 * g + 2], W[4 * g + 3]);
     }
     const uint32_t jb = n - base;
     const uint32_t je = min(NW, n_end - base);
@@ -667,8 +653,9 @@ struct Particle64 {
   uint32_t nhit;
   uint32_t death_step;
 
-  __device__ static void box_muller(uint32_t a, uint32_t b, double &c, double &s) {
-    box_muller64(a, b, c, s);
+  __device__ static void box_muller(uint32_t a, uint32_t b, const BmLds *t, double &c,
+                                    double &s) {
+    box_muller64(a, b, t, c, s);
   }
 
   // FP64 positions are always measured from the initial vertex.
@@ -871,7 +858,7 @@ struct Particle64 {
       }
       if (!done) {
         // the next sub-step, from the vertex (normal folded into the edge)
-        H.w = box_muller64_cos(hd.y, hd.z);
+        H.w = box_muller64_cos(hd.y, hd.z, G.bm);
         H.h = h;
         const double w2 = (sp.eo & 1u) ? -fabs(H.w) : fabs(H.w);
         const double mu2 = drift(x);
@@ -1052,7 +1039,7 @@ struct Particle32 {
     }
   }
 
-  __device__ static void box_muller(uint32_t a, uint32_t b, float &c, float &s) {
+  __device__ static void box_muller(uint32_t a, uint32_t b, const BmLds *, float &c, float &s) {
     box_muller32(a, b, c, s);
   }
 
@@ -1406,8 +1393,8 @@ __device__ __forceinline__ void flush_obs(const SetDev &S, const uint32_t *s_obs
 
 __device__ __forceinline__ int32_t align16(int32_t v) { return (v + 15) & ~15; }
 
-// Shared memory of a step block: [exit counters (LDS)][staged tables]
-// [snapshot bins (LDS)].
+// Shared memory of a step block: [FP64: Box-Muller tables][exit counters
+// (LDS)][staged tables][snapshot bins (LDS)].
 // Staged tables keep their relative layout: vertex blocks, slot table and
 // guide tables, then the edge records of the kernel's precision.
 template <bool FP64, bool STAGED>
@@ -1440,12 +1427,18 @@ template <bool FP64, bool TRACE, bool LDS, bool STAGED, bool OBS, int GEN>
 __device__ __forceinline__ void step_block(const GraphDev &G, const SetDev &S,
                                            const StepArgs &A, uint32_t pid,
                                            unsigned long long *s_tot, char *smem) {
+  BmLds *bm = (BmLds *)smem;
+  if (FP64) {
+    stage_bm(bm);
+    smem += sizeof(BmLds);
+  }
   uint32_t *s_exit = (uint32_t *)smem;
   if (threadIdx.x < 4) s_tot[threadIdx.x] = 0;
   if (LDS)
     for (int32_t s = threadIdx.x; s < G.nnz; s += blockDim.x) s_exit[s] = 0;
   const int32_t ex = LDS ? exit_bytes(G.nnz) : 0;
-  const GView view = block_view<FP64, STAGED>(G, smem + ex);
+  GView view = block_view<FP64, STAGED>(G, smem + ex);
+  if (FP64) view.bm = bm;
   ObsSink o{nullptr, G.e64};
   if (OBS && A.obs_lds) {
     o.lds = (uint32_t *)(smem + align16(ex + (STAGED ? (FP64 ? G.stage_bytes64
@@ -2188,8 +2181,8 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
         fresh_keys<real>(k0, k1);
         const U4 o = philox_main(ctr, g, k0, k1);
         real W[4];
-        Q::box_muller(o.x, o.y, W[0], W[1]);
-        Q::box_muller(o.z, o.w, W[2], W[3]);
+        Q::box_muller(o.x, o.y, G.bm, W[0], W[1]);
+        Q::box_muller(o.z, o.w, G.bm, W[2], W[3]);
         Pos H[5];
         H[0] = ln.p;
         uint64_t m_visit = 0ull;
@@ -2355,8 +2348,8 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
   }
 }
 
-// Shared memory of a pool block: [exit counters][staged tables][pools]
-// [snapshot bins].  Stages the set's tables, runs its particles until the
+// Shared memory of a pool block: [FP64: Box-Muller tables][exit counters]
+// [staged tables][pools][snapshot bins].  Stages the set's tables, runs its particles until the
 // set's counter has run out and the block's pools are empty, and adds the
 // block's counts to the set's counters.
 template <int PW, bool FP64, bool TRACE>
@@ -2368,12 +2361,18 @@ __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
                                            char *smem) {
   using Pool = PoolLds<PW, FP64, TRACE>;
   using Ln = std::conditional_t<FP64, Lane64<TRACE, LDS, GEN>, Lane32<TRACE, LDS, GEN>>;
+  BmLds *bm = (BmLds *)smem;
+  if (FP64) {
+    stage_bm(bm);
+    smem += sizeof(BmLds);
+  }
   uint32_t *s_exit = (uint32_t *)smem;
   if (threadIdx.x < 4) s_tot[threadIdx.x] = 0;
   if (LDS)
     for (int32_t s = threadIdx.x; s < G.nnz; s += blockDim.x) s_exit[s] = 0;
   const int32_t ex = LDS ? exit_bytes(G.nnz) : 0;
-  const GView view = block_view<FP64, STAGED>(G, smem + ex);
+  GView view = block_view<FP64, STAGED>(G, smem + ex);
+  if (FP64) view.bm = bm;
   const int32_t o_pools =
       align16(ex + (STAGED ? (FP64 ? G.stage_bytes64 : G.stage_bytes32) : 0));
   Pool *pools = (Pool *)(smem + o_pools);
@@ -2785,7 +2784,8 @@ void with_pool(int32_t kernel, F &&f) {
 }
 
 // LDS layout of a step block, shared by the host launchers and the
-// kernels' offsets: [exit counters][staged tables][pools][snapshot bins].
+// kernels' offsets: [FP64: Box-Muller tables][exit counters][staged
+// tables][pools][snapshot bins].
 // Within kLdsBlockMax bytes, exit counters come first (they take an atomic
 // per hit-step), staged tables next, snapshot bins last.
 struct LdsPlan {
@@ -2795,14 +2795,15 @@ struct LdsPlan {
   size_t shm;
 };
 
-LdsPlan plan_lds(int32_t nnz, int32_t stage, size_t pools, const SetDev *obs_set,
+LdsPlan plan_lds(bool fp64, int32_t nnz, int32_t stage, size_t pools, const SetDev *obs_set,
                  int32_t n_edges) {
   LdsPlan p{};
   p.lds_exit = nnz <= kLdsExitMax;
   p.staged = stage > 0;
   auto size = [&]() {
     const int32_t ex = p.lds_exit ? ((nnz * 4 + 15) & ~15) : 0;
-    const size_t b = (size_t)((ex + (p.staged ? stage : 0) + 15) & ~15) + pools;
+    const size_t b = (fp64 ? sizeof(BmLds) : 0) +
+                     (size_t)((ex + (p.staged ? stage : 0) + 15) & ~15) + pools;
     return (b + 15) & ~(size_t)15;
   };
   if (size() > (size_t)kLdsBlockMax) p.staged = false;
@@ -2872,7 +2873,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
   if constexpr (FP64) {
     if (a.kernel == 3) {
       // FP64 wave pools (128 per wave, 8-step windows) on a resident grid
-      const LdsPlan lp = plan_lds(g.nnz, g.stage_bytes64,
+      const LdsPlan lp = plan_lds(true, g.nnz, g.stage_bytes64,
                                   sizeof(PoolLds64<TRACE, kPoolSmall>) * kWavesPerBlock, &s,
                                   g.E);
       a.obs_lds = lp.obs_lds;
@@ -2896,7 +2897,8 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
     with_pool(a.kernel, [&](auto PWc) {
       constexpr int PW = decltype(PWc)::value;
       const int32_t stage = g.stage_bytes32;
-      const LdsPlan lp = plan_lds(g.nnz, stage, sizeof(PoolLds32<TRACE, PW>) * kWavesPerBlock,
+      const LdsPlan lp = plan_lds(false, g.nnz, stage,
+                                  sizeof(PoolLds32<TRACE, PW>) * kWavesPerBlock,
                                   &s, g.E);
       a.obs_lds = lp.obs_lds;
       const uint32_t need = set_pool(a, s.n, PW);
@@ -2941,7 +2943,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
     return hipGetLastError();
   }
   const int32_t stage = FP64 ? g.stage_bytes64 : g.stage_bytes32;
-  const LdsPlan lp = plan_lds(g.nnz, stage, 0, &s, g.E);
+  const LdsPlan lp = plan_lds(FP64, g.nnz, stage, 0, &s, g.E);
   a.obs_lds = lp.obs_lds;
   const uint32_t blocks = (s.n + kBlock - 1) / kBlock;
   if (!FP64 && !TRACE && !obs && a.probe) {
@@ -2977,7 +2979,7 @@ KernelLaunch batch_launch_t(int32_t n_items, int32_t max_nnz, int32_t max_stage,
     constexpr int PW = decltype(PWc)::value;
     const size_t pool_bytes = FP64 ? sizeof(PoolLds64<TRACE, kPoolSmall>) * kWavesPerBlock
                                    : sizeof(PoolLds32<TRACE, PW>) * kWavesPerBlock;
-    const LdsPlan lp = plan_lds(max_nnz, max_stage, pools ? pool_bytes : 0, nullptr, 0);
+    const LdsPlan lp = plan_lds(FP64, max_nnz, max_stage, pools ? pool_bytes : 0, nullptr, 0);
     k.shm = lp.shm;
     with_gen(gen, [&](auto Gn) {
       constexpr int gn = decltype(Gn)::value;
