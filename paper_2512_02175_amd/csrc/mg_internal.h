@@ -219,6 +219,7 @@ struct BatchItem {
 };
 
 constexpr int kBlock = 256;
+constexpr int kHistBlock = 1024;     // threads of an LDS histogram's block
 // FP32 wave pools hold 128 or 256 particles per wave (2 or 4 per lane); the
 // step schedule (StepArgs::kernel) picks: 0 one particle per lane, 1 pools
 // of 128, 2 pools of 256.
@@ -229,7 +230,8 @@ inline int pool_per_wave(int32_t kernel) { return kernel == 2 ? kPoolLarge : kPo
 constexpr int kLdsExitMax = 16384;  // slots counted in LDS (64 KiB of u32) when
                                     // the block's LDS budget allows
 constexpr int kLdsStageMax = 24576; // graph tables staged in LDS up to this size
-constexpr int kLdsHistMax = 16384;  // histogram bins privatised in LDS (64 KiB)
+constexpr int kLdsHistMax = 32768;  // histogram bins privatised in LDS (128 KiB)
+constexpr int kLdsHistEdges = 512;  // and edges whose binning it keeps beside them
 constexpr int kLdsObsMax = 4096;    // streamed-histogram bins privatised in LDS
 constexpr int kLdsBlockMax = 65536; // LDS bytes a step block may take
 
@@ -271,10 +273,10 @@ KernelLaunch batch_launch(int32_t n_items, int32_t max_nnz, int32_t max_stage,
 // its LDS plan), and whether that plan stages the tables.
 int32_t batch_blocks_per_cu(int32_t max_nnz, int32_t max_stage, const StepArgs &a, bool fp64,
                             bool trace, int32_t gen, bool *staged);
-// tiled: edge-range LDS tiles when E * nb exceeds one LDS copy (else 64-bit
-// global atomics); below that size both take the single LDS copy.
+// One LDS copy of the bins per block up to kLdsHistMax of them, else 64-bit
+// global atomics.
 hipError_t launch_histogram(const GraphDev &g, const SetDev &s, int32_t nb,
-                            uint64_t *out, bool fp64, bool tiled, hipStream_t st);
+                            uint64_t *out, bool fp64, hipStream_t st);
 hipError_t launch_histogram_csr(const GraphDev &g, const SetDev &s, const int32_t *off,
                                 const double *up, int32_t nbins, uint64_t *out, bool fp64,
                                 hipStream_t st);

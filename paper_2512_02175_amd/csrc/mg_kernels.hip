@@ -18,6 +18,7 @@
 //
 // Compiled with -ffp-contract=off: every fused multiply-add is explicit.
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -482,10 +483,12 @@ __device__ __forceinline__ void count_exit(uint32_t *s_exit, uint64_t *g_exit,
 // times the FP64 inverse bin width nb / span, rounded down, clamped to
 // [0, nb - 1] (the appendix histogram kernel, with x = span and anything
 // beyond in the last bin).
-__device__ __forceinline__ int32_t bin_of(double x, double span, int32_t nb) {
-  const double inv = (double)nb / span;
+__device__ __forceinline__ int32_t bin_at(double x, double inv, int32_t nb) {
   const double f = floor(x * inv);
   return f < 0.0 ? 0 : (f > (double)(nb - 1) ? nb - 1 : (int32_t)f);
+}
+__device__ __forceinline__ int32_t bin_of(double x, double span, int32_t nb) {
+  return bin_at(x, (double)nb / span, nb);
 }
 
 // Streamed histogram.  A snapshot adds every alive particle's bin at each
@@ -2629,76 +2632,117 @@ __global__ __launch_bounds__(kBlock) void k_init(GraphDev G, SetDev S, int mode,
 }
 
 // ----------------------------------------------------------- histogram --
-template <bool FP64, bool LDS>
-__global__ __launch_bounds__(kBlock) void k_hist(GraphDev G, SetDev S, int32_t nb,
-                                                 uint64_t *out) {
-  extern __shared__ uint32_t s_bin[];
-  const int32_t nbins = G.E * nb;
-  if (LDS) {
-    for (int32_t b = threadIdx.x; b < nbins; b += blockDim.x) s_bin[b] = 0;
-    __syncthreads();
-  }
-  const uint32_t stride = gridDim.x * kBlock;
-  for (uint32_t pid = blockIdx.x * kBlock + threadIdx.x; pid < S.n; pid += stride) {
-    const uint32_t ef = S.ef[pid];
-    if (ef & kDeadBit) continue;
-    const int32_t e = (int32_t)(ef & kEdgeMask);
-    const EdgeRec64 &r = G.e64[e];
-    double x;
+// The four particles 4 i .. 4 i + 3 of a set (those below n): state words and
+// positions in one wide load each.
+template <bool FP64>
+struct Quad {
+  uint32_t ef[4];
+  double2 x[2];   // FP64
+  float4 y[2];    // FP32
+  __device__ __forceinline__ void load(const SetDev &S, uint32_t i) {
+    const uint4 e = ((const uint4 *)S.ef)[i];
+    ef[0] = e.x, ef[1] = e.y, ef[2] = e.z, ef[3] = e.w;
     if (FP64) {
-      x = S.x64[pid];
+      x[0] = ((const double2 *)S.x64)[2 * i];
+      x[1] = ((const double2 *)S.x64)[2 * i + 1];
     } else {
-      const float2 yy = S.y32[pid];
-      const double y = (double)yy.x + (double)yy.y;
-      x = (ef & kSideBit) ? r.L - y : y;
+      y[0] = ((const float4 *)S.y32)[2 * i];
+      y[1] = ((const float4 *)S.y32)[2 * i + 1];
     }
-    const int32_t idx = e * nb + bin_of(x, r.span, nb);
-    if (LDS)
-      atomicAdd(&s_bin[idx], 1u);
-    else
-      atomicAdd((unsigned long long *)&out[idx], 1ull);
   }
-  if (LDS) {
-    __syncthreads();
-    for (int32_t b = threadIdx.x; b < nbins; b += blockDim.x)
-      if (s_bin[b]) atomicAdd((unsigned long long *)&out[b], (unsigned long long)s_bin[b]);
+  __device__ __forceinline__ void load_tail(const SetDev &S, uint32_t first) {
+    for (uint32_t k = 0; k < 4; ++k) {
+      const uint32_t id = first + k;
+      ef[k] = id < S.n ? S.ef[id] : kDeadBit;
+      const uint32_t at = id < S.n ? id : first;
+      if (FP64) {
+        const double v = S.x64[at];
+        (k & 1u ? x[k >> 1].y : x[k >> 1].x) = v;
+      } else {
+        const float2 v = S.y32[at];
+        if (k & 1u)
+          y[k >> 1].z = v.x, y[k >> 1].w = v.y;
+        else
+          y[k >> 1].x = v.x, y[k >> 1].y = v.y;
+      }
+    }
+  }
+  // position of particle k from the initial vertex of its edge of length L
+  __device__ __forceinline__ double pos(uint32_t k, double L) const {
+    if (FP64) return k & 1u ? x[k >> 1].y : x[k >> 1].x;
+    const float4 &v = y[k >> 1];
+    const double d = k & 1u ? (double)v.z + (double)v.w : (double)v.x + (double)v.y;
+    return (ef[k] & kSideBit) ? L - d : d;
+  }
+};
+
+// Calls f(quad, k) for every alive particle of the set, four per thread and
+// turn, over the whole grid.
+template <bool FP64, typename F>
+__device__ __forceinline__ void for_alive(const SetDev &S, F &&f) {
+  const uint32_t quads = S.n / 4u, stride = gridDim.x * blockDim.x;
+  Quad<FP64> q;
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < quads; i += stride) {
+    q.load(S, i);
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+      if (!(q.ef[k] & kDeadBit)) f(q, k);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0 && (S.n & 3u)) {
+    q.load_tail(S, 4u * quads);
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+      if (!(q.ef[k] & kDeadBit)) f(q, k);
   }
 }
 
-// Histogram too large for one LDS copy, in edge-range tiles: blockIdx.y
-// picks a range of whole edges whose bins fit in LDS, and the block counts
-// only the particles on those edges (the state word decides; the position
-// is read only for them), then merges its u32 counts into the u64 bins.
-template <bool FP64>
-__global__ __launch_bounds__(kBlock) void k_hist_tiled(GraphDev G, SetDev S, int32_t nb,
-                                                       int32_t edges_per_tile, uint64_t *out) {
-  extern __shared__ uint32_t s_bin[];
-  const int32_t e0 = (int32_t)blockIdx.y * edges_per_tile;
-  const int32_t e1 = min(G.E, e0 + edges_per_tile);
-  const int32_t nbins = (e1 - e0) * nb;
-  for (int32_t b = threadIdx.x; b < nbins; b += blockDim.x) s_bin[b] = 0;
-  __syncthreads();
-  const uint32_t stride = gridDim.x * kBlock;
-  for (uint32_t pid = blockIdx.x * kBlock + threadIdx.x; pid < S.n; pid += stride) {
-    const uint32_t ef = S.ef[pid];
-    if (ef & kDeadBit) continue;
-    const int32_t e = (int32_t)(ef & kEdgeMask);
-    if (e < e0 || e >= e1) continue;
-    const EdgeRec64 &r = G.e64[e];
-    double x;
-    if (FP64) {
-      x = S.x64[pid];
-    } else {
-      const float2 yy = S.y32[pid];
-      const double y = (double)yy.x + (double)yy.y;
-      x = (ef & kSideBit) ? r.L - y : y;
-    }
-    atomicAdd(&s_bin[(e - e0) * nb + bin_of(x, r.span, nb)], 1u);
-  }
-  __syncthreads();
-  uint64_t *o = out + (int64_t)e0 * nb;
+// Adds a block's LDS bins to the u64 counters.
+__device__ __forceinline__ void merge_bins(const uint32_t *s_bin, int32_t nbins, uint64_t *out) {
   for (int32_t b = threadIdx.x; b < nbins; b += blockDim.x)
-    if (s_bin[b]) atomicAdd((unsigned long long *)&o[b], (unsigned long long)s_bin[b]);
+    if (s_bin[b]) atomicAdd((unsigned long long *)&out[b], (unsigned long long)s_bin[b]);
+}
+
+// Uniform bins in LDS: [the edges' {length, inverse bin width}][bins].  Bound
+// by the latency of its loads (few blocks fit beside a copy of the bins), so
+// 16 waves share a copy and a thread takes four particles per turn, and the
+// inverse widths are made once per block: 1e7 particles on 64 edges of 256
+// bins 34 us, where one particle per turn in blocks of four waves took 111;
+// 1e6 particles 57 -> 10 us.
+template <bool FP64>
+__global__ __launch_bounds__(kHistBlock) void k_hist_lds(GraphDev G, SetDev S, int32_t nb,
+                                                         int32_t edges, uint64_t *out) {
+  extern __shared__ uint4 smem4[];
+  const int32_t nbins = G.E * nb;
+  double2 *s_edge = (double2 *)smem4;   // edges = G.E, or 0: from the records
+  uint32_t *s_bin = (uint32_t *)(s_edge + edges);
+  for (int32_t b = threadIdx.x; b < nbins; b += blockDim.x) s_bin[b] = 0;
+  for (int32_t e = threadIdx.x; e < edges; e += blockDim.x)
+    s_edge[e] = make_double2(G.e64[e].L, (double)nb / G.e64[e].span);
+  __syncthreads();
+  for_alive<FP64>(S, [&](const Quad<FP64> &q, uint32_t k) {
+    const int32_t e = (int32_t)(q.ef[k] & kEdgeMask);
+    const double2 r = edges ? s_edge[e]
+                            : make_double2(G.e64[e].L, (double)nb / G.e64[e].span);
+    atomicAdd(&s_bin[e * nb + bin_at(q.pos(k, r.x), r.y, nb)], 1u);
+  });
+  __syncthreads();
+  merge_bins(s_bin, nbins, out);
+}
+
+// Uniform bins too many for LDS: 64-bit global atomics, about 2.2e10 a
+// second whatever the number of bins beyond 32768 (1e7 particles 430 us, 1e8
+// 4.55 ms).  Passing over the particles once per range of edges whose bins
+// fit in LDS loses to them: 128000 bins 680 us for 1e7 particles, 262144 bins
+// 1.2 ms, 1.7e6 bins 57 ms for 1e8.
+template <bool FP64>
+__global__ __launch_bounds__(kBlock) void k_hist_global(GraphDev G, SetDev S, int32_t nb,
+                                                        uint64_t *out) {
+  for_alive<FP64>(S, [&](const Quad<FP64> &q, uint32_t k) {
+    const int32_t e = (int32_t)(q.ef[k] & kEdgeMask);
+    const EdgeRec64 &r = G.e64[e];
+    const int32_t idx = e * nb + bin_of(q.pos(k, r.L), r.span, nb);
+    atomicAdd((unsigned long long *)&out[idx], 1ull);
+  });
 }
 
 // Histogram over per-edge bins of any widths (the appendix's general
@@ -2707,27 +2751,18 @@ __global__ __launch_bounds__(kBlock) void k_hist_tiled(GraphDev G, SetDev S, int
 // x takes the first bin whose upper boundary is >= x (binary search), or the
 // edge's last bin.
 template <bool FP64, bool LDS>
-__global__ __launch_bounds__(kBlock) void k_hist_csr(GraphDev G, SetDev S, const int32_t *off,
-                                                     const double *up, int32_t nbins,
-                                                     uint64_t *out) {
-  extern __shared__ uint32_t s_bin[];
+__global__ __launch_bounds__(kHistBlock) void k_hist_csr(GraphDev G, SetDev S,
+                                                         const int32_t *off, const double *up,
+                                                         int32_t nbins, uint64_t *out) {
+  extern __shared__ uint4 smem4[];
+  uint32_t *s_bin = (uint32_t *)smem4;
   if (LDS) {
     for (int32_t b = threadIdx.x; b < nbins; b += blockDim.x) s_bin[b] = 0;
     __syncthreads();
   }
-  const uint32_t stride = gridDim.x * kBlock;
-  for (uint32_t pid = blockIdx.x * kBlock + threadIdx.x; pid < S.n; pid += stride) {
-    const uint32_t ef = S.ef[pid];
-    if (ef & kDeadBit) continue;
-    const int32_t e = (int32_t)(ef & kEdgeMask);
-    double x;
-    if (FP64) {
-      x = S.x64[pid];
-    } else {
-      const float2 yy = S.y32[pid];
-      const double y = (double)yy.x + (double)yy.y;
-      x = (ef & kSideBit) ? G.e64[e].L - y : y;
-    }
+  for_alive<FP64>(S, [&](const Quad<FP64> &q, uint32_t k) {
+    const int32_t e = (int32_t)(q.ef[k] & kEdgeMask);
+    const double x = q.pos(k, FP64 ? 0.0 : G.e64[e].L);
     int32_t lo = off[e], hi = off[e + 1] - 1;  // the answer lies in [lo, hi]
     while (lo < hi) {
       const int32_t mid = (lo + hi) >> 1;
@@ -2740,11 +2775,10 @@ __global__ __launch_bounds__(kBlock) void k_hist_csr(GraphDev G, SetDev S, const
       atomicAdd(&s_bin[lo], 1u);
     else
       atomicAdd((unsigned long long *)&out[lo], 1ull);
-  }
+  });
   if (LDS) {
     __syncthreads();
-    for (int32_t b = threadIdx.x; b < nbins; b += blockDim.x)
-      if (s_bin[b]) atomicAdd((unsigned long long *)&out[b], (unsigned long long)s_bin[b]);
+    merge_bins(s_bin, nbins, out);
   }
 }
 
@@ -3061,17 +3095,27 @@ KernelLaunch batch_launch(int32_t n_items, int32_t max_nnz, int32_t max_stage,
                : batch_launch_t<false, false>(n_items, max_nnz, max_stage, a, obs, gen);
 }
 
+// Blocks of an LDS histogram: reading falls with their number, merging their
+// copies into the counters grows with it, so the best number goes with the
+// square root of particles per bin (16384 bins: 64 blocks for 1e6 particles
+// 10 us, 16 blocks 15, 512 blocks 27; 128 for 1e7 34 us, 16 blocks 148, 512
+// blocks 68).
+static uint32_t lds_hist_blocks(uint32_t n, int64_t nbins) {
+  const double best = 5.0 * std::sqrt((double)n / (double)std::max<int64_t>(nbins, 1));
+  const uint32_t most = std::min((n + 4095u) / 4096u, 512u);
+  return std::max(1u, std::min((uint32_t)best, most));
+}
+
 hipError_t launch_histogram_csr(const GraphDev &g, const SetDev &s, const int32_t *off,
                                 const double *up, int32_t nbins, uint64_t *out, bool fp64,
                                 hipStream_t st) {
   const bool lds = nbins <= kLdsHistMax;
-  uint32_t blocks = (s.n + kBlock - 1) / kBlock;
-  if (lds && blocks > 1024) blocks = 1024;
-  if (!lds && blocks > 8192) blocks = 8192;
   const size_t shm = lds ? (size_t)nbins * 4 : 0;
+  const uint32_t blocks =
+      lds ? lds_hist_blocks(s.n, nbins) : std::min((s.n + 4095u) / 4096u, 2048u);
   with_flags([&](auto F, auto L) {
     hipLaunchKernelGGL((k_hist_csr<decltype(F)::value, decltype(L)::value>), dim3(blocks),
-                       dim3(kBlock), shm, st, g, s, off, up, nbins, out);
+                       dim3(kHistBlock), shm, st, g, s, off, up, nbins, out);
   }, fp64, lds);
   return hipGetLastError();
 }
@@ -3092,35 +3136,22 @@ hipError_t launch_fill_zero_u64(uint64_t *p, int64_t n, hipStream_t st) {
 }
 
 hipError_t launch_histogram(const GraphDev &g, const SetDev &s, int32_t nb,
-                            uint64_t *out, bool fp64, bool tiled, hipStream_t st) {
+                            uint64_t *out, bool fp64, hipStream_t st) {
   const int64_t nbins = (int64_t)g.E * nb;
-  if (tiled && nbins > kLdsHistMax && nb <= kLdsHistMax) {
-    const int32_t ept = kLdsHistMax / nb;
-    const uint32_t tiles = (uint32_t)((g.E + ept - 1) / ept);
-    uint32_t bx = (s.n + kBlock - 1) / kBlock;
-    const uint32_t want = std::max<uint32_t>(1u, 4096u / tiles);  // ~4096 blocks in all
-    if (bx > want) bx = want;
-    const size_t shm = (size_t)ept * nb * 4;
-    if (fp64)
-      hipLaunchKernelGGL((k_hist_tiled<true>), dim3(bx, tiles), dim3(kBlock), shm, st, g, s, nb,
-                         ept, out);
-    else
-      hipLaunchKernelGGL((k_hist_tiled<false>), dim3(bx, tiles), dim3(kBlock), shm, st, g, s, nb,
-                         ept, out);
+  if (nbins <= kLdsHistMax) {
+    const int32_t edges = g.E <= kLdsHistEdges ? g.E : 0;
+    const size_t shm = (size_t)nbins * 4 + (size_t)edges * 16;
+    with_flags([&](auto F) {
+      hipLaunchKernelGGL((k_hist_lds<decltype(F)::value>), dim3(lds_hist_blocks(s.n, nbins)),
+                         dim3(kHistBlock), shm, st, g, s, nb, edges, out);
+    }, fp64);
     return hipGetLastError();
   }
-  const bool lds = nbins <= kLdsHistMax;
-  uint32_t blocks = (s.n + kBlock - 1) / kBlock;
-  if (lds && blocks > 1024) blocks = 1024;  // amortise the LDS merge
-  if (!lds && blocks > 8192) blocks = 8192;
-  const size_t shm = lds ? (size_t)nbins * 4 : 0;
-  if (fp64) {
-    if (lds) hipLaunchKernelGGL((k_hist<true, true>), dim3(blocks), dim3(kBlock), shm, st, g, s, nb, out);
-    else hipLaunchKernelGGL((k_hist<true, false>), dim3(blocks), dim3(kBlock), shm, st, g, s, nb, out);
-  } else {
-    if (lds) hipLaunchKernelGGL((k_hist<false, true>), dim3(blocks), dim3(kBlock), shm, st, g, s, nb, out);
-    else hipLaunchKernelGGL((k_hist<false, false>), dim3(blocks), dim3(kBlock), shm, st, g, s, nb, out);
-  }
+  const uint32_t blocks = std::min((s.n + 4 * kBlock - 1) / (4 * kBlock), 8192u);
+  with_flags([&](auto F) {
+    hipLaunchKernelGGL((k_hist_global<decltype(F)::value>), dim3(blocks), dim3(kBlock), 0, st, g,
+                       s, nb, out);
+  }, fp64);
   return hipGetLastError();
 }
 
