@@ -722,7 +722,13 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
   const size_t o_wz = align_up(o_lt + 8 * (size_t)E, 256);
   const size_t o_t64 = align_up(o_wz + sizeof(WzRec) * wzt.size(), 256);
   const size_t o_t32 = align_up(o_t64 + sizeof(TabRec64) * tab64.size(), 256);
-  const size_t total = align_up(o_t32 + sizeof(TabRec32) * tab32.size(), 256);
+  const size_t hashed = align_up(o_t32 + sizeof(TabRec32) * tab32.size(), 256);
+  // behind what the fingerprint covers: the FP32 path's higher terms (the
+  // records' own, rounded) and its tabulated intervals, as the kernels stage
+  // them
+  const size_t o_hi = hashed;
+  const size_t o_x32 = o_hi + (g->gen ? sizeof(EdgeHi32) * E : 0);
+  const size_t total = align_up(o_x32 + sizeof(TabRec32) * tab32.size(), 256);
   hipError_t he = hipMalloc(&g->dev, total);
   if (he != hipSuccess) {
     delete g;
@@ -741,6 +747,17 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
     std::memcpy(host.data() + o_t64, tab64.data(), sizeof(TabRec64) * tab64.size());
     std::memcpy(host.data() + o_t32, tab32.data(), sizeof(TabRec32) * tab32.size());
   }
+  if (g->gen) {
+    std::vector<EdgeHi32> hi(E);
+    for (int32_t e = 0; e < E; ++e) {
+      const EdgeRec64 &r = e64[e];
+      hi[e] = {(float)r.c2, (float)r.c3, (float)r.s1, (float)r.s2, (float)r.s3,
+               (float)r.inv_h, r.tab0, r.tab_k};
+    }
+    std::memcpy(host.data() + o_hi, hi.data(), sizeof(EdgeHi32) * E);
+    if (!tab32.empty())
+      std::memcpy(host.data() + o_x32, tab32.data(), sizeof(TabRec32) * tab32.size());
+  }
   he = hipMemcpy(base, host.data(), total, hipMemcpyHostToDevice);
   if (he != hipSuccess) {
     (void)hipFree(g->dev);
@@ -749,7 +766,7 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
   }
   {
     uint64_t h = 0xcbf29ce484222325ull;
-    for (char c : host) h = (h ^ (uint8_t)c) * 0x100000001b3ull;
+    for (size_t i = 0; i < hashed; ++i) h = (h ^ (uint8_t)host[i]) * 0x100000001b3ull;
     g->fingerprint = h;
   }
   g->gd.tables = base;
@@ -761,7 +778,8 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
   g->gd.len_thr = (const uint64_t *)(base + o_lt);
   g->gd.wz = wzt.empty() ? nullptr : (const WzRec *)(base + o_wz);
   g->gd.tab64 = tab64.empty() ? nullptr : (const TabRec64 *)(base + o_t64);
-  g->gd.tab32 = tab32.empty() ? nullptr : (const TabRec32 *)(base + o_t32);
+  g->gd.tab32 = tab32.empty() ? nullptr : (const TabRec32 *)(base + o_x32);
+  g->gd.hi32 = g->gen ? (const EdgeHi32 *)(base + o_hi) : nullptr;
   g->gd.n_guide = (int32_t)ng;
   g->gd.o_vtx = (int32_t)o_vtx;
   g->gd.o_slots = (int32_t)o_sl;
@@ -772,6 +790,14 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
   const size_t st64 = o_32 + sizeof(EdgeRec64) * E;
   g->gd.stage_bytes32 = st32 <= (size_t)kLdsStageMax ? (int32_t)st32 : 0;
   g->gd.stage_bytes64 = st64 <= (size_t)kLdsStageMax ? (int32_t)st64 : 0;
+  // the higher terms and tabulated intervals join the staged tables when all
+  // of them fit
+  const size_t x32 = g->gen ? sizeof(EdgeHi32) * E + sizeof(TabRec32) * tab32.size() : 0;
+  const size_t x64 = sizeof(TabRec64) * tab64.size();
+  g->gd.x_bytes32 = st32 + x32 <= (size_t)kLdsStageMax ? (int32_t)x32 : 0;
+  g->gd.x_bytes64 = st64 + x64 <= (size_t)kLdsStageMax ? (int32_t)x64 : 0;
+  g->gd.stage_bytes32 += g->gd.x_bytes32;
+  g->gd.stage_bytes64 += g->gd.x_bytes64;
   g->gd.V = V;
   g->gd.E = E;
   g->gd.nnz = nnz;

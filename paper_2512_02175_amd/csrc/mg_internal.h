@@ -68,6 +68,13 @@ struct alignas(16) EdgeRec32 {
   float near;
 };
 
+// The FP32 path's higher coefficient terms of an edge (graphs of the general
+// levels): the FP64 record's, rounded.
+struct alignas(16) EdgeHi32 {
+  float c2, c3, s1, s2, s3, inv_h;
+  int32_t tab0, tab_k;
+};
+
 // Vertex block, 32 bytes: everything a vertex hit needs in one load.
 //   first  global id of the vertex's first CSR slot (slot s = first + k);
 //   deg    number of slots, -1 for an absorbing vertex.
@@ -124,8 +131,11 @@ struct GraphDev {
   int32_t V, E, nnz, n_guide;
   // byte offsets of vtx, slots, guide, e32, e64 inside `tables`
   int32_t o_vtx, o_slots, o_guide, o_e32, o_e64;
-  int32_t stage_bytes32;  // vtx..e32 (FP32 kernels stage this range)
-  int32_t stage_bytes64;  // vtx..guide + e64 (FP64 kernels)
+  int32_t stage_bytes32;  // vtx..e32 (FP32 kernels stage this range) + x_bytes32
+  int32_t stage_bytes64;  // vtx..guide + e64 (FP64 kernels) + x_bytes64
+  // of which, on graphs of the general levels whose tables fit with them, the
+  // higher terms and tabulated intervals (hi32 and tab32, contiguous; tab64)
+  int32_t x_bytes32, x_bytes64;
   // method-variant level: 0 affine coefficients and standard, absorbing or
   // mirror vertices; kGenCubic some edge has higher (cubic) drift or
   // diffusion terms; kGenFull some edge is tabulated or some vertex is a
@@ -137,6 +147,7 @@ struct GraphDev {
   const WzRec *wz;        // Wentzell table (rows named by VtxBlk::wz), or null
   const TabRec64 *tab64;  // tabulated-coefficient intervals, or null
   const TabRec32 *tab32;
+  const EdgeHi32 *hi32;   // [E] higher terms of the FP32 path, or null (affine)
 };
 
 // Counters of one particle set: exit[nnz], absorbed[V], totals[4]

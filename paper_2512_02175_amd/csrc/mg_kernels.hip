@@ -415,8 +415,7 @@ struct GView {
   const int32_t *guide;
   const EdgeRec32 *e32;
   const EdgeRec64 *e64;
-  const EdgeRec64 *hi64;  // global FP64 records: the FP32 path reads the
-                          // higher coefficient terms from them
+  const EdgeHi32 *hi32;   // the FP32 path's higher coefficient terms
   const WzRec *wz;        // global Wentzell table
   const TabRec64 *tab64;  // global tabulated-coefficient intervals
   const TabRec32 *tab32;
@@ -424,7 +423,7 @@ struct GView {
 };
 
 __device__ __forceinline__ GView global_view(const GraphDev &G) {
-  return {G.vtx, G.slots, G.guide, G.e32, G.e64, G.e64, G.wz, G.tab64, G.tab32, nullptr};
+  return {G.vtx, G.slots, G.guide, G.e32, G.e64, G.hi32, G.wz, G.tab64, G.tab32, nullptr};
 }
 
 struct SlotPick {
@@ -987,14 +986,14 @@ struct Particle32 {
     ad = as * dt;
     gs = side ? -g0 : g0;
     if constexpr (GEN) {
-      const EdgeRec64 &P = G.hi64[e];
-      c2 = (float)P.c2;
-      c3 = (float)P.c3;
-      s1 = (float)P.s1;
-      s2 = (float)P.s2;
-      s3 = (float)P.s3;
+      const EdgeHi32 P = G.hi32[e];
+      c2 = P.c2;
+      c3 = P.c3;
+      s1 = P.s1;
+      s2 = P.s2;
+      s3 = P.s3;
       if constexpr (GEN == kGenFull) {
-        inv_h = (float)P.inv_h;
+        inv_h = P.inv_h;
         tab0 = P.tab0;
         tab_k = P.tab_k;
       }
@@ -1399,11 +1398,20 @@ __device__ __forceinline__ int32_t align16(int32_t v) { return (v + 15) & ~15; }
 // Shared memory of a step block: [FP64: Box-Muller tables][exit counters
 // (LDS)][staged tables][snapshot bins (LDS)].
 // Staged tables keep their relative layout: vertex blocks, slot table and
-// guide tables, then the edge records of the kernel's precision.
-template <bool FP64, bool STAGED>
+// guide tables, then the edge records of the kernel's precision; on graphs of
+// the general levels the higher terms and tabulated intervals follow, if the
+// host found that all of them fit (each step evaluates them: from global
+// memory a load of L2 latency per step and coefficient).  1000 steps, 8
+// tabulated edges of 16 intervals, 1e4 particles 2.94 -> 1.67 ms in FP32 and
+// 3.25 -> 1.64 in FP64, 2e5 3.37 -> 2.41 and 4.08 -> 2.87; 64 cubic edges,
+// 1e4 particles in FP32 0.75 -> 0.51 (with the pools spread over more waves,
+// which is most of it where the tables do not fit: 200 tabulated edges, 1e4
+// particles in FP64 5.41 -> 2.84).
+template <bool FP64, bool STAGED, int GEN>
 __device__ __forceinline__ GView block_view(const GraphDev &G, char *smem) {
   if (!STAGED) return global_view(G);
-  const int32_t bytes = FP64 ? G.stage_bytes64 : G.stage_bytes32;
+  const int32_t x = GEN ? (FP64 ? G.x_bytes64 : G.x_bytes32) : 0;
+  const int32_t bytes = (FP64 ? G.stage_bytes64 - G.x_bytes64 : G.stage_bytes32 - G.x_bytes32);
   const int32_t head = G.o_e32;
   const uint4 *src_head = (const uint4 *)G.tables;
   const uint4 *src_edge = (const uint4 *)(G.tables + (FP64 ? G.o_e64 : G.o_e32));
@@ -1417,10 +1425,22 @@ __device__ __forceinline__ GView block_view(const GraphDev &G, char *smem) {
   v.guide = (const int32_t *)(smem + G.o_guide);
   v.e32 = (const EdgeRec32 *)(smem + head);
   v.e64 = (const EdgeRec64 *)(smem + head);
-  v.hi64 = G.e64;
+  v.hi32 = G.hi32;
   v.wz = G.wz;
   v.tab64 = G.tab64;
   v.tab32 = G.tab32;
+  v.bm = nullptr;
+  if (GEN && x) {
+    const uint4 *src = FP64 ? (const uint4 *)G.tab64 : (const uint4 *)G.hi32;
+    uint4 *to = dst + bytes / 16;
+    for (int32_t i = threadIdx.x; i < x / 16; i += blockDim.x) to[i] = src[i];
+    if (FP64) {
+      v.tab64 = (const TabRec64 *)to;
+    } else {
+      v.hi32 = (const EdgeHi32 *)to;
+      v.tab32 = (const TabRec32 *)((const EdgeHi32 *)to + G.E);
+    }
+  }
   return v;
 }
 
@@ -1440,7 +1460,7 @@ __device__ __forceinline__ void step_block(const GraphDev &G, const SetDev &S,
   if (LDS)
     for (int32_t s = threadIdx.x; s < G.nnz; s += blockDim.x) s_exit[s] = 0;
   const int32_t ex = LDS ? exit_bytes(G.nnz) : 0;
-  GView view = block_view<FP64, STAGED>(G, smem + ex);
+  GView view = block_view<FP64, STAGED, GEN>(G, smem + ex);
   if (FP64) view.bm = bm;
   ObsSink o{nullptr, G.e64};
   if (OBS && A.obs_lds) {
@@ -2374,7 +2394,7 @@ __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
   if (LDS)
     for (int32_t s = threadIdx.x; s < G.nnz; s += blockDim.x) s_exit[s] = 0;
   const int32_t ex = LDS ? exit_bytes(G.nnz) : 0;
-  GView view = block_view<FP64, STAGED>(G, smem + ex);
+  GView view = block_view<FP64, STAGED, GEN>(G, smem + ex);
   if (FP64) view.bm = bm;
   const int32_t o_pools =
       align16(ex + (STAGED ? (FP64 ? G.stage_bytes64 : G.stage_bytes32) : 0));
@@ -2407,14 +2427,15 @@ void k_pool32(GraphDev G, SetDev S, StepArgs A) {
   pool_block<false, TRACE, LDS, STAGED, OBS, PW, GEN>(G, S, A, s_tot, (char *)smem4);
 }
 
-// FP64 wave pools: the same schedule over FP64 particles (pools of 128,
-// 8-step windows).  Two FP64 particles per lane take more registers: four
-// waves per SIMD.
+// FP64 wave pools: the same schedule over FP64 particles (pools of 128).  Two
+// FP64 particles per lane take more registers: four waves per SIMD, three at
+// the full general level, whose 160 registers would spill (three, four and
+// five waves run the affine level alike: it is bound by VALU issue).
 #ifndef MG_POOL64_WAVES_PER_EU
 #define MG_POOL64_WAVES_PER_EU 4
 #endif
 template <bool TRACE, bool LDS, bool STAGED, bool OBS, int GEN>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL64_WAVES_PER_EU)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEN == kGenFull ? 3 : MG_POOL64_WAVES_PER_EU)))
 void k_pool64(GraphDev G, SetDev S, StepArgs A) {
   extern __shared__ uint4 smem4[];
   __shared__ unsigned long long s_tot[4];
@@ -2462,7 +2483,7 @@ void k_pool32_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem 
 
 // The same over FP64 sets: FP64 wave pools (128 per wave, 8-step windows).
 template <bool TRACE, bool LDS, bool STAGED, bool OBS, int GEN = 0>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL64_WAVES_PER_EU)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEN == kGenFull ? 3 : MG_POOL64_WAVES_PER_EU)))
 void k_pool64_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem *items,
                     StepArgs A) {
   extern __shared__ uint4 smem4[];
