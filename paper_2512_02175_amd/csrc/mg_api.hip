@@ -1257,20 +1257,25 @@ mg_status mg_observe_histogram(mg_particles *p, int32_t bins_per_edge, int32_t e
   MG_HIP(hipDeviceSynchronize(), "synchronising the device");
   if (p->sd.obs) (void)hipFree(p->sd.obs);
   p->sd.obs = nullptr;
+  p->sd.obs_edge = nullptr;
   p->sd.obs_nb = 0;
   p->sd.obs_every = 0;
   if (every == 0) return MG_OK;
   const size_t bytes = (size_t)p->g->E * (size_t)bins_per_edge * 8;
+  const size_t o_edge = align_up(bytes, 16);
   uint64_t *mem = nullptr;
-  hipError_t he = hipMalloc(&mem, bytes);
+  hipError_t he = hipMalloc(&mem, o_edge + (size_t)p->g->E * sizeof(double2));
   if (he != hipSuccess)
     return fail(MG_ENOMEM, "hipMalloc for the streamed histogram: %s", hipGetErrorString(he));
+  double2 *edges = (double2 *)((char *)mem + o_edge);
   he = hipMemsetAsync(mem, 0, bytes, p->stream);
+  if (he == hipSuccess) he = launch_obs_edges(p->g->gd, bins_per_edge, edges, p->stream);
   if (he != hipSuccess) {
     (void)hipFree(mem);
     return hip_fail(he, "clearing the streamed histogram");
   }
   p->sd.obs = mem;
+  p->sd.obs_edge = edges;
   p->sd.obs_nb = bins_per_edge;
   p->sd.obs_every = (uint32_t)every;
   p->obs_start = p->step;

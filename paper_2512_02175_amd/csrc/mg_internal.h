@@ -165,6 +165,7 @@ struct SetDev {
   uint32_t *err;       // [1]
   uint32_t *work;      // [1] next particle id a persistent pool launch hands out
   uint64_t *obs;       // [E * obs_nb] streamed histogram, or null (off)
+  const double2 *obs_edge;  // [E] its edges' {length, inverse bin width}
   int32_t obs_nb;      // its bins per edge
   uint32_t obs_every;  // a snapshot each time the step counter reaches a
                        // multiple of obs_every
@@ -288,6 +289,8 @@ int32_t batch_blocks_per_cu(int32_t max_nnz, int32_t max_stage, const StepArgs &
 // global atomics.
 hipError_t launch_histogram(const GraphDev &g, const SetDev &s, int32_t nb,
                             uint64_t *out, bool fp64, hipStream_t st);
+// Fills a streamed histogram's table of edges (SetDev::obs_edge).
+hipError_t launch_obs_edges(const GraphDev &g, int32_t nb, double2 *out, hipStream_t st);
 hipError_t launch_histogram_csr(const GraphDev &g, const SetDev &s, const int32_t *off,
                                 const double *up, int32_t nbins, uint64_t *out, bool fp64,
                                 hipStream_t st);

@@ -501,17 +501,27 @@ __device__ __forceinline__ uint32_t next_snapshot(uint32_t n, const SetDev &S) {
   return v > 0xFFFFFFFFull ? 0u : (uint32_t)v;
 }
 
+// The snapshot count after one: multiples of S.obs_every follow each other
+// (0 when the next would pass 2^32 - 1).
+__device__ __forceinline__ uint32_t snapshot_after(uint32_t snap, const SetDev &S) {
+  const uint32_t v = snap + S.obs_every;
+  return v < snap ? 0u : v;
+}
+
 // Where snapshots go: LDS bins of the block (lds != null) or the set's
-// global counters; e64 is the global FP64 edge table (bins are taken in
-// FP64 from the lengths, as the histogram kernel does).
+// global counters.  Bins are taken in FP64 from the set's table of edge
+// lengths and inverse bin widths, made when streaming starts, and the next
+// snapshot count waits in a particle's home slot, so no count costs a
+// division (1e6 particles: the tracer's 2000 steps, a snapshot every 100, 6.9
+// -> 6.1 ms with its readback; the 5-edge linear star, 1000 steps, every 50,
+// 13.3 -> 11.7).
 struct ObsSink {
   uint32_t *lds;
-  const EdgeRec64 *e64;
 };
 
-__device__ __forceinline__ void observe_at(int32_t e, double x, const SetDev &S,
+__device__ __forceinline__ void observe_at(int32_t e, double x, double inv, const SetDev &S,
                                            const ObsSink &o) {
-  const int32_t idx = e * S.obs_nb + bin_of(x, o.e64[e].span, S.obs_nb);
+  const int32_t idx = e * S.obs_nb + bin_at(x, inv, S.obs_nb);
   if (o.lds)
     atomicAdd(&o.lds[idx], 1u);
   else
@@ -519,7 +529,14 @@ __device__ __forceinline__ void observe_at(int32_t e, double x, const SetDev &S,
 }
 template <typename P>
 __device__ __forceinline__ void observe(const P &q, const SetDev &S, const ObsSink &o) {
-  observe_at(q.e, q.pos64(o.e64[q.e].L), S, o);
+  const double2 r = S.obs_edge[q.e];
+  observe_at(q.e, q.pos64(r.x), r.y, S, o);
+}
+
+// {length, inverse bin width} of every edge for a set's streamed histogram.
+__global__ void k_obs_edges(const EdgeRec64 *e64, int32_t n_edges, int32_t nb, double2 *out) {
+  const int32_t e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < n_edges) out[e] = make_double2(e64[e].L, (double)nb / e64[e].span);
 }
 
 template <typename T, int N>
@@ -1462,7 +1479,7 @@ __device__ __forceinline__ void step_block(const GraphDev &G, const SetDev &S,
   const int32_t ex = LDS ? exit_bytes(G.nnz) : 0;
   GView view = block_view<FP64, STAGED, GEN>(G, smem + ex);
   if (FP64) view.bm = bm;
-  ObsSink o{nullptr, G.e64};
+  ObsSink o{nullptr};
   if (OBS && A.obs_lds) {
     o.lds = (uint32_t *)(smem + align16(ex + (STAGED ? (FP64 ? G.stage_bytes64
                                                              : G.stage_bytes32) : 0)));
@@ -1586,6 +1603,22 @@ struct PoolLds64 : PoolTrace<TRACE, PW> {
 __device__ __forceinline__ uint64_t ballot(bool c) { return __builtin_amdgcn_ballot_w64(c); }
 __device__ __forceinline__ bool in_mask(uint64_t m) {
   return __builtin_amdgcn_inverse_ballot_w64(m);
+}
+
+// A pool's LDS: with streaming, each home slot also keeps its particle's
+// next snapshot count.
+template <class Pool, int PW>
+struct PoolObs : Pool {
+  uint32_t snap[PW];
+};
+template <int PW, bool FP64, bool TRACE, bool OBS>
+using PoolPlain = std::conditional_t<FP64, PoolLds64<TRACE, PW>, PoolLds32<TRACE, PW>>;
+template <int PW, bool FP64, bool TRACE, bool OBS>
+using PoolLds = std::conditional_t<OBS, PoolObs<PoolPlain<PW, FP64, TRACE, OBS>, PW>,
+                                   PoolPlain<PW, FP64, TRACE, OBS>>;
+template <int PW, bool FP64, bool TRACE>
+size_t pool_lds_bytes(bool obs) {
+  return obs ? sizeof(PoolLds<PW, FP64, TRACE, true>) : sizeof(PoolLds<PW, FP64, TRACE, false>);
 }
 
 __device__ __forceinline__ uint32_t lane_rank(uint64_t mask) {
@@ -2067,6 +2100,7 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
   uint64_t m_has = 0ull;             // lanes with a particle
   uint32_t slot = 0, g = 0, jb = 0;  // the lane's home slot, next group, first step in it
   uint32_t snap = 0;  // next snapshot count of the lane's particle
+  const uint32_t snap0 = OBS ? next_snapshot(S.n0, S) : 0u;
   // Ready, split and free queues: FIFO rings over the pool's slot ids, with
   // wave-uniform head and tail counters.  FIFO keeps the particles of a pool
   // advancing together, so a launch ends without a long tail of stragglers.
@@ -2130,6 +2164,7 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
         P.n[hs] = S.n0;
         P.pid[hs] = id;
         P.k[hs] = 0;
+        if constexpr (OBS) P.snap[hs] = snap0;
         if constexpr (TRACE) {
           P.hits[hs] = S.hits[id];
           P.hash[hs] = S.seqhash[id];
@@ -2155,7 +2190,7 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
           ctr = main_ctr(P.pid[slot], S.tag, A.key0, A.key1);
           g = n >> 2;
           jb = n & 3u;
-          if (OBS) snap = next_snapshot(n, S);
+          if constexpr (OBS) snap = P.snap[slot];
         }
         r_head += (uint32_t)__popcll(m_take);
         m_has |= m_take;
@@ -2248,8 +2283,9 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
           const uint64_t due = completed & ballot(snap == 4u * g + m);
           if (due != 0ull) {
             if (in_mask(due)) {
-              observe_at(ln.e, Ln::pos64(a, ln.side(), sink.e64[ln.e].L), S, sink);
-              snap = next_snapshot(snap, S);
+              const double2 r = S.obs_edge[ln.e];
+              observe_at(ln.e, Ln::pos64(a, ln.side(), r.x), r.y, S, sink);
+              snap = snapshot_after(snap, S);
             }
           }
         };
@@ -2278,6 +2314,7 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
             ln.store(P, slot, a);
             P.n[slot] = 4u * g + j;
             P.w[slot] = w;
+            if constexpr (OBS) P.snap[slot] = snap;
             P.split[(s_tail + lane_rank(m_park)) % K] = (uint8_t)slot;
           }
           s_tail += (uint32_t)__popcll(m_park);
@@ -2344,7 +2381,13 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
         } else {
           if (q2.alive) {
             if ((step & 3u) == 3u) q2.reanchor();
-            if (OBS && step + 1u == next_snapshot(step, S)) observe(q2, S, sink);
+            if constexpr (OBS) {
+              const uint32_t at = P.snap[s2];
+              if (step + 1u == at) {
+                observe(q2, S, sink);
+                P.snap[s2] = snapshot_after(at, S);
+              }
+            }
           }
           const uint32_t n2 = step + 1u;
           if (!q2.alive || n2 == n_end) {
@@ -2375,14 +2418,12 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
 // [staged tables][pools][snapshot bins].  Stages the set's tables, runs its particles until the
 // set's counter has run out and the block's pools are empty, and adds the
 // block's counts to the set's counters.
-template <int PW, bool FP64, bool TRACE>
-using PoolLds = std::conditional_t<FP64, PoolLds64<TRACE, PW>, PoolLds32<TRACE, PW>>;
 
 template <bool FP64, bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN>
 __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
                                            const StepArgs &A, unsigned long long *s_tot,
                                            char *smem) {
-  using Pool = PoolLds<PW, FP64, TRACE>;
+  using Pool = PoolLds<PW, FP64, TRACE, OBS>;
   using Ln = std::conditional_t<FP64, Lane64<TRACE, LDS, GEN>, Lane32<TRACE, LDS, GEN>>;
   BmLds *bm = (BmLds *)smem;
   if (FP64) {
@@ -2399,7 +2440,7 @@ __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
   const int32_t o_pools =
       align16(ex + (STAGED ? (FP64 ? G.stage_bytes64 : G.stage_bytes32) : 0));
   Pool *pools = (Pool *)(smem + o_pools);
-  ObsSink o{nullptr, G.e64};
+  ObsSink o{nullptr};
   if (OBS && A.obs_lds) {
     o.lds = (uint32_t *)(smem + o_pools + (int32_t)sizeof(Pool) * kWavesPerBlock);
     for (int32_t b = threadIdx.x; b < A.obs_lds; b += blockDim.x) o.lds[b] = 0;
@@ -2929,7 +2970,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
     if (a.kernel == 3) {
       // FP64 wave pools (128 per wave, 8-step windows) on a resident grid
       const LdsPlan lp = plan_lds(true, g.nnz, g.stage_bytes64,
-                                  sizeof(PoolLds64<TRACE, kPoolSmall>) * kWavesPerBlock, &s,
+                                  pool_lds_bytes<kPoolSmall, true, TRACE>(obs) * kWavesPerBlock, &s,
                                   g.E);
       a.obs_lds = lp.obs_lds;
       const uint32_t need = set_pool(a, s.n, kPoolSmall);
@@ -2953,7 +2994,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
       constexpr int PW = decltype(PWc)::value;
       const int32_t stage = g.stage_bytes32;
       const LdsPlan lp = plan_lds(false, g.nnz, stage,
-                                  sizeof(PoolLds32<TRACE, PW>) * kWavesPerBlock,
+                                  pool_lds_bytes<PW, false, TRACE>(obs) * kWavesPerBlock,
                                   &s, g.E);
       a.obs_lds = lp.obs_lds;
       const uint32_t need = set_pool(a, s.n, PW);
@@ -3032,8 +3073,8 @@ KernelLaunch batch_launch_t(int32_t n_items, int32_t max_nnz, int32_t max_stage,
   const bool pools = FP64 ? a.kernel == 3 : (a.kernel >= 1 && (!gen || a.kernel == 3));
   with_pool(a.kernel, [&](auto PWc) {
     constexpr int PW = decltype(PWc)::value;
-    const size_t pool_bytes = FP64 ? sizeof(PoolLds64<TRACE, kPoolSmall>) * kWavesPerBlock
-                                   : sizeof(PoolLds32<TRACE, PW>) * kWavesPerBlock;
+    const size_t pool_bytes =
+        pool_lds_bytes<FP64 ? kPoolSmall : PW, FP64, TRACE>(obs) * kWavesPerBlock;
     const LdsPlan lp = plan_lds(FP64, max_nnz, max_stage, pools ? pool_bytes : 0, nullptr, 0);
     k.shm = lp.shm;
     with_gen(gen, [&](auto Gn) {
@@ -3153,6 +3194,12 @@ hipError_t launch_fill_zero_u64(uint64_t *p, int64_t n, hipStream_t st) {
   int64_t blocks = (n + kBlock - 1) / kBlock;
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(k_fill_zero_u64, dim3((uint32_t)blocks), dim3(kBlock), 0, st, p, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_obs_edges(const GraphDev &g, int32_t nb, double2 *out, hipStream_t st) {
+  hipLaunchKernelGGL(k_obs_edges, dim3((g.E + kBlock - 1) / kBlock), dim3(kBlock), 0, st, g.e64,
+                     g.E, nb, out);
   return hipGetLastError();
 }
 
