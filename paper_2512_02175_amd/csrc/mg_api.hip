@@ -12,6 +12,8 @@
 #include <cstring>
 #include <functional>
 #include <mutex>
+#include <new>
+#include <optional>
 #include <string>
 #include <vector>
 
@@ -289,15 +291,233 @@ SetLayout set_layout(int32_t V, int32_t nnz, int64_t n, mg_precision prec, bool 
   return L;
 }
 
+// ------------------------------------------------------------ readback --
+// Results reach host memory through pinned staging: a kernel writes them
+// there, the call waits once, and copies them to the caller's arrays.  (A
+// copy into pageable memory makes the runtime stage and wait for each array:
+// the four arrays of mg_exit_counts and the error word took about 60 us, and
+// mg_particles_read a pass over the particles on the host besides.)
+//
+// Staging blocks, pinned memory and device counters of two sizes, are kept in
+// one pool per process, by device: taken by a call for as long as it lasts
+// (it waits for its stream before it gives the block back, so blocks never
+// carry work from one stream to another), at most kStagingKeep free ones of
+// a size are kept, and all are freed when the last graph is destroyed.
+struct Staging {
+  int device = -1;
+  int cls = 0;
+  char *host = nullptr;
+  char *dev = nullptr;
+  hipEvent_t ev[2] = {nullptr, nullptr};
+};
+constexpr size_t kStagingHost[2] = {(size_t)256 << 10, (size_t)8 << 20};
+constexpr size_t kStagingDev[2] = {(size_t)256 << 10, (size_t)16 << 20};
+constexpr int kStagingKeep = 4;
+
+std::mutex g_staging_mu;
+Staging *g_staging[4 * kStagingKeep] = {};  // free blocks
+int64_t g_live_graphs = 0;
+
+void staging_free(Staging *s) {
+  for (hipEvent_t e : s->ev)
+    if (e) (void)hipEventDestroy(e);
+  if (s->host) (void)hipHostFree(s->host);
+  if (s->dev) (void)hipFree(s->dev);
+  delete s;
+}
+
+void staging_graphs(int change) {
+  Staging *drop[4 * kStagingKeep] = {};
+  {
+    std::lock_guard<std::mutex> lock(g_staging_mu);
+    g_live_graphs += change;
+    if (g_live_graphs <= 0) std::swap(drop, g_staging);
+  }
+  for (Staging *s : drop)
+    if (s) staging_free(s);
+}
+
+// A call's block: null when none could be had (the caller then copies
+// straight to its destination).
+class Lease {
+ public:
+  explicit Lease(size_t host, size_t dev = 0) {
+    if (dev > kStagingDev[1]) return;
+    const int cls = host > kStagingHost[0] || dev > kStagingDev[0] ? 1 : 0;
+    s_ = take(cls);
+    // a smaller block also carries a readback, in more pieces
+    if (!s_ && cls == 1 && dev == 0) s_ = take(0);
+  }
+  Lease(const Lease &) = delete;
+  Lease &operator=(const Lease &) = delete;
+  ~Lease() {
+    if (!s_) return;
+    {
+      std::lock_guard<std::mutex> lock(g_staging_mu);
+      int same = 0;
+      Staging **slot = nullptr;
+      for (Staging *&f : g_staging) {
+        if (f) same += f->device == s_->device && f->cls == s_->cls;
+        else if (!slot) slot = &f;
+      }
+      if (g_live_graphs > 0 && same < kStagingKeep && slot) {
+        *slot = s_;
+        return;
+      }
+    }
+    staging_free(s_);
+  }
+  Staging *operator->() const { return s_; }
+  explicit operator bool() const { return s_ != nullptr; }
+  size_t host_bytes() const { return kStagingHost[s_->cls]; }
+
+ private:
+  static Staging *take(int cls) {
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return nullptr;
+    {
+      std::lock_guard<std::mutex> lock(g_staging_mu);
+      for (Staging *&f : g_staging)
+        if (f && f->device == device && f->cls == cls) {
+          Staging *s = f;
+          f = nullptr;
+          return s;
+        }
+    }
+    Staging *s = new (std::nothrow) Staging();
+    if (!s) return nullptr;
+    s->device = device;
+    s->cls = cls;
+    hipError_t he = hipHostMalloc((void **)&s->host, kStagingHost[cls], 0);
+    if (he == hipSuccess) he = hipMalloc((void **)&s->dev, kStagingDev[cls]);
+    for (hipEvent_t &e : s->ev)
+      if (he == hipSuccess) he = hipEventCreateWithFlags(&e, hipEventDisableTiming);
+    if (he != hipSuccess) {
+      (void)hipGetLastError();
+      staging_free(s);
+      return nullptr;
+    }
+    return s;
+  }
+  Staging *s_ = nullptr;
+};
+
+bool is_device_pointer(const void *ptr);
+
+mg_status device_error(uint32_t err) {
+  if (err & kErrEdge) return fail(MG_EDEVICE, "a particle's edge id is out of range");
+  if (err & kErrPos) return fail(MG_EDEVICE, "a particle's position is outside its edge");
+  return MG_OK;
+}
+
 mg_status check_device_error(const mg_particles *p) {
   uint32_t err = 0;
   MG_HIP(hipMemcpyAsync(&err, p->sd.err, 4, hipMemcpyDeviceToHost, p->stream),
          "reading the device error word");
   MG_HIP(hipStreamSynchronize(p->stream), "synchronising the stream");
-  if (err & kErrEdge) return fail(MG_EDEVICE, "a particle's edge id is out of range");
-  if (err & kErrPos) return fail(MG_EDEVICE, "a particle's position is outside its edge");
-  return MG_OK;
+  return device_error(err);
 }
+
+// Arrays of a set (or of its call) on their way to the caller, copied by
+// finish() after everything queued on the set's stream; it waits, and reports
+// the set's device error word.
+class Readback {
+ public:
+  explicit Readback(const mg_particles *p) : p_(p) {}
+  void add(void *dst, const void *src, size_t bytes) {
+    if (dst && bytes) seg_[n_++] = {dst, src, bytes};
+  }
+  mg_status finish(const char *what) {
+    size_t total = 16;
+    bool host = true;
+    for (int i = 0; i < n_; ++i) {
+      total += align_up(seg_[i].bytes, 16);
+      host = host && !is_device_pointer(seg_[i].dst);
+    }
+    if (host) {
+      Lease st(std::min(total, kStagingHost[1]));
+      if (st) return total <= st.host_bytes() ? at_once(st, what) : in_chunks(st, what);
+    }
+    for (int i = 0; i < n_; ++i)
+      MG_HIP(hipMemcpyAsync(seg_[i].dst, seg_[i].src, seg_[i].bytes, hipMemcpyDefault,
+                            p_->stream), what);
+    return check_device_error(p_);
+  }
+
+ private:
+  struct Seg {
+    void *dst;
+    const void *src;
+    size_t bytes;
+  };
+  const mg_particles *p_;
+  Seg seg_[kCopySegs - 1];
+  int n_ = 0;
+
+  mg_status at_once(const Lease &st, const char *what) {
+    CopyOut c{};
+    size_t off = 16;
+    c.src[0] = p_->sd.err;
+    c.dst[0] = st->host;
+    c.words[0] = 1;
+    c.n = 1;
+    for (int i = 0; i < n_; ++i) {
+      c.src[c.n] = seg_[i].src;
+      c.dst[c.n] = st->host + off;
+      c.words[c.n++] = (uint32_t)(seg_[i].bytes / 4);
+      off += align_up(seg_[i].bytes, 16);
+    }
+    MG_HIP(launch_copy_out(c, p_->stream), what);
+    MG_HIP(hipStreamSynchronize(p_->stream), what);
+    off = 16;
+    for (int i = 0; i < n_; ++i) {
+      std::memcpy(seg_[i].dst, st->host + off, seg_[i].bytes);
+      off += align_up(seg_[i].bytes, 16);
+    }
+    uint32_t err;
+    std::memcpy(&err, st->host, 4);
+    return device_error(err);
+  }
+
+  // Large arrays in halves of the block: the host copies one out while the
+  // other fills.
+  mg_status in_chunks(const Lease &st, const char *what) {
+    const size_t half = st.host_bytes() / 2;
+    struct Piece {
+      char *dst;
+      size_t bytes;
+    } last[2] = {};
+    int k = 0;
+    hipError_t he = hipSuccess;
+    auto drain = [&](int h) {
+      if (!last[h].bytes || he != hipSuccess) return;
+      he = hipEventSynchronize(st->ev[h]);
+      if (he == hipSuccess) std::memcpy(last[h].dst, st->host + h * half, last[h].bytes);
+      last[h].bytes = 0;
+    };
+    for (int i = 0; i < n_; ++i)
+      for (size_t at = 0; at < seg_[i].bytes && he == hipSuccess; at += half, k ^= 1) {
+        const size_t bytes = std::min(half, seg_[i].bytes - at);
+        drain(k);
+        CopyOut c{};
+        c.src[0] = (const char *)seg_[i].src + at;
+        c.dst[0] = st->host + k * half;
+        c.words[0] = (uint32_t)(bytes / 4);
+        c.n = 1;
+        if (he == hipSuccess) he = launch_copy_out(c, p_->stream);
+        if (he == hipSuccess) he = hipEventRecord(st->ev[k], p_->stream);
+        if (he == hipSuccess) last[k] = {(char *)seg_[i].dst + at, bytes};
+        drain(k ^ 1);
+      }
+    drain(0);
+    drain(1);
+    if (he != hipSuccess) {
+      (void)hipStreamSynchronize(p_->stream);
+      return hip_fail(he, what);
+    }
+    return check_device_error(p_);
+  }
+};
 
 bool is_device_pointer(const void *ptr) {
   hipPointerAttribute_t attr;
@@ -801,6 +1021,7 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
   g->gd.V = V;
   g->gd.E = E;
   g->gd.nnz = nnz;
+  staging_graphs(1);
   *out = g;
   return MG_OK;
 }
@@ -809,6 +1030,7 @@ void mg_graph_destroy(mg_graph *g) {
   if (!g) return;
   if (g->dev) (void)hipFree(g->dev);
   delete g;
+  staging_graphs(-1);
 }
 
 int64_t mg_particles_arena_bytes(const mg_graph *g, int64_t n, const mg_options *opt) {
@@ -1152,18 +1374,33 @@ mg_status mg_histogram(const mg_particles *p, int32_t bins_per_edge, uint64_t *o
   if (out_len < need) return fail(MG_EINVAL, "out_len %lld < E * bins_per_edge = %lld",
                                   (long long)out_len, (long long)need);
   const bool dev_out = is_device_pointer(out);
-  uint64_t *d_out = out;
-  if (!dev_out) MG_HIP(hipMalloc(&d_out, (size_t)need * 8), "allocating the histogram");
-  const bool fp64 = p->prec == MG_FP64;
-  hipError_t he = hipMemsetAsync(d_out, 0, (size_t)need * 8, p->stream);
+  // a host output's counters: in a staging block, or allocated if they exceed
+  // one
+  uint64_t *d_out = out, *own = nullptr;
+  std::optional<Lease> st;
+  if (!dev_out) {
+    st.emplace(0, (size_t)need * 8);
+    if (*st) {
+      d_out = (uint64_t *)(*st)->dev;
+    } else {
+      MG_HIP(hipMalloc(&own, (size_t)need * 8), "allocating the histogram");
+      d_out = own;
+    }
+  }
+  hipError_t he = launch_fill_zero_u64(d_out, need, p->stream);
   if (he == hipSuccess)
-    he = launch_histogram(p->g->gd, p->sd, bins_per_edge, d_out, fp64, p->stream);
-  if (he == hipSuccess && !dev_out)
-    he = hipMemcpyAsync(out, d_out, (size_t)need * 8, hipMemcpyDeviceToHost, p->stream);
-  if (he == hipSuccess) he = hipStreamSynchronize(p->stream);
-  if (!dev_out) (void)hipFree(d_out);
-  if (he != hipSuccess) return hip_fail(he, "computing the histogram");
-  return check_device_error(p);
+    he = launch_histogram(p->g->gd, p->sd, bins_per_edge, d_out, p->prec == MG_FP64, p->stream);
+  mg_status res = MG_OK;
+  if (he == hipSuccess) {
+    Readback rb(p);
+    if (!dev_out) rb.add(out, d_out, (size_t)need * 8);
+    res = rb.finish("computing the histogram");
+  } else {
+    (void)hipStreamSynchronize(p->stream);
+    res = hip_fail(he, "computing the histogram");
+  }
+  if (own) (void)hipFree(own);
+  return res;
 }
 
 mg_status mg_histogram_csr(const mg_particles *p, const int32_t *bin_offsets,
@@ -1177,27 +1414,45 @@ mg_status mg_histogram_csr(const mg_particles *p, const int32_t *bin_offsets,
   const size_t o_off = 0, o_up = align_up(sizeof(int32_t) * (E + 1), 256),
                o_out = align_up(o_up + sizeof(double) * nbins, 256),
                total = o_out + (dev_out ? 0 : sizeof(uint64_t) * nbins);
-  char *mem = nullptr;
-  MG_HIP(hipMalloc(&mem, total), "allocating the bin tables");
+  // the bin tables (and a host output's counters) in a staging block, sent up
+  // from its pinned half, or allocated if they exceed one
+  Lease st(o_out, total);
+  char *mem = st ? st->dev : nullptr, *own = nullptr;
+  if (!st || o_out > st.host_bytes()) {
+    MG_HIP(hipMalloc(&own, total), "allocating the bin tables");
+    mem = own;
+  }
   int32_t *d_off = (int32_t *)(mem + o_off);
   double *d_up = (double *)(mem + o_up);
   uint64_t *d_out = dev_out ? out : (uint64_t *)(mem + o_out);
-  hipError_t he = hipMemcpyAsync(d_off, bin_offsets, sizeof(int32_t) * (E + 1),
-                                 hipMemcpyHostToDevice, p->stream);
-  if (he == hipSuccess)
-    he = hipMemcpyAsync(d_up, bin_upper, sizeof(double) * nbins, hipMemcpyHostToDevice,
+  hipError_t he = hipSuccess;
+  if (own) {
+    he = hipMemcpyAsync(d_off, bin_offsets, sizeof(int32_t) * (E + 1), hipMemcpyHostToDevice,
                         p->stream);
-  if (he == hipSuccess) he = hipMemsetAsync(d_out, 0, sizeof(uint64_t) * nbins, p->stream);
+    if (he == hipSuccess)
+      he = hipMemcpyAsync(d_up, bin_upper, sizeof(double) * nbins, hipMemcpyHostToDevice,
+                          p->stream);
+  } else {
+    std::memcpy(st->host + o_off, bin_offsets, sizeof(int32_t) * (E + 1));
+    std::memcpy(st->host + o_up, bin_upper, sizeof(double) * nbins);
+    he = hipMemcpyAsync(mem, st->host, o_up + sizeof(double) * nbins, hipMemcpyHostToDevice,
+                        p->stream);
+  }
+  if (he == hipSuccess) he = launch_fill_zero_u64(d_out, nbins, p->stream);
   if (he == hipSuccess)
     he = launch_histogram_csr(p->g->gd, p->sd, d_off, d_up, (int32_t)nbins, d_out,
                               p->prec == MG_FP64, p->stream);
-  if (he == hipSuccess && !dev_out)
-    he = hipMemcpyAsync(out, d_out, sizeof(uint64_t) * nbins, hipMemcpyDeviceToHost,
-                        p->stream);
-  if (he == hipSuccess) he = hipStreamSynchronize(p->stream);
-  (void)hipFree(mem);
-  if (he != hipSuccess) return hip_fail(he, "computing the histogram");
-  return check_device_error(p);
+  mg_status res;
+  if (he == hipSuccess) {
+    Readback rb(p);
+    if (!dev_out) rb.add(out, d_out, sizeof(uint64_t) * nbins);
+    res = rb.finish("computing the histogram");
+  } else {
+    (void)hipStreamSynchronize(p->stream);
+    res = hip_fail(he, "computing the histogram");
+  }
+  if (own) (void)hipFree(own);
+  return res;
 }
 
 mg_status mg_histogram_csr_noalloc(const mg_particles *p, const int32_t *bin_offsets,
@@ -1292,13 +1547,13 @@ mg_status mg_observed_histogram(const mg_particles *p, uint64_t *out, int64_t ou
     if (out_len < need)
       return fail(MG_EINVAL, "out_len %lld < E * bins_per_edge = %lld", (long long)out_len,
                   (long long)need);
-    MG_HIP(hipMemcpyAsync(out, p->sd.obs, (size_t)need * 8, hipMemcpyDefault, p->stream),
-           "copying the streamed histogram");
   }
-  MG_HIP(hipStreamSynchronize(p->stream), "synchronising the stream");
-  if (n_snapshots)
+  Readback rb(p);
+  rb.add(out, p->sd.obs, (size_t)need * 8);
+  const mg_status st = rb.finish("copying the streamed histogram");
+  if ((st == MG_OK || st == MG_EDEVICE) && n_snapshots)
     *n_snapshots = (int64_t)(p->step / p->sd.obs_every - p->obs_start / p->sd.obs_every);
-  return check_device_error(p);
+  return st;
 }
 
 mg_status mg_density_l2(const mg_graph *g, int32_t bins_per_edge, const uint64_t *counts,
@@ -1350,17 +1605,11 @@ mg_status mg_exit_counts(const mg_particles *p, uint64_t *slot_counts, uint64_t 
                          uint64_t *totals) {
   g_err.clear();
   if (!p) return fail(MG_EINVAL, "particles is NULL");
-  if (slot_counts)
-    MG_HIP(hipMemcpyAsync(slot_counts, p->sd.exit_cnt, (size_t)p->g->nnz * 8,
-                          hipMemcpyDefault, p->stream), "copying exit counts");
-  if (absorbed)
-    MG_HIP(hipMemcpyAsync(absorbed, p->sd.absorbed, (size_t)p->g->V * 8, hipMemcpyDefault,
-                          p->stream), "copying absorbed counts");
-  if (totals)
-    MG_HIP(hipMemcpyAsync(totals, p->sd.totals, 4 * 8, hipMemcpyDefault, p->stream),
-           "copying totals");
-  MG_HIP(hipStreamSynchronize(p->stream), "synchronising the stream");
-  return check_device_error(p);
+  Readback rb(p);
+  rb.add(slot_counts, p->sd.exit_cnt, (size_t)p->g->nnz * 8);
+  rb.add(absorbed, p->sd.absorbed, (size_t)p->g->V * 8);
+  rb.add(totals, p->sd.totals, 4 * 8);
+  return rb.finish("copying the counters");
 }
 
 mg_status mg_particles_read(const mg_particles *p, int64_t first, int64_t count,
@@ -1371,43 +1620,97 @@ mg_status mg_particles_read(const mg_particles *p, int64_t first, int64_t count,
   if (first < 0 || count < 0 || first + count > p->n) return fail(MG_EINVAL, "range out of bounds");
   if ((seqhash || hits) && !p->trace) return fail(MG_ESTATE, "the set was created without trace");
   if (count == 0) return MG_OK;
-  std::vector<uint32_t> ef(count);
-  MG_HIP(hipMemcpyAsync(ef.data(), p->sd.ef + first, (size_t)count * 4, hipMemcpyDeviceToHost,
-                        p->stream), "copying states");
-  std::vector<double> x64;
-  std::vector<float2> y32;
-  if (pos) {
-    if (p->prec == MG_FP64) {
-      x64.resize(count);
-      MG_HIP(hipMemcpyAsync(x64.data(), p->sd.x64 + first, (size_t)count * 8,
-                            hipMemcpyDeviceToHost, p->stream), "copying positions");
-    } else {
-      y32.resize(count);
-      MG_HIP(hipMemcpyAsync(y32.data(), p->sd.y32 + first, (size_t)count * 8,
-                            hipMemcpyDeviceToHost, p->stream), "copying positions");
-    }
-  }
-  if (seqhash)
+  // hashes and hit counts wanted in device memory go there directly
+  if (seqhash && is_device_pointer(seqhash)) {
     MG_HIP(hipMemcpyAsync(seqhash, p->sd.seqhash + first, (size_t)count * 8, hipMemcpyDefault,
                           p->stream), "copying hashes");
-  if (hits)
+    seqhash = nullptr;
+  }
+  if (hits && is_device_pointer(hits)) {
     MG_HIP(hipMemcpyAsync(hits, p->sd.hits + first, (size_t)count * 4, hipMemcpyDefault,
                           p->stream), "copying hit counts");
-  MG_HIP(hipStreamSynchronize(p->stream), "synchronising the stream");
-  for (int64_t i = 0; i < count; ++i) {
-    const int32_t e = (int32_t)(ef[i] & kEdgeMask);
-    if (edge) edge[i] = e;
-    if (alive) alive[i] = (ef[i] & kDeadBit) ? 0 : 1;
-    if (pos) {
-      if (p->prec == MG_FP64) {
-        pos[i] = x64[i];
-      } else {
-        const double y = (double)y32[i].x + (double)y32[i].y;
-        pos[i] = (ef[i] & kSideBit) ? p->g->length[e] - y : y;
-      }
-    }
+    hits = nullptr;
   }
-  return check_device_error(p);
+  // the particles in chunks through the two halves of a staging block, one
+  // converted by the device while the host copies the other out
+  const size_t each = (edge ? 4 : 0) + (pos ? 8 : 0) + (alive ? 1 : 0) + (seqhash ? 8 : 0) +
+                      (hits ? 4 : 0);
+  if (each == 0) return check_device_error(p);
+  const Lease st(std::min(2 * ((size_t)count * each + 64), kStagingHost[1]));
+  if (!st) return fail(MG_ENOMEM, "no staging memory for the readback");
+  const size_t half = st.host_bytes() / 2;
+  const int64_t most = (int64_t)((half - 64) / each) & ~63ll;
+  // the device error word, in the last bytes of the block
+  char *const err_at = st->host + st.host_bytes() - 64;
+  {
+    CopyOut c{};
+    c.src[0] = p->sd.err;
+    c.dst[0] = err_at;
+    c.words[0] = 1;
+    c.n = 1;
+    MG_HIP(launch_copy_out(c, p->stream), "reading the device error word");
+  }
+  struct Chunk {
+    int64_t at, n;
+  } last[2] = {};
+  struct Views {
+    int32_t *edge;
+    double *pos;
+    uint8_t *alive;
+    uint64_t *hash;
+    uint32_t *hits;
+  };
+  // a chunk's arrays in its half, the widest first so that each is aligned
+  auto views = [&](int h, int64_t n) {
+    char *q = st->host + h * half;
+    Views v{};
+    auto take = [&](bool want, size_t bytes) {
+      char *r = want ? q : nullptr;
+      if (want) q += bytes * (size_t)n;
+      return r;
+    };
+    v.pos = (double *)take(pos, 8);
+    v.hash = (uint64_t *)take(seqhash, 8);
+    v.edge = (int32_t *)take(edge, 4);
+    v.hits = (uint32_t *)take(hits, 4);
+    v.alive = (uint8_t *)take(alive, 1);
+    return v;
+  };
+  hipError_t he = hipSuccess;
+  auto drain = [&](int h) {
+    const Chunk c = last[h];
+    last[h].n = 0;
+    if (!c.n || he != hipSuccess) return;
+    he = hipEventSynchronize(st->ev[h]);
+    if (he != hipSuccess) return;
+    const Views v = views(h, c.n);
+    if (edge) std::memcpy(edge + c.at, v.edge, (size_t)c.n * 4);
+    if (pos) std::memcpy(pos + c.at, v.pos, (size_t)c.n * 8);
+    if (alive) std::memcpy(alive + c.at, v.alive, (size_t)c.n);
+    if (seqhash) std::memcpy(seqhash + c.at, v.hash, (size_t)c.n * 8);
+    if (hits) std::memcpy(hits + c.at, v.hits, (size_t)c.n * 4);
+  };
+  int k = 0;
+  for (int64_t at = 0; at < count && he == hipSuccess; at += most, k ^= 1) {
+    const int64_t n = std::min(most, count - at);
+    drain(k);
+    const Views v = views(k, n);
+    if (he == hipSuccess)
+      he = launch_read(p->g->gd, p->sd, (uint32_t)(first + at), (uint32_t)n, v.edge, v.pos,
+                       v.alive, v.hash, v.hits, p->prec == MG_FP64, p->stream);
+    if (he == hipSuccess) he = hipEventRecord(st->ev[k], p->stream);
+    if (he == hipSuccess) last[k] = {at, n};
+    drain(k ^ 1);
+  }
+  drain(0);
+  drain(1);
+  if (he != hipSuccess) {
+    (void)hipStreamSynchronize(p->stream);
+    return hip_fail(he, "reading the particles");
+  }
+  uint32_t err;
+  std::memcpy(&err, err_at, 4);
+  return device_error(err);
 }
 
 // ----------------------------------------------------- event trace --

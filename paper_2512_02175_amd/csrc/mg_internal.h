@@ -295,6 +295,22 @@ hipError_t launch_histogram_csr(const GraphDev &g, const SetDev &s, const int32_
                                 const double *up, int32_t nbins, uint64_t *out, bool fp64,
                                 hipStream_t st);
 
+// Copies up to kCopySegs arrays (4-byte words; 16-byte aligned ends) into
+// pinned host memory with one kernel.
+constexpr int kCopySegs = 6;
+struct CopyOut {
+  const void *src[kCopySegs];
+  void *dst[kCopySegs];
+  uint32_t words[kCopySegs];
+  int32_t n;
+};
+hipError_t launch_copy_out(const CopyOut &c, hipStream_t st);
+// Converts particles first .. first + count - 1 to the readback's form (any
+// output may be null).
+hipError_t launch_read(const GraphDev &g, const SetDev &s, uint32_t first, uint32_t count,
+                       int32_t *edge, double *pos, uint8_t *alive, uint64_t *hash,
+                       uint32_t *hits, bool fp64, hipStream_t st);
+
 // Clears n 64-bit words with a kernel (no memset node in captured work).
 hipError_t launch_fill_zero_u64(uint64_t *p, int64_t n, hipStream_t st);
 

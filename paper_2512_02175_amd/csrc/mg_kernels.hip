@@ -2844,6 +2844,42 @@ __global__ __launch_bounds__(kHistBlock) void k_hist_csr(GraphDev G, SetDev S,
   }
 }
 
+// ------------------------------------------------------------ readback --
+// Writes go straight to pinned host memory: one launch and one wait where
+// separate copies into pageable memory each took a wait of their own.
+__global__ __launch_bounds__(kBlock) void k_copy_out(CopyOut c) {
+  const int32_t s = (int32_t)blockIdx.y;
+  const uint32_t words = c.words[s], quads = words / 4u, stride = gridDim.x * kBlock;
+  const uint32_t i0 = blockIdx.x * kBlock + threadIdx.x;
+  for (uint32_t i = i0; i < quads; i += stride) ((uint4 *)c.dst[s])[i] = ((const uint4 *)c.src[s])[i];
+  if (i0 < (words & 3u))
+    ((uint32_t *)c.dst[s])[4u * quads + i0] = ((const uint32_t *)c.src[s])[4u * quads + i0];
+}
+
+template <bool FP64>
+__global__ __launch_bounds__(kBlock) void k_read(GraphDev G, SetDev S, uint32_t first,
+                                                 uint32_t count, int32_t *edge, double *pos,
+                                                 uint8_t *alive, uint64_t *hash,
+                                                 uint32_t *hits) {
+  const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+  if (i >= count) return;
+  const uint32_t id = first + i, ef = S.ef[id];
+  const int32_t e = (int32_t)(ef & kEdgeMask);
+  if (edge) edge[i] = e;
+  if (alive) alive[i] = (ef & kDeadBit) ? 0 : 1;
+  if (pos) {
+    if (FP64) {
+      pos[i] = S.x64[id];
+    } else {
+      const float2 yy = S.y32[id];
+      const double y = (double)yy.x + (double)yy.y;
+      pos[i] = (ef & kSideBit) ? (e < G.E ? G.e64[e].L : 0.0) - y : y;
+    }
+  }
+  if (hash) hash[i] = S.seqhash[id];
+  if (hits) hits[i] = S.hits[id];
+}
+
 // Calls f(std::bool_constant<x>...) for the run-time flags, so one launch
 // site covers every compiled variant.
 template <typename F>
@@ -3194,6 +3230,25 @@ hipError_t launch_fill_zero_u64(uint64_t *p, int64_t n, hipStream_t st) {
   int64_t blocks = (n + kBlock - 1) / kBlock;
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(k_fill_zero_u64, dim3((uint32_t)blocks), dim3(kBlock), 0, st, p, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_out(const CopyOut &c, hipStream_t st) {
+  uint32_t most = 1;
+  for (int32_t i = 0; i < c.n; ++i) most = std::max(most, c.words[i]);
+  const uint32_t blocks = std::min((most / 4u + kBlock) / kBlock, 256u);
+  hipLaunchKernelGGL(k_copy_out, dim3(blocks, (uint32_t)c.n), dim3(kBlock), 0, st, c);
+  return hipGetLastError();
+}
+
+hipError_t launch_read(const GraphDev &g, const SetDev &s, uint32_t first, uint32_t count,
+                       int32_t *edge, double *pos, uint8_t *alive, uint64_t *hash,
+                       uint32_t *hits, bool fp64, hipStream_t st) {
+  const dim3 blocks((count + kBlock - 1) / kBlock);
+  with_flags([&](auto F) {
+    hipLaunchKernelGGL(k_read<decltype(F)::value>, blocks, dim3(kBlock), 0, st, g, s, first,
+                       count, edge, pos, alive, hash, hits);
+  }, fp64);
   return hipGetLastError();
 }
 
