@@ -521,9 +521,11 @@ void mg_batch_destroy(mg_batch *b);
  * appends one JSON line with the key and the choice.  Lines that do not
  * parse are skipped; a file that cannot be read or written is ignored.
  * Sets created with
- * schedule MG_SCHED_AUTO are tuned this way on their first mg_simulate at
- * each dt; until then (and in a batch built from untuned sets) they use
- * pools of 128 with 8-step windows.  Fixed pool schedules start a partial
+ * schedule MG_SCHED_AUTO are tuned this way by the first mg_simulate at a dt
+ * that finds 20 times the probes' particle-steps run on the graph at that dt
+ * by untuned sets (at once where a result is known, or MG_TUNE_CACHE names a
+ * file); until then (and in a batch built from untuned sets) they use
+ * MG_SCHED_POOLS_W8.  Fixed pool schedules start a partial
  * pass at 16 idle lanes.  FP64 sets have nothing to probe (their set's FP64 schedule).  `out` (may be
  * NULL) receives the choice and the probe times.  A probe allocates scratch
  * device memory and synchronises the stream.
