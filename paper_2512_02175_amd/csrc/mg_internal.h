@@ -275,8 +275,9 @@ struct KernelLaunch {
   size_t shm;
   bool persistent;  // a resident grid over the items: k_batch_reset goes first
 };
-// k_batch_reset(const SetDev *sets, int32_t n_sets, uint32_t *claim): clears
-// the sets' particle counters and the item counter of a persistent batch.
+// k_batch_reset(const SetDev *sets, int32_t n_sets, uint32_t *claim, int32_t
+// n_claims): clears the sets' particle counters and the groups' item counters
+// of a persistent batch.
 const void *batch_reset_kernel();
 KernelLaunch batch_launch(int32_t n_items, int32_t max_nnz, int32_t max_stage,
                           const StepArgs &a, bool fp64, bool trace, bool obs, int32_t gen);

@@ -2555,13 +2555,14 @@ void k_pool64_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem 
   }
 }
 
-// Clears the particle counters of a batch's sets and its item counter
-// before a launch of k_pool32_batch or k_pool64_batch (a kernel, so that the
-// launch chain can be a HIP graph of kernel nodes).
-__global__ void k_batch_reset(const SetDev *sets, int32_t n_sets, uint32_t *claim) {
+// Clears the particle counters of a batch's sets and its groups' item
+// counters before the launches of k_pool32_batch or k_pool64_batch (a kernel,
+// so that the launches can be a HIP graph of kernel nodes).
+__global__ void k_batch_reset(const SetDev *sets, int32_t n_sets, uint32_t *claim,
+                              int32_t n_claims) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n_sets) *sets[i].work = 0u;
-  if (i == 0) *claim = 0u;
+  if (i < n_claims) claim[i] = 0u;
 }
 
 // Autotuning probes: the FP32 step kernels under names of their own, so a
