@@ -950,7 +950,19 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
   // them
   const size_t o_hi = hashed;
   const size_t o_x32 = o_hi + (g->gen ? sizeof(EdgeHi32) * E : 0);
-  const size_t total = align_up(o_x32 + sizeof(TabRec32) * tab32.size(), 256);
+  // and the guide of the init draw
+  int32_t len_bits = 0;
+  while ((1 << len_bits) < E && len_bits < 20) ++len_bits;
+  std::vector<int32_t> lguide(((size_t)1 << len_bits) + 1, 0);
+  if (!infinite)
+    for (int64_t b = 0, e = 0; b < (1ll << len_bits); ++b) {
+      const uint64_t low = (uint64_t)b << (32 - len_bits);
+      while (e < E - 1 && lthr[e] <= low) ++e;
+      lguide[b] = (int32_t)e;
+    }
+  lguide.back() = E - 1;
+  const size_t o_lg = align_up(o_x32 + sizeof(TabRec32) * tab32.size(), 256);
+  const size_t total = align_up(o_lg + 4 * lguide.size(), 256);
   hipError_t he = hipMalloc(&g->dev, total);
   if (he != hipSuccess) {
     delete g;
@@ -969,6 +981,7 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
     std::memcpy(host.data() + o_t64, tab64.data(), sizeof(TabRec64) * tab64.size());
     std::memcpy(host.data() + o_t32, tab32.data(), sizeof(TabRec32) * tab32.size());
   }
+  std::memcpy(host.data() + o_lg, lguide.data(), 4 * lguide.size());
   if (g->gen) {
     std::vector<EdgeHi32> hi(E);
     for (int32_t e = 0; e < E; ++e) {
@@ -1002,6 +1015,8 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
   g->gd.tab64 = tab64.empty() ? nullptr : (const TabRec64 *)(base + o_t64);
   g->gd.tab32 = tab32.empty() ? nullptr : (const TabRec32 *)(base + o_x32);
   g->gd.hi32 = g->gen ? (const EdgeHi32 *)(base + o_hi) : nullptr;
+  g->gd.len_guide = (const int32_t *)(base + o_lg);
+  g->gd.len_bits = len_bits;
   g->gd.n_guide = (int32_t)ng;
   g->gd.o_vtx = (int32_t)o_vtx;
   g->gd.o_slots = (int32_t)o_sl;

