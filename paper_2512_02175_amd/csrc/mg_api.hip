@@ -1327,11 +1327,15 @@ static int32_t pool_idle(const mg_particles *p) {
 // at 1 / 8 / 16 / 24 lanes 2000 steps of 1e7 FP32 particles on the 64-edge
 // star take 32.4 / 32.3 / 31.2 / 31.3 ms at 7.1 % hits a step, 23.1 / 21.2 /
 // 20.7 / 21.9 at 2.1 %, and 1000 steps of 3e7 on the vascular network
-// (0.35 %) 19.3 / 18.6 / 19.2 / 20.4.
-static void set_schedule(StepArgs &a, int32_t kernel, int32_t idle) {
+// (0.35 %) 19.3 / 18.6 / 19.2 / 20.4.  Hence 16 lanes where the tables are
+// staged in LDS, and 8 where an FP32 set reads them from global memory: a
+// refill there waits for loads that the other lanes' steps hide, and pays
+// earlier.  (FP64, 16 against 8: 55.2 against 56.2 ms for 2000 steps of 1e7
+// on the 64-edge star.)
+static void set_schedule(StepArgs &a, int32_t kernel, int32_t idle, bool fp64, bool staged) {
   a.kernel = kernel;
   a.idle = idle;
-  a.refill = kernel == 3 ? 16 : 8;
+  a.refill = kernel == 3 && (fp64 || staged) ? 16 : 8;
   a.pool_cap = (uint32_t)pool_per_wave(kernel);
 }
 
@@ -1391,7 +1395,8 @@ mg_status mg_simulate(mg_particles *p, int64_t n_steps, double dt, uint64_t seed
   a.key0 = (uint32_t)seed;
   a.key1 = (uint32_t)(seed >> 32);
   a.dt = dt;
-  set_schedule(a, step_kernel(p), pool_idle(p));
+  set_schedule(a, step_kernel(p), pool_idle(p), p->prec == MG_FP64,
+               p->g->gd.stage_bytes32 > 0);
   // a set without a fixed launch length takes the tuned one
   const uint32_t chunk = chunk_steps(
       (p->steps_per_launch == 0 && p->tuned && p->tuned_dt == dt) ? p->tuned_spl
@@ -2294,7 +2299,7 @@ mg_status mg_batch_simulate(mg_batch *b, int64_t n_steps, double dt, uint64_t se
   a.key0 = (uint32_t)seed;
   a.key1 = (uint32_t)(seed >> 32);
   a.dt = dt;
-  set_schedule(a, b->kernel, pool_idle(p0));
+  set_schedule(a, b->kernel, pool_idle(p0), p0->prec == MG_FP64, true);
   const uint32_t chunk = chunk_steps(p0->steps_per_launch);
   const int32_t n_sets = (int32_t)b->sets.size();
   // the previous call's upload must have left the pinned buffer
@@ -2432,7 +2437,7 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
     if (he == hipSuccess)
       he = hipMemcpyAsync(sd.y32, p->sd.y32, (size_t)n * 8, hipMemcpyDeviceToDevice, p->stream);
     if (he == hipSuccess) he = hipEventRecord(e0, p->stream);
-    set_schedule(a, cand_kernel[i], cand_idle[i]);
+    set_schedule(a, cand_kernel[i], cand_idle[i], false, p->g->gd.stage_bytes32 > 0);
     if (he == hipSuccess) he = launch_step(p->g->gd, sd, a, false, false, p->stream);
     if (he == hipSuccess) he = hipEventRecord(e1, p->stream);
     if (he == hipSuccess) he = hipEventSynchronize(e1);
@@ -2448,7 +2453,8 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
   // steps per launch for the chosen schedule: 2 x steps as one launch
   // against two launches of `steps` (each launch ends with a tail of partly
   // filled waves; the launch count is the only difference)
-  set_schedule(a, cand_kernel[best_i], cand_idle[best_i]);
+  set_schedule(a, cand_kernel[best_i], cand_idle[best_i], false,
+               p->g->gd.stage_bytes32 > 0);
   for (int i = 0; i < 2 && he == hipSuccess; ++i) {
     he = hipMemcpyAsync(sd.ef, p->sd.ef, (size_t)n * 4, hipMemcpyDeviceToDevice, p->stream);
     if (he == hipSuccess)
