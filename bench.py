@@ -39,13 +39,13 @@ PEAK_LANE_OPS = 256 * 4 * 32 * 2.4e9
 # multiply, select) = 2.
 ALG_FP32_STEP = 27.5
 ALG_FP32_HIT = 80.0      # per vertex hit: Philox, one normal, root, time, slot, edge
-# FP64 particle-step: 1/4 Philox = 10; 1/2 Box-Muller pair (2 converts and
-# 2 scalings of the uniforms; the logarithm by an integer range reduction
-# and a degree-6 polynomial for the atanh series, 29; the factor -2, 1; the
-# square root, 9; the angle, 1; sine and cosine by quarter-turn reduction
-# and two degree-5 polynomials, 23; 2 multiplies) = 34.5; the first sub-step
-# (2 fma, 2 compares, 2 selects of 64-bit values) = 8.5.
-ALG_FP64_STEP = 53.0
+# FP64 particle-step: 1/4 Philox = 10; 1/2 Box-Muller pair (the logarithm of
+# the uniform by an interval's reciprocal and a degree-5 polynomial, its
+# conversions and integer range reduction included, 18; the square root, 10;
+# sine and cosine by the addition theorem at the nearest 128th of a turn, 20;
+# 2 multiplies) = 25; the first sub-step (2 fma, 2 compares, 2 selects of
+# 64-bit values) = 8.5.
+ALG_FP64_STEP = 43.5
 ALG_FP64_HIT = 130.0
 # cubic drift and diffusion: two Horner steps more for mu and three for
 # sigma at every sub-step start (a step, or a restart from a vertex)
@@ -707,7 +707,7 @@ def run_double_well(args, B, torch):
             "roofline": {"bound": "alu", "achieved": achieved / 1e12,
                          "peak": PEAK_LANE_OPS / 1e12, "unit": "T VALU lane-ops/s",
                          "frac": achieved / PEAK_LANE_OPS, "traffic": None,
-                         "kernel": "k_pool32 (128 per wave, 8-step windows, cubic "
+                         "kernel": "k_pool32 (128 per wave, cubic "
                                    "coefficients)",
                          "kernel_ms_per_call": k * 1e3,
                          "alg_lane_ops_per_particle_step": per_step}}
@@ -879,7 +879,7 @@ def main():
         wall_plain = time.perf_counter() - t2
         sub_plain = sum(r["substeps"] for r in res_plain)
         out_fp64 = {"value": sub64 / wall64, "unit": "particle-substeps/s",
-                    "kernel": "k_pool64 (128 per wave, 8-step windows)",
+                    "kernel": "k_pool64 (128 per wave)",
                     "kernel_substeps_per_s": sub64 / k64,
                     "alg_frac_of_alu_peak": w64 / k64 / PEAK_LANE_OPS,
                     "fp32_speedup": value / (sub64 / wall64),

@@ -197,12 +197,12 @@ void mg_graph_destroy(mg_graph *g);
  *                 MG_SCHED_POOLS (2: each wave cycles 128 particles through
  *                 its lanes and resolves vertex hits in full-width passes),
  *                 MG_SCHED_POOLS256 (3: the same with 256 particles) or
- *                 MG_SCHED_POOLS_W8 (4: pools of 128 whose lanes take
- *                 windows of 8 first sub-steps, two Philox groups, per
- *                 pass instead of 4).
+ *                 MG_SCHED_POOLS_W8 (4: pools of 128 whose lanes run on
+ *                 until 16 of them, not 8, lack a particle, where the
+ *                 graph's tables are staged in LDS or the set is FP64).
  *                 Results are identical; only the speed differs.  FP64 sets
  *                 run MG_SCHED_LANES or MG_SCHED_POOLS_W8 (FP64 wave pools
- *                 of 128 with 8-step windows, also the automatic choice;
+ *                 of 128, also the automatic choice;
  *                 MG_SCHED_POOLS and MG_SCHED_POOLS256 are refused), with
  *                 identical results, in mg_simulate and in batches.
  *                 On a graph with higher coefficient terms (mg_graph_desc)
@@ -502,7 +502,7 @@ void mg_batch_destroy(mg_batch *b);
  * Autotuning of an FP32 set's kernel schedule.  The candidates (one
  * particle per lane; wave pools of 128 particles (2 per lane) that start a
  * partial split pass at 4, 8, 16 or 32 idle lanes; pools of 256 (4 per
- * lane) at 8 or 16; pools of 128 with 8-step windows at 8, 16 or 32) all
+ * lane) at 8 or 16; MG_SCHED_POOLS_W8 pools of 128 at 8, 16 or 32) all
  * give identical results, so tuning changes only
  * speed.  Each candidate advances a scratch copy of the set's first
  * min(n, 2^22) particles by probe_steps steps (<= 0: 1024) of size dt with
@@ -520,24 +520,23 @@ void mg_batch_destroy(mg_batch *b);
  * and takes that result (n_probes 0, no probe times); after probing it
  * appends one JSON line with the key and the choice.  Lines that do not
  * parse are skipped; a file that cannot be read or written is ignored.
- * Sets created with
- * schedule MG_SCHED_AUTO are tuned this way by the first mg_simulate at a dt
- * that finds 20 times the probes' particle-steps run on the graph at that dt
- * by untuned sets (at once where a result is known, or MG_TUNE_CACHE names a
- * file); until then (and in a batch built from untuned sets) they use
- * MG_SCHED_POOLS_W8.  Fixed pool schedules start a partial
- * pass at 16 idle lanes.  FP64 sets have nothing to probe (their set's FP64 schedule).  `out` (may be
- * NULL) receives the choice and the probe times.  A probe allocates scratch
- * device memory and synchronises the stream.
+ * Sets created with schedule MG_SCHED_AUTO are tuned this way by the first
+ * mg_simulate at a dt that finds 20 times the probes' particle-steps run on
+ * the graph at that dt by untuned sets (at once where a result is known, or
+ * MG_TUNE_CACHE names a file); until then (and in a batch built from untuned
+ * sets) they use MG_SCHED_POOLS_W8.  Fixed pool schedules start a partial
+ * pass at 16 idle lanes.  FP64 sets have nothing to probe (their set's FP64
+ * schedule).  `out` (may be NULL) receives the choice and the probe times.  A
+ * probe allocates scratch device memory and synchronises the stream.
  */
 typedef struct {
   int32_t schedule;      /* MG_SCHED_LANES, _POOLS, _POOLS256 or _POOLS_W8 */
   int32_t idle_trigger;  /* pools: idle lanes that start a partial split pass */
   int32_t pool_size;     /* pools: particles per wave (128 or 256), else 0 */
-  int32_t window;        /* first sub-steps per lane and pass (4 or 8) */
+  int32_t window;        /* 8: MG_SCHED_POOLS_W8; 4: the other pools */
   int32_t n_probes;      /* entries used in probe_ms */
   float probe_ms[12];    /* lanes, pools128@4, @8, @16, @32, pools256@8, @16,
-                            pools128 8-step windows@8, @16, @32 */
+                            MG_SCHED_POOLS_W8@8, @16, @32 */
   int32_t steps_per_launch;  /* 0: a whole call per launch; else the chunk */
   float launch_ms[2];    /* the chosen schedule over 2 probe_steps steps: one
                             launch, two launches of probe_steps */
