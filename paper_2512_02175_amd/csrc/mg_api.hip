@@ -189,8 +189,8 @@ struct mg_graph {
   std::vector<uint8_t> at_infinity;  // [V]
   // some edge has higher coefficients (mu beyond affine or sigma(x) not
   // constant), some vertex is a Wentzell vertex; gen: either (the kernels'
-  // general instantiation; FP32 sets run the lane schedule or pools of 128
-  // with 8-step windows)
+  // general instantiation; FP32 sets run the lane schedule or
+  // MG_SCHED_POOLS_W8)
   bool poly = false;
   bool wentzell = false;
   bool gen = false;
@@ -1277,8 +1277,8 @@ static mg_status check_steps(const mg_particles *p, int64_t n_steps, double dt) 
 }
 
 // Step kernel (StepArgs::kernel) of an FP32 schedule: 0 one particle per
-// lane, 1 / 2 wave pools of 128 / 256 particles, 3 pools of 128 with
-// 8-step windows; and back.
+// lane, 1 / 2 wave pools of 128 / 256 particles, 3 pools of 128 with the
+// later refill (set_schedule); and back.
 static int32_t kernel_of(int32_t schedule) {
   switch (schedule) {
     case MG_SCHED_LANES: return 0;
@@ -1294,20 +1294,19 @@ static int32_t schedule_of(int32_t kernel) {
 }
 
 // FP32 step kernel of a set.  Automatic selection takes the autotuned
-// choice, or pools of 128 with 8-step windows until tuned (the fastest
+// choice, or MG_SCHED_POOLS_W8 until tuned (the fastest
 // schedule at the hit rates of config 2, the vascular network and the
 // batch of config 4).
 static int32_t fp32_kernel(const mg_particles *p) {
-  // cubic coefficients: the lane schedule or pools of 128 with 8-step
-  // windows (FP64 sets ignore this)
+  // cubic coefficients: the lane schedule or MG_SCHED_POOLS_W8 (FP64 sets
+  // ignore this)
   if (p->g->gen && p->prec == MG_FP32) return p->schedule == MG_SCHED_LANES ? 0 : 3;
   if (p->schedule != MG_SCHED_AUTO) return kernel_of(p->schedule);
   return p->tuned ? p->tuned_kernel : 3;
 }
 
 // FP64 step kernel of a set: the lane schedule (MG_SCHED_LANES) or wave
-// pools of 128 with 8-step windows (MG_SCHED_POOLS_W8, and the automatic
-// choice).
+// pools of 128 (MG_SCHED_POOLS_W8, and the automatic choice).
 static int32_t fp64_kernel(const mg_particles *p) {
   return p->schedule == MG_SCHED_LANES ? 0 : 3;
 }
@@ -2421,8 +2420,7 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
   a.dt = dt;
   a.probe = 1;
   // one particle per lane; pools of 128 (2 per lane) at four idle triggers;
-  // pools of 256 (4 per lane) at two; pools of 128 with 8-step windows at
-  // three
+  // pools of 256 (4 per lane) at two; MG_SCHED_POOLS_W8 at three
   constexpr int kCand = 10;
   static_assert(kCand <= (int)(sizeof(mg_tuning::probe_ms) / sizeof(float)), "probe_ms");
   const int32_t cand_kernel[kCand] = {0, 1, 1, 1, 1, 2, 2, 3, 3, 3};

@@ -2522,7 +2522,7 @@ void k_pool32_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem 
   }
 }
 
-// The same over FP64 sets: FP64 wave pools (128 per wave, 8-step windows).
+// The same over FP64 sets: FP64 wave pools (128 per wave).
 template <bool TRACE, bool LDS, bool STAGED, bool OBS, int GEN = 0>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEN == kGenFull ? 3 : MG_POOL64_WAVES_PER_EU)))
 void k_pool64_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem *items,
@@ -2984,20 +2984,34 @@ uint32_t device_cus() {
 // 964 / 822 / 1078 / 1465); 3e5 (1986 / 1914 / 3135 / -, 1266 / 1298 / 2065
 // / -).  The lanes that stand idle before a refill or a partial split pass
 // shrink with the pool.
-uint32_t set_pool(StepArgs &a, uint32_t n, int32_t pool) {
+//
+// The reservations of a launch of 32 steps or more also leave every SIMD
+// eight of them (or a pool's worth each), and in FP32 64 particles a wave last
+// up to six waves a SIMD (FP64 has three or four: 2e5 particles with tabulated
+// coefficients 3.7 ms at 128, 4.1 at 64).  A reservation is one wave's serial
+// work, and the 240 ids
+// that keep the counter's updates cheap at 500 steps left 3e5 particles to
+// 1250 waves.  FP32, 500 steps of 1.5e5 / 3e5 / 1e6 / 3e6 particles on the
+// 64-edge star 0.80 / 0.90 / 1.46 / 2.51 -> 0.47 / 0.63 / 1.18 / 2.51 ms, 50
+// steps 0.14 / 0.22 / 0.46 / 0.60 -> 0.12 / 0.17 / 0.29 / 0.44; on the 5-edge
+// star with 2 hits a step 12.4 / 13.8 / 21.3 / 41.3 -> 4.6 / 6.2 / 14.9 / 41.6.
+// Shorter launches are bound by the updates and keep the large reservations.
+uint32_t set_pool(StepArgs &a, uint32_t n, int32_t pool, bool fp64) {
   const uint32_t simds = 4u * device_cus();
   uint32_t cap = (uint32_t)pool;
   if (n <= 16u * simds)
     cap = 16;
   else if (n <= 32u * simds)
     cap = 32;
-  else if (n <= 2u * 64u * simds)
+  else if (n <= (a.nsteps >= 32u && !fp64 ? 6u : 2u) * 64u * simds)
     cap = 64;
   const int32_t lanes = (int32_t)std::min<uint32_t>(cap, 64u);
   a.pool_cap = cap;
   a.idle = std::max(1, a.idle * lanes / 64);
   a.refill = std::max(1, a.refill * lanes / 64);
   if (cap < (uint32_t)pool) a.claim_chunk = std::min(a.claim_chunk, cap);
+  if (a.nsteps >= 32u)
+    a.claim_chunk = std::min(a.claim_chunk, std::max(cap, (n / (8u * simds)) & ~15u));
   const uint32_t per_block = cap * kWavesPerBlock;
   return (n + per_block - 1) / per_block;
 }
@@ -3009,12 +3023,12 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
   const bool obs = s.obs != nullptr;
   if constexpr (FP64) {
     if (a.kernel == 3) {
-      // FP64 wave pools (128 per wave, 8-step windows) on a resident grid
+      // FP64 wave pools (128 per wave) on a resident grid
       const LdsPlan lp = plan_lds(true, g.nnz, g.stage_bytes64,
                                   pool_lds_bytes<kPoolSmall, true, TRACE>(obs) * kWavesPerBlock, &s,
                                   g.E);
       a.obs_lds = lp.obs_lds;
-      const uint32_t need = set_pool(a, s.n, kPoolSmall);
+      const uint32_t need = set_pool(a, s.n, kPoolSmall, true);
       hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(64), 0, st, s.work);
       with_gen(g.gen, [&](auto Gn) {
         constexpr int gn = decltype(Gn)::value;
@@ -3038,7 +3052,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                                   pool_lds_bytes<PW, false, TRACE>(obs) * kWavesPerBlock,
                                   &s, g.E);
       a.obs_lds = lp.obs_lds;
-      const uint32_t need = set_pool(a, s.n, PW);
+      const uint32_t need = set_pool(a, s.n, PW, false);
       hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(64), 0, st, s.work);
       if (!TRACE && !obs && a.probe) {
         with_flags([&](auto L, auto T) {
@@ -3109,8 +3123,8 @@ KernelLaunch batch_launch_t(int32_t n_items, int32_t max_nnz, int32_t max_stage,
   k.grid = dim3(n_items);
   k.block = dim3(kBlock);
   k.persistent = false;
-  // FP32: the wave pools of the set's schedule (only pools of 128 with
-  // 8-step windows for the general levels); FP64: its wave pools
+  // FP32: the wave pools of the set's schedule (only MG_SCHED_POOLS_W8 for
+  // the general levels); FP64: its wave pools
   const bool pools = FP64 ? a.kernel == 3 : (a.kernel >= 1 && (!gen || a.kernel == 3));
   with_pool(a.kernel, [&](auto PWc) {
     constexpr int PW = decltype(PWc)::value;
