@@ -524,8 +524,9 @@ void mg_batch_destroy(mg_batch *b);
  * mg_simulate at a dt that finds 20 times the probes' particle-steps run on
  * the graph at that dt by untuned sets (at once where a result is known, or
  * MG_TUNE_CACHE names a file); until then (and in a batch built from untuned
- * sets) they use MG_SCHED_POOLS_W8.  Fixed pool schedules start a partial
- * pass at 16 idle lanes.  FP64 sets have nothing to probe (their set's FP64
+ * sets) they use MG_SCHED_POOLS_W8 (a set alone MG_SCHED_LANES where the
+ * drift towards an end takes most steps to a vertex on every edge).  Fixed
+ * pool schedules start a partial pass at 16 idle lanes.  FP64 sets have nothing to probe (their set's FP64
  * schedule).  `out` (may be NULL) receives the choice and the probe times.  A
  * probe allocates scratch device memory and synchronises the stream.
  */
