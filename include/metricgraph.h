@@ -334,8 +334,9 @@ mg_status mg_histogram_csr_noalloc(const mg_particles *p, const int32_t *bin_off
  * stationary density after burn-in, Sec. 4.1's error measurement).  The
  * accumulator starts at zero; calling again discards it and starts a new
  * one; every = 0 turns streaming off.  Allocates device memory for the
- * accumulator (outside any arena); first waits for all work on the device
- * (a batch may run the set on another stream).  Batched sets stream too.
+ * accumulator and a 16-byte record per edge (outside any arena); first waits
+ * for all work on the device, and for the set's stream before it returns (a
+ * batch may run the set on another stream).  Batched sets stream too.
  */
 mg_status mg_observe_histogram(mg_particles *p, int32_t bins_per_edge, int32_t every);
 

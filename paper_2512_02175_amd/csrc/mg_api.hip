@@ -1596,9 +1596,11 @@ mg_status mg_observe_histogram(mg_particles *p, int32_t bins_per_edge, int32_t e
   double2 *edges = (double2 *)((char *)mem + o_edge);
   he = hipMemsetAsync(mem, 0, bytes, p->stream);
   if (he == hipSuccess) he = launch_obs_edges(p->g->gd, bins_per_edge, edges, p->stream);
+  // both are in place before a batch may run the set on another stream
+  if (he == hipSuccess) he = hipStreamSynchronize(p->stream);
   if (he != hipSuccess) {
     (void)hipFree(mem);
-    return hip_fail(he, "clearing the streamed histogram");
+    return hip_fail(he, "setting up the streamed histogram");
   }
   p->sd.obs = mem;
   p->sd.obs_edge = edges;
