@@ -25,6 +25,13 @@
  *    stream).  Calls that return results synchronise that stream.  An error
  *    found by a kernel (state out of range, non-finite position) is reported
  *    as MG_EDEVICE by the next call that synchronises.
+ *  - mg_histogram, mg_histogram_csr, mg_exit_counts, mg_observed_histogram and
+ *    mg_particles_read bring results to host memory through staging blocks
+ *    (pinned host memory of 256 KiB or 8 MiB; for the histograms' counters
+ *    also device memory of 256 KiB or 16 MiB), allocated when first needed.
+ *    At most four free blocks of a size are kept per device, until the last
+ *    graph is destroyed.  Where a block cannot be had, a call copies without
+ *    one.
  */
 #ifndef METRICGRAPH_H
 #define METRICGRAPH_H

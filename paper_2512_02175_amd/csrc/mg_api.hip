@@ -303,11 +303,12 @@ SetLayout set_layout(int32_t V, int32_t nnz, int64_t n, mg_precision prec, bool 
 // the four arrays of mg_exit_counts and the error word took about 60 us, and
 // mg_particles_read a pass over the particles on the host besides.)
 //
-// Staging blocks, pinned memory and device counters of two sizes, are kept in
-// one pool per process, by device: taken by a call for as long as it lasts
-// (it waits for its stream before it gives the block back, so blocks never
-// carry work from one stream to another), at most kStagingKeep free ones of
-// a size are kept, and all are freed when the last graph is destroyed.
+// Staging blocks, pinned memory of two sizes and (made when a call first asks
+// for them) as many device counters, are kept in one pool per process, by
+// device: taken by a call for as long as it lasts (it waits for its stream
+// before it gives the block back, so blocks never carry work from one stream
+// to another), at most kStagingKeep free ones of a size are kept, and all are
+// freed when the last graph is destroyed.
 struct Staging {
   int device = -1;
   int cls = 0;
@@ -342,59 +343,73 @@ void staging_graphs(int change) {
     if (s) staging_free(s);
 }
 
-// A call's block: null when none could be had (the caller then copies
-// straight to its destination).
+// A call's block, with device counters if it wants some: null when none could
+// be had (the caller then copies straight to its destination).
 class Lease {
  public:
   explicit Lease(size_t host, size_t dev = 0) {
     if (dev > kStagingDev[1]) return;
     const int cls = host > kStagingHost[0] || dev > kStagingDev[0] ? 1 : 0;
-    s_ = take(cls);
+    s_ = take(cls, dev > 0);
     // a smaller block also carries a readback, in more pieces
-    if (!s_ && cls == 1 && dev == 0) s_ = take(0);
+    if (!s_ && cls == 1 && dev == 0) s_ = take(0, false);
+    if (s_ && dev && !s_->dev &&
+        hipMalloc((void **)&s_->dev, kStagingDev[s_->cls]) != hipSuccess) {
+      (void)hipGetLastError();
+      s_->dev = nullptr;
+      give_back();
+    }
   }
   Lease(const Lease &) = delete;
   Lease &operator=(const Lease &) = delete;
   ~Lease() {
-    if (!s_) return;
-    {
-      std::lock_guard<std::mutex> lock(g_staging_mu);
-      int same = 0;
-      Staging **slot = nullptr;
-      for (Staging *&f : g_staging) {
-        if (f) same += f->device == s_->device && f->cls == s_->cls;
-        else if (!slot) slot = &f;
-      }
-      if (g_live_graphs > 0 && same < kStagingKeep && slot) {
-        *slot = s_;
-        return;
-      }
-    }
-    staging_free(s_);
+    if (s_) give_back();
   }
   Staging *operator->() const { return s_; }
   explicit operator bool() const { return s_ != nullptr; }
   size_t host_bytes() const { return kStagingHost[s_->cls]; }
 
  private:
-  static Staging *take(int cls) {
+  void give_back() {
+    Staging *const b = s_;
+    s_ = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(g_staging_mu);
+      int same = 0;
+      Staging **slot = nullptr;
+      for (Staging *&f : g_staging) {
+        if (f) same += f->device == b->device && f->cls == b->cls;
+        else if (!slot) slot = &f;
+      }
+      if (g_live_graphs > 0 && same < kStagingKeep && slot) {
+        *slot = b;
+        return;
+      }
+    }
+    staging_free(b);
+  }
+  // a free block, of those with or without counters first, or a new one
+  static Staging *take(int cls, bool counters) {
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return nullptr;
     {
       std::lock_guard<std::mutex> lock(g_staging_mu);
+      Staging **best = nullptr;
       for (Staging *&f : g_staging)
-        if (f && f->device == device && f->cls == cls) {
-          Staging *s = f;
-          f = nullptr;
-          return s;
-        }
+        if (f && f->device == device && f->cls == cls &&
+            (!best || ((f->dev != nullptr) == counters && ((*best)->dev != nullptr) != counters)))
+          best = &f;
+      if (best) {
+        Staging *s = *best;
+        *best = nullptr;
+        return s;
+      }
     }
     Staging *s = new (std::nothrow) Staging();
     if (!s) return nullptr;
     s->device = device;
     s->cls = cls;
     hipError_t he = hipHostMalloc((void **)&s->host, kStagingHost[cls], 0);
-    if (he == hipSuccess) he = hipMalloc((void **)&s->dev, kStagingDev[cls]);
     for (hipEvent_t &e : s->ev)
       if (he == hipSuccess) he = hipEventCreateWithFlags(&e, hipEventDisableTiming);
     if (he != hipSuccess) {
@@ -1685,6 +1700,47 @@ mg_status mg_exit_counts(const mg_particles *p, uint64_t *slot_counts, uint64_t 
   return rb.finish("copying the counters");
 }
 
+// mg_particles_read's range by plain copies into pageable memory, a piece at a
+// time, converted on the host: for a call that can have no staging block.
+static mg_status read_plain(const mg_particles *p, int64_t first, int64_t count, int32_t *edge,
+                            double *pos, uint8_t *alive, uint64_t *seqhash, uint32_t *hits) {
+  auto get = [&](void *dst, const void *src, int64_t n, size_t each) {
+    return hipMemcpyAsync(dst, src, (size_t)n * each, hipMemcpyDeviceToHost, p->stream);
+  };
+  if (seqhash) MG_HIP(get(seqhash, p->sd.seqhash + first, count, 8), "copying hashes");
+  if (hits) MG_HIP(get(hits, p->sd.hits + first, count, 4), "copying hit counts");
+  constexpr int64_t kPiece = 4096;
+  uint32_t ef[kPiece];
+  double x[kPiece];
+  static_assert(sizeof(float2) == sizeof(double), "one position");
+  for (int64_t at = 0; at < count; at += kPiece) {
+    const int64_t n = std::min(kPiece, count - at);
+    hipError_t he = get(ef, p->sd.ef + first + at, n, 4);
+    if (he == hipSuccess && pos)
+      he = get(x, p->prec == MG_FP64 ? (const void *)(p->sd.x64 + first + at)
+                                     : (const void *)(p->sd.y32 + first + at), n, 8);
+    // (also after an error: the pieces are this call's own)
+    const hipError_t hs = hipStreamSynchronize(p->stream);
+    if (he == hipSuccess) he = hs;
+    if (he != hipSuccess) return hip_fail(he, "reading the particles");
+    for (int64_t i = 0; i < n; ++i) {
+      const int32_t e = (int32_t)(ef[i] & kEdgeMask);
+      if (edge) edge[at + i] = e;
+      if (alive) alive[at + i] = (ef[i] & kDeadBit) ? 0 : 1;
+      if (!pos) continue;
+      if (p->prec == MG_FP64) {
+        pos[at + i] = x[i];
+      } else {
+        float v[2];
+        std::memcpy(v, &x[i], 8);
+        const double y = (double)v[0] + (double)v[1];
+        pos[at + i] = (ef[i] & kSideBit) ? (e < p->g->E ? p->g->length[e] : 0.0) - y : y;
+      }
+    }
+  }
+  return check_device_error(p);
+}
+
 mg_status mg_particles_read(const mg_particles *p, int64_t first, int64_t count,
                             int32_t *edge, double *pos, uint8_t *alive, uint64_t *seqhash,
                             uint32_t *hits) {
@@ -1710,7 +1766,7 @@ mg_status mg_particles_read(const mg_particles *p, int64_t first, int64_t count,
                       (hits ? 4 : 0);
   if (each == 0) return check_device_error(p);
   const Lease st(std::min(2 * ((size_t)count * each + 64), kStagingHost[1]));
-  if (!st) return fail(MG_ENOMEM, "no staging memory for the readback");
+  if (!st) return read_plain(p, first, count, edge, pos, alive, seqhash, hits);
   const size_t half = st.host_bytes() / 2;
   const int64_t most = (int64_t)((half - 64) / each) & ~63ll;
   // the device error word, in the last bytes of the block

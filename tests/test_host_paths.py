@@ -31,3 +31,64 @@ l = log()
 last = max(i for i, x in enumerate(l) if "k_obs_edges" in x or x.startswith("memset"))
 assert any(x == "sync stream=0x77" or x == "sync_device" for x in l[last + 1:]), l
 """)
+
+
+@pytest.mark.parametrize("name", ["hipHostMalloc", "hipMalloc"])
+def test_readback_without_staging_memory(stub, name):
+    """No pinned (or no device) memory for a staging block: every call that read
+    its results without allocating any still returns them."""
+    stub(f"name = {name!r}" + """
+def results(p, trace):
+    r = B.mg_particles_read(p, 3, 9000, trace=trace)
+    return ([r[k] for k in r] + [B.mg_particles_read(p)["x"]] + list(B.mg_exit_counts(p))
+            + list(B.mg_observed_histogram(p)))
+G = B.mg_graph_create(workloads.star_graph(5, [0.5, 1.0, 1.5, 2.0, 2.5]))
+for prec in (0, 1):
+    for trace in (False, True):
+        p = B.mg_particles_init(G, 10_001, 2, precision=prec, trace=trace)
+        img = B.mg_particles_save(p)
+        # states of every kind: edges, both reference ends, removed particles
+        i = np.arange(10_001)
+        ef = (i % 5).astype(np.uint32)
+        if prec:
+            ef |= ((i // 5) % 2).astype(np.uint32) << 30
+        ef |= (i % 7 == 0).astype(np.uint32) << 31
+        img[96:96 + 4 * i.size] = ef.view(np.uint8)
+        at = 96 + -(-4 * i.size // 8) * 8
+        x = (0.4 * i / i.size)
+        x = x.astype(np.float32) if prec else x
+        img[at:at + 8 * i.size] = (np.stack([x, x * np.float32(1e-9)], 1).copy().view(np.uint8).ravel()
+                                   if prec else x.view(np.uint8))
+        p = B.mg_particles_load(G, img)
+        B.mg_observe_histogram(p, 7, 3)
+        want = results(p, trace)
+        for q in (p, None):
+            if q is None:                     # and with no block kept from before
+                del p
+                G2 = G; B.mg_graph_destroy(G)
+                G = B.mg_graph_create(workloads.star_graph(5, [0.5, 1.0, 1.5, 2.0, 2.5]))
+                q = B.mg_particles_load(G, img)
+                B.mg_observe_histogram(q, 7, 3)
+            fail(name)
+            got = results(q, trace)
+            fail("")
+            assert all(np.array_equal(a, b) for a, b in zip(want, got)), (prec, trace)
+        del q
+""")
+
+
+def test_a_readback_takes_no_device_memory(stub):
+    stub("""
+G = B.mg_graph_create(workloads.star_graph(5))
+p = B.mg_particles_init(G, 100_001, 2, precision=1)
+B.mg_observe_histogram(p, 7, 3)
+log()
+B.mg_particles_read(p), B.mg_exit_counts(p), B.mg_observed_histogram(p)
+out = C.c_void_p(S.stub_device_block(8 * 50))
+assert L.mg_histogram(p.handle, 10, out, 50) == 0
+assert not [x for x in log() if x.startswith("malloc")]
+B.mg_histogram(p, 10)                       # its counters
+assert len([x for x in log() if x.startswith("malloc")]) == 1
+B.mg_histogram(p, 10)                       # kept
+assert not [x for x in log() if "malloc" in x]
+""")
