@@ -448,6 +448,14 @@ class Readback {
     if (dst && bytes) seg_[n_++] = {dst, src, bytes};
   }
   mg_status finish(const char *what) {
+    const mg_status st = copy(what);
+    // after an error too, nothing queued is left that uses a block of the call
+    if (st != MG_OK) (void)hipStreamSynchronize(p_->stream);
+    return st;
+  }
+
+ private:
+  mg_status copy(const char *what) {
     size_t total = 16;
     bool host = true;
     for (int i = 0; i < n_; ++i) {
@@ -464,7 +472,6 @@ class Readback {
     return check_device_error(p_);
   }
 
- private:
   struct Seg {
     void *dst;
     const void *src;
@@ -531,10 +538,7 @@ class Readback {
       }
     drain(0);
     drain(1);
-    if (he != hipSuccess) {
-      (void)hipStreamSynchronize(p_->stream);
-      return hip_fail(he, what);
-    }
+    if (he != hipSuccess) return hip_fail(he, what);
     return check_device_error(p_);
   }
 };

@@ -92,3 +92,34 @@ assert len([x for x in log() if x.startswith("malloc")]) == 1
 B.mg_histogram(p, 10)                       # kept
 assert not [x for x in log() if "malloc" in x]
 """)
+
+
+@pytest.mark.parametrize("call", ["histogram", "csr", "exits", "observed", "read"])
+def test_a_block_is_given_back_without_work_on_it(stub, call):
+    """After a failed launch the call waits for what it had queued before its
+    staging blocks go back to the pool."""
+    stub(f"call = {call!r}" + """
+E = 5000
+G = B.mg_graph_create(workloads.star_graph(E))
+st = C.c_void_p(0x77)
+p = B.mg_particles_init(G, 700_001, 2, stream=st)
+B.mg_observe_histogram(p, 300, 3)           # 12 MB of counters: several pieces
+off = (np.arange(E + 1) * 4).astype(np.int32)
+up = np.tile([0.25, 0.5, 0.75, 1.0], E)
+f = {"histogram": lambda: B.mg_histogram(p, 100), "csr": lambda: B.mg_histogram_csr(p, off, up),
+     "exits": lambda: B.mg_exit_counts(p), "observed": lambda: B.mg_observed_histogram(p),
+     "read": lambda: B.mg_particles_read(p)}[call]
+log()
+f()
+n = len([x for x in log() if x.startswith("launch")])
+for k in range(n):
+    fail("hipLaunchKernel", skip=k, count=1)
+    try:
+        f()
+        assert False
+    except B.MgError as e:
+        assert e.status == B.MG_EDEVICE
+    l = log()
+    last = max([i for i, x in enumerate(l) if x.startswith(("launch ", "copy "))], default=-1)
+    assert last < 0 or "sync stream=0x77" in l[last + 1:], (k, l)
+""")
