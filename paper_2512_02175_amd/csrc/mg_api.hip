@@ -224,6 +224,7 @@ struct mg_particles {
   SetDev sd{};
   uint64_t step = 0;
   uint64_t obs_start = 0;  // step counter when the streamed histogram started
+  int device = -1;         // where the set's memory is
   void *ev_mem = nullptr;  // event trace: counter, ids and records
 };
 
@@ -342,6 +343,27 @@ void staging_graphs(int change) {
   for (Staging *s : drop)
     if (s) staging_free(s);
 }
+
+// The set's device made the calling thread's current one for as long as a
+// readback lasts: its kernels, blocks and events belong to that device, and a
+// caller may have another one current (copies did not depend on it).
+class OnDevice {
+ public:
+  explicit OnDevice(const mg_particles *p) {
+    int now = -1;
+    if (p->device >= 0 && hipGetDevice(&now) == hipSuccess && now != p->device &&
+        hipSetDevice(p->device) == hipSuccess)
+      was_ = now;
+  }
+  OnDevice(const OnDevice &) = delete;
+  OnDevice &operator=(const OnDevice &) = delete;
+  ~OnDevice() {
+    if (was_ >= 0) (void)hipSetDevice(was_);
+  }
+
+ private:
+  int was_ = -1;
+};
 
 // A call's block, with device counters if it wants some: null when none could
 // be had (the caller then copies straight to its destination).
@@ -1139,6 +1161,11 @@ static mg_status alloc_set(const mg_graph *g, int64_t n, const mg_options &o,
     }
     p->owns = true;
   }
+  hipPointerAttribute_t attr;
+  if (hipPointerGetAttributes(&attr, p->mem) == hipSuccess)
+    p->device = attr.device;
+  else
+    (void)hipGetLastError();
   char *base = (char *)p->mem;
   SetDev &s = p->sd;
   s.ef = (uint32_t *)(base + L.ef);
@@ -1463,6 +1490,7 @@ mg_status mg_histogram(const mg_particles *p, int32_t bins_per_edge, uint64_t *o
   if (need > 0x7FFFFFFF) return fail(MG_EINVAL, "E * bins_per_edge too large");
   if (out_len < need) return fail(MG_EINVAL, "out_len %lld < E * bins_per_edge = %lld",
                                   (long long)out_len, (long long)need);
+  const OnDevice on(p);
   const bool dev_out = is_device_pointer(out);
   // a host output's counters: in a staging block, or allocated if they exceed
   // one
@@ -1499,6 +1527,7 @@ mg_status mg_histogram_csr(const mg_particles *p, const int32_t *bin_offsets,
   int64_t nbins = 0;
   const mg_status vs = check_csr_bins(p, bin_offsets, bin_upper, out, out_len, &nbins);
   if (vs != MG_OK) return vs;
+  const OnDevice on(p);
   const int32_t E = p->g->E;
   const bool dev_out = is_device_pointer(out);
   const size_t o_off = 0, o_up = align_up(sizeof(int32_t) * (E + 1), 256),
@@ -1640,6 +1669,7 @@ mg_status mg_observed_histogram(const mg_particles *p, uint64_t *out, int64_t ou
       return fail(MG_EINVAL, "out_len %lld < E * bins_per_edge = %lld", (long long)out_len,
                   (long long)need);
   }
+  const OnDevice on(p);
   Readback rb(p);
   rb.add(out, p->sd.obs, (size_t)need * 8);
   const mg_status st = rb.finish("copying the streamed histogram");
@@ -1697,6 +1727,7 @@ mg_status mg_exit_counts(const mg_particles *p, uint64_t *slot_counts, uint64_t 
                          uint64_t *totals) {
   g_err.clear();
   if (!p) return fail(MG_EINVAL, "particles is NULL");
+  const OnDevice on(p);
   Readback rb(p);
   rb.add(slot_counts, p->sd.exit_cnt, (size_t)p->g->nnz * 8);
   rb.add(absorbed, p->sd.absorbed, (size_t)p->g->V * 8);
@@ -1753,6 +1784,7 @@ mg_status mg_particles_read(const mg_particles *p, int64_t first, int64_t count,
   if (first < 0 || count < 0 || first + count > p->n) return fail(MG_EINVAL, "range out of bounds");
   if ((seqhash || hits) && !p->trace) return fail(MG_ESTATE, "the set was created without trace");
   if (count == 0) return MG_OK;
+  const OnDevice on(p);
   // hashes and hit counts wanted in device memory go there directly
   if (seqhash && is_device_pointer(seqhash)) {
     MG_HIP(hipMemcpyAsync(seqhash, p->sd.seqhash + first, (size_t)count * 8, hipMemcpyDefault,

@@ -123,3 +123,29 @@ for k in range(n):
     last = max([i for i, x in enumerate(l) if x.startswith(("launch ", "copy "))], default=-1)
     assert last < 0 or "sync stream=0x77" in l[last + 1:], (k, l)
 """)
+
+
+def test_readback_on_the_sets_device(stub):
+    """With another device current, the results of a set come through kernels,
+    blocks and events of its own device, and the current one is restored."""
+    stub("""
+E = 5000
+S.stub_device(1)
+g = workloads.star_graph(E)
+G = B.mg_graph_create(g)
+p = B.mg_particles_init(G, 700_001, 2)
+B.mg_observe_histogram(p, 300, 3)
+S.stub_device(0)
+off = (np.arange(E + 1) * 4).astype(np.int32)
+up = np.tile([0.25, 0.5, 0.75, 1.0], E)
+log()
+for f in (lambda: B.mg_particles_read(p), lambda: B.mg_exit_counts(p),
+          lambda: B.mg_observed_histogram(p), lambda: B.mg_histogram(p, 100),
+          lambda: B.mg_histogram_csr(p, off, up)):
+    f()
+    l = log()
+    seen = [x for x in l if "device=" in x]
+    assert seen and all("device=1" in x for x in seen), l
+    q = B.mg_particles_init(G, 10, 2)       # still the caller's
+    assert any(x.startswith("malloc") and "device=0" in x for x in log())
+""")
