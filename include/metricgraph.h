@@ -536,7 +536,8 @@ void mg_batch_destroy(mg_batch *b);
  * drift towards an end takes most steps to a vertex on every edge).  Fixed
  * pool schedules start a partial pass at 16 idle lanes.  FP64 sets have nothing to probe (their set's FP64
  * schedule).  `out` (may be NULL) receives the choice and the probe times.  A
- * probe allocates scratch device memory and synchronises the stream.
+ * probe allocates scratch device memory and synchronises the stream; a
+ * mg_simulate call on a stream under capture never probes.
  */
 typedef struct {
   int32_t schedule;      /* MG_SCHED_LANES, _POOLS, _POOLS256 or _POOLS_W8 */

@@ -1428,19 +1428,28 @@ static bool due_tuning(const mg_particles *p, int64_t n_steps, double dt) {
       20 * (10.0 * 1024 + 2 * 2048) * (double)std::min<int64_t>(p->n, 1 << 22);
   const char *file = std::getenv("MG_TUNE_CACHE");
   // (a probe that would pass step 2^32 is refused by mg_autotune)
-  if ((file && *file) || p->step + 2ull * 1024 > 0xFFFFFFFFull) return true;
-  std::lock_guard<std::mutex> lock(p->g->tune_mu);
-  for (const auto &c : p->g->tune_cache)
-    if (c.first == dt) return true;
-  for (auto &w : p->g->tune_work)
-    if (w.first == dt) {
-      if (w.second >= pays) return true;
-      w.second += (double)n_steps * (double)p->n;
-      return false;
+  bool due = (file && *file) || p->step + 2ull * 1024 > 0xFFFFFFFFull;
+  {
+    std::lock_guard<std::mutex> lock(p->g->tune_mu);
+    for (const auto &c : p->g->tune_cache)
+      if (c.first == dt) return true;
+    auto &work = p->g->tune_work;
+    auto w = std::find_if(work.begin(), work.end(), [&](const auto &x) { return x.first == dt; });
+    if (w != work.end()) {
+      due = due || w->second >= pays;
+      w->second += (double)n_steps * (double)p->n;
+    } else if (work.size() < 1024) {
+      work.emplace_back(dt, (double)n_steps * (double)p->n);
     }
-  if (p->g->tune_work.size() < 1024)
-    p->g->tune_work.emplace_back(dt, (double)n_steps * (double)p->n);
-  return false;
+  }
+  // a probe allocates and waits: none inside a capture, which runs the default
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (due && (hipStreamIsCapturing(p->stream, &cap) != hipSuccess ||
+              cap != hipStreamCaptureStatusNone)) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return due;
 }
 
 mg_status mg_simulate(mg_particles *p, int64_t n_steps, double dt, uint64_t seed) {

@@ -149,3 +149,29 @@ for f in (lambda: B.mg_particles_read(p), lambda: B.mg_exit_counts(p),
     q = B.mg_particles_init(G, 10, 2)       # still the caller's
     assert any(x.startswith("malloc") and "device=0" in x for x in log())
 """)
+
+
+def test_no_probe_inside_a_capture(stub):
+    """A set that has run may be captured: the call only launches, also where its
+    graph has become due for tuning or a tuning file is named."""
+    code = """
+G = B.mg_graph_create(workloads.star_graph(5))
+p = B.mg_particles_init(G, 100, 2, precision=1)
+%s
+S.stub_capture(1)
+log()
+for dt in (1e-2, 1e-3):
+    B.mg_simulate(p, 10, dt, 1)
+    l = log()
+    assert all(x.startswith("launch") for x in l) and steps(l) and not any("probe" in x for x in l), l
+S.stub_capture(0)
+B.mg_simulate(p, 10, 1e-2, 1)
+assert any("probe" in x for x in log())
+S.stub_capture(1)                           # a known result is taken
+q = B.mg_particles_init(G, 100, 2, precision=1)
+log()
+B.mg_simulate(q, 10, 1e-2, 1)
+assert steps(log())[0][2]["kernel"] == 0    # (the first of equal probes)
+"""
+    stub(code % f"B.mg_simulate(p, {20 * 14336}, 1e-2, 1)")
+    stub(code % "", MG_TUNE_CACHE="/nonexistent/tune")
