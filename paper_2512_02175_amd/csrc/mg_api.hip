@@ -1358,7 +1358,13 @@ static int32_t fp32_kernel(const mg_particles *p) {
   return p->tuned ? p->tuned_kernel : 3;
 }
 
-// The FP32 kernel of an untuned automatic set at dt.  Where the drift takes a
+// The schedule of a set at dt: a tuned choice holds at the dt it was timed at.
+static bool tuned_at(const mg_particles *p, double dt) {
+  return p->schedule == MG_SCHED_AUTO && p->tuned && p->tuned_dt == dt;
+}
+
+// The FP32 kernel of a set at dt: the tuned choice or, for an automatic set
+// that is untuned there, the default.  Where the drift takes a
 // particle to an end of its edge by 0.85 of a step's noise or more, on every
 // edge, most steps make several hits and a pool would run little but split
 // passes: one particle per lane.  500 steps of 3e5 / 1e6 / 3e6 particles on
@@ -1366,9 +1372,9 @@ static int32_t fp32_kernel(const mg_particles *p) {
 // pools: dt 10^-2 (1.0 of a step's noise, 4.0 hits a step) 7.2 / 19.4 / 51.9
 // against 9.3 / 23.3 / 65.3 ms, 5 10^-3 (0.71) 7.1 / 19.0 / 51.2 against
 // 6.2 / 14.9 / 41.6.
-static int32_t untuned_fp32_kernel(const mg_particles *p, double dt) {
-  if (p->schedule != MG_SCHED_AUTO || p->g->gen || p->tuned) return fp32_kernel(p);
-  return p->g->pull * std::sqrt(dt) >= 0.85 ? 0 : fp32_kernel(p);
+static int32_t fp32_kernel_at(const mg_particles *p, double dt) {
+  if (p->schedule != MG_SCHED_AUTO || p->g->gen || tuned_at(p, dt)) return fp32_kernel(p);
+  return p->g->pull * std::sqrt(dt) >= 0.85 ? 0 : 3;
 }
 
 // FP64 step kernel of a set: the lane schedule (MG_SCHED_LANES) or wave
@@ -1383,6 +1389,9 @@ static int32_t step_kernel(const mg_particles *p) {
 
 static int32_t pool_idle(const mg_particles *p) {
   return (p->schedule == MG_SCHED_AUTO && p->tuned) ? p->tuned_idle : 16;
+}
+static int32_t pool_idle_at(const mg_particles *p, double dt) {
+  return tuned_at(p, dt) ? p->tuned_idle : 16;
 }
 
 // Schedule fields of a launch: the kernel, the idle lanes that start a
@@ -1469,13 +1478,12 @@ mg_status mg_simulate(mg_particles *p, int64_t n_steps, double dt, uint64_t seed
   a.key0 = (uint32_t)seed;
   a.key1 = (uint32_t)(seed >> 32);
   a.dt = dt;
-  set_schedule(a, p->prec == MG_FP32 ? untuned_fp32_kernel(p, dt) : step_kernel(p),
-               pool_idle(p), p->prec == MG_FP64,
+  set_schedule(a, p->prec == MG_FP32 ? fp32_kernel_at(p, dt) : step_kernel(p),
+               pool_idle_at(p, dt), p->prec == MG_FP64,
                p->g->gd.stage_bytes32 > 0);
   // a set without a fixed launch length takes the tuned one
-  const uint32_t chunk = chunk_steps(
-      (p->steps_per_launch == 0 && p->tuned && p->tuned_dt == dt) ? p->tuned_spl
-                                                                    : p->steps_per_launch);
+  const uint32_t chunk = chunk_steps(p->steps_per_launch == 0 && tuned_at(p, dt)
+                                         ? p->tuned_spl : p->steps_per_launch);
   int64_t left = n_steps;
   while (left > 0) {
     const uint32_t now = (uint32_t)std::min<int64_t>(left, chunk);

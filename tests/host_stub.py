@@ -13,7 +13,6 @@ import ctypes as C, re, sys
 S = C.CDLL({so!r}, mode=C.RTLD_GLOBAL)
 S.stub_log.restype = C.c_char_p
 S.stub_device_block.restype = C.c_void_p
-S.stub_elapsed.argtypes = [C.c_float]
 sys.path.insert(0, {root!r})
 import numpy as np
 import workloads

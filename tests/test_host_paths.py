@@ -175,3 +175,38 @@ assert steps(log())[0][2]["kernel"] == 0    # (the first of equal probes)
 """
     stub(code % f"B.mg_simulate(p, {20 * 14336}, 1e-2, 1)")
     stub(code % "", MG_TUNE_CACHE="/nonexistent/tune")
+
+
+def test_a_tuned_choice_holds_at_its_time_step(stub):
+    """A set tuned at one dt runs the default at another (one particle per lane
+    where nearly every step is spent at vertices), not the tuned choice, until
+    it is tuned there; and the tuned choice again at its own."""
+    stub("""
+def ran(p, dt):
+    log()
+    B.mg_simulate(p, 5, dt, 1)
+    a = steps(log())[-1][2]
+    return a["kernel"], a["idle"]
+n = 1_000_000                               # full pools: idle as chosen
+G = B.mg_graph_create(workloads.star_graph(5))
+p = B.mg_particles_init(G, n, 2, precision=1)
+assert ran(p, 1e-2) == (3, 16)
+S.stub_fast(0)                              # lanes
+B.mg_autotune(p, 1e-2)
+assert ran(p, 1e-2)[0] == 0
+assert ran(p, 1e-3) == (3, 16)
+assert ran(p, 1e-2)[0] == 0
+S.stub_fast(5)                              # pools of 256 at 8 idle lanes
+B.mg_autotune(p, 1e-3)
+assert ran(p, 1e-3) == (2, 8)
+assert ran(p, 2e-3) == (3, 16)
+assert ran(p, 1e-2)[0] == 0                 # (known from the graph)
+# strong drift to the centre
+G = B.mg_graph_create(workloads.paper_star5("linear", np.inf))
+p = B.mg_particles_init(G, n, 1, vertex=0, precision=1)
+S.stub_fast(7)                              # MG_SCHED_POOLS_W8 at 8 idle lanes
+B.mg_autotune(p, 1e-4)
+assert ran(p, 1e-4) == (3, 8)
+assert ran(p, 2e-2)[0] == 0
+assert ran(p, 1e-3) == (3, 16)
+""")
