@@ -497,7 +497,8 @@ mg_status mg_particles_load(const mg_graph *g, const void *image, int64_t image_
  * small graphs do not run at the occupancy of the largest one; a group
  * with under 1/32 of the particles joins the next group of larger need.
  * All sets must have the same precision, max_splits, trace flag and
- * schedule; each keeps its own graph_tag, counters and step counter, and
+ * schedule (automatic FP32 sets: the same tuned choice; one that has run but
+ * is not tuned yet goes along with the tuned ones); each keeps its own graph_tag, counters and step counter, and
  * every set's results equal those of mg_simulate on that set alone.  The
  * batch references the sets, which must outlive it; it launches on the
  * first set's stream.

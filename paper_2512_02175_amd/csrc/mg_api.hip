@@ -225,6 +225,7 @@ struct mg_particles {
   uint64_t step = 0;
   uint64_t obs_start = 0;  // step counter when the streamed histogram started
   int device = -1;         // where the set's memory is
+  bool ran_default = false;  // automatic FP32 set that has run untuned
   void *ev_mem = nullptr;  // event trace: counter, ids and records
 };
 
@@ -252,6 +253,7 @@ struct mg_batch {
   bool gen = false;       // some set's graph has a general method variant
   int32_t gen_level = 0;  // the highest method-variant level of its graphs
   int32_t kernel = 1;     // step schedule fixed at creation (tile size follows it)
+  const mg_particles *schedule_of = nullptr;  // the set whose idle trigger it takes
   // Per-call set descriptors go up from pinned memory; the launch chain of a
   // call is a HIP graph of kernel nodes, re-instantiated only when the
   // call's shape (steps, dt, seed, schedule) changes.
@@ -1481,6 +1483,8 @@ mg_status mg_simulate(mg_particles *p, int64_t n_steps, double dt, uint64_t seed
   set_schedule(a, p->prec == MG_FP32 ? fp32_kernel_at(p, dt) : step_kernel(p),
                pool_idle_at(p, dt), p->prec == MG_FP64,
                p->g->gd.stage_bytes32 > 0);
+  p->ran_default = p->ran_default || (n_steps > 0 && p->prec == MG_FP32 && !p->g->gen &&
+                                      p->schedule == MG_SCHED_AUTO && !tuned_at(p, dt));
   // a set without a fixed launch length takes the tuned one
   const uint32_t chunk = chunk_steps(p->steps_per_launch == 0 && tuned_at(p, dt)
                                          ? p->tuned_spl : p->steps_per_launch);
@@ -2201,12 +2205,24 @@ mg_status mg_batch_create(int32_t n_sets, mg_particles *const *sets, mg_batch **
   if (!out) return fail(MG_EINVAL, "out is NULL");
   *out = nullptr;
   if (n_sets < 1 || !sets) return fail(MG_EINVAL, "need at least one set");
-  for (int32_t i = 0; i < n_sets; ++i) {
+  for (int32_t i = 0; i < n_sets; ++i)
     if (!sets[i]) return fail(MG_EINVAL, "set %d is NULL", i);
+  // An automatic set that has run but is not tuned yet goes along with the
+  // tuned ones (whether a set is tuned depends on how far it has run, which
+  // does not decide what sets may share a batch).
+  auto follows = [](const mg_particles *p) { return p->ran_default && !p->tuned; };
+  const mg_particles *lead = sets[0];
+  bool lead_tuned = false;
+  for (int32_t i = 0; i < n_sets && !lead_tuned; ++i)
+    if (sets[i]->schedule == MG_SCHED_AUTO && sets[i]->tuned) {
+      lead = sets[i];
+      lead_tuned = true;
+    }
+  for (int32_t i = 0; i < n_sets; ++i) {
     if (sets[i]->prec != sets[0]->prec) return fail(MG_EINVAL, "sets differ in precision");
     if (sets[i]->max_splits != sets[0]->max_splits) return fail(MG_EINVAL, "sets differ in max_splits");
     if (sets[i]->trace != sets[0]->trace) return fail(MG_EINVAL, "sets differ in trace");
-    if (step_kernel(sets[i]) != step_kernel(sets[0]))
+    if (step_kernel(sets[i]) != step_kernel(lead) && !(lead_tuned && follows(sets[i])))
       return fail(MG_EINVAL, "sets differ in schedule");
     // the FP32 general step (cubic coefficients, Wentzell vertices)
     // evaluates the coefficients at the position, the affine one uses
@@ -2219,7 +2235,8 @@ mg_status mg_batch_create(int32_t n_sets, mg_particles *const *sets, mg_batch **
   }
   mg_batch *b = new mg_batch();
   b->sets.assign(sets, sets + n_sets);
-  b->kernel = step_kernel(sets[0]);
+  b->kernel = step_kernel(lead);
+  b->schedule_of = follows(sets[0]) ? lead : sets[0];
   const bool fp64 = sets[0]->prec == MG_FP64;
   const bool trace = sets[0]->trace;
   for (int32_t i = 0; i < n_sets; ++i) {
@@ -2430,7 +2447,7 @@ mg_status mg_batch_simulate(mg_batch *b, int64_t n_steps, double dt, uint64_t se
   a.key0 = (uint32_t)seed;
   a.key1 = (uint32_t)(seed >> 32);
   a.dt = dt;
-  set_schedule(a, b->kernel, pool_idle(p0), p0->prec == MG_FP64, true);
+  set_schedule(a, b->kernel, pool_idle(b->schedule_of), p0->prec == MG_FP64, true);
   const uint32_t chunk = chunk_steps(p0->steps_per_launch);
   const int32_t n_sets = (int32_t)b->sets.size();
   // the previous call's upload must have left the pinned buffer

@@ -210,3 +210,36 @@ assert ran(p, 1e-4) == (3, 8)
 assert ran(p, 2e-2)[0] == 0
 assert ran(p, 1e-3) == (3, 16)
 """)
+
+
+def test_batches_of_tuned_and_untuned_sets(stub):
+    """Sets that ran on the automatic schedule share a batch whether or not each
+    has run far enough to be tuned; what differed in schedule still does."""
+    stub("""
+G = [B.mg_graph_create(workloads.star_graph(5 + i)) for i in range(2)]
+def make(i, **kw):
+    return B.mg_particles_init(G[i], 1000, 2, precision=1, **kw)
+far, near, new = make(0), make(1), make(1)
+lanes, pools = make(1, schedule=B.MG_SCHED_LANES), make(1, schedule=B.MG_SCHED_POOLS)
+B.mg_simulate(near, 3, 1e-2, 1)
+B.mg_simulate(far, 3, 1e-2, 1)
+B.mg_batch_create([near, far, new])         # none tuned: one default
+S.stub_fast(5)                              # pools of 256 at 8 idle lanes
+B.mg_autotune(far, 1e-2)
+def refused(*sets):
+    try:
+        B.mg_batch_create(list(sets))
+    except B.MgError as e:
+        return e.status == B.MG_EINVAL and "schedule" in str(e)
+    return False
+for sets in ([near, far], [far, near]):
+    b = B.mg_batch_create(sets)
+    log()
+    B.mg_batch_simulate(b, 4, 1e-2, 1)
+    (k, _, a), = steps(log())
+    assert "k_pool32_batch" in k and "Li256E" in k and a["kernel"] == 2 and a["idle"] == 8, (k, a)
+B.mg_autotune(lanes, 1e-2)                  # a fixed schedule stays what it is
+assert refused(far, new) and refused(far, lanes) and refused(near, lanes) and refused(lanes, near)
+assert refused(far, pools) and refused(near, pools, far)
+B.mg_batch_create([lanes, make(0, schedule=B.MG_SCHED_LANES)])
+""")
