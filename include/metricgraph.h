@@ -529,10 +529,12 @@ void mg_batch_destroy(mg_batch *b);
  * and takes that result (n_probes 0, no probe times); after probing it
  * appends one JSON line with the key and the choice.  Lines that do not
  * parse are skipped; a file that cannot be read or written is ignored.
- * Sets created with schedule MG_SCHED_AUTO are tuned this way by the first
- * mg_simulate at a dt that finds 20 times the probes' particle-steps run on
- * the graph at that dt by untuned sets (at once where a result is known, or
- * MG_TUNE_CACHE names a file); until then (and in a batch built from untuned
+ * A line stays valid across versions of the library (the choices mean the same
+ * and change no result); remove the file to have sets tuned again.
+ * Sets created with schedule MG_SCHED_AUTO are tuned this way by the
+ * mg_simulate call that brings the steps of untuned sets on the graph at its
+ * dt to 20 times the probes' particle-steps (at once where a result is known,
+ * or MG_TUNE_CACHE names a file); until then (and in a batch built from untuned
  * sets) they use MG_SCHED_POOLS_W8 (a set alone MG_SCHED_LANES where the
  * drift towards an end takes most steps to a vertex on every edge).  Fixed
  * pool schedules start a partial pass at 16 idle lanes.  FP64 sets have nothing to probe (their set's FP64

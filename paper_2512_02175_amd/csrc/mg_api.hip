@@ -1426,14 +1426,15 @@ static uint32_t chunk_steps(int32_t spl) {
 }
 
 // Whether an untuned automatic set is tuned before it runs n_steps at dt.  The
-// probes advance up to 2^22 particles by 10 x 1024 + 2 x 2048 steps, and the
-// choice that they return is at best 5 % faster than the default (64-edge
-// star, 10^7 particles x 10^4 steps: 130.5 against 130.7 ms at dt 10^-2, 94.0
-// against 94.6 at 10^-3).  A graph is therefore tuned once its sets have run,
-// at this dt, 20 times the probes' particle-steps: sooner, the probes could not
-// have paid for themselves (they made a first run of 1000 steps on a new graph
-// take 12 to 190 ms instead of its own 0.08 to 12).  A result that is known,
-// from the graph or the tuning file, is taken at once.
+// probes advance up to 2^22 particles by 10 x 1024 + 2 x 2048 steps, for a
+// choice that is little faster than the default (64-edge star, 10^7 particles
+// x 10^4 steps: 130.5 against 130.7 ms at dt 10^-2, 94.0 against 94.6 at
+// 10^-3).  A graph is therefore tuned by the call that brings the work of its
+// untuned sets at this dt to 20 times the probes' particle-steps, one long
+// call among them: sooner, the probes could not have paid for themselves (they
+// made a first run of 1000 steps on a new graph take 12 to 190 ms instead of
+// its own 0.08 to 12).  A result that is known, from the graph or the tuning
+// file, is taken at once.
 static bool due_tuning(const mg_particles *p, int64_t n_steps, double dt) {
   const double pays =
       20 * (10.0 * 1024 + 2 * 2048) * (double)std::min<int64_t>(p->n, 1 << 22);
@@ -1444,14 +1445,14 @@ static bool due_tuning(const mg_particles *p, int64_t n_steps, double dt) {
     std::lock_guard<std::mutex> lock(p->g->tune_mu);
     for (const auto &c : p->g->tune_cache)
       if (c.first == dt) return true;
+    double total = (double)n_steps * (double)p->n;
     auto &work = p->g->tune_work;
     auto w = std::find_if(work.begin(), work.end(), [&](const auto &x) { return x.first == dt; });
-    if (w != work.end()) {
-      due = due || w->second >= pays;
-      w->second += (double)n_steps * (double)p->n;
-    } else if (work.size() < 1024) {
-      work.emplace_back(dt, (double)n_steps * (double)p->n);
-    }
+    if (w != work.end())
+      total = w->second += total;
+    else if (work.size() < 1024)
+      work.emplace_back(dt, total);
+    due = due || total >= pays;
   }
   // a probe allocates and waits: none inside a capture, which runs the default
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

@@ -160,7 +160,7 @@ p = B.mg_particles_init(G, 100, 2, precision=1)
 %s
 S.stub_capture(1)
 log()
-for dt in (1e-2, 1e-3):
+for dt in (1e-2, 1e-2, 1e-3):
     B.mg_simulate(p, 10, dt, 1)
     l = log()
     assert all(x.startswith("launch") for x in l) and steps(l) and not any("probe" in x for x in l), l
@@ -173,7 +173,7 @@ log()
 B.mg_simulate(q, 10, 1e-2, 1)
 assert steps(log())[0][2]["kernel"] == 0    # (the first of equal probes)
 """
-    stub(code % f"B.mg_simulate(p, {20 * 14336}, 1e-2, 1)")
+    stub(code % f"B.mg_simulate(p, {20 * 14336 - 1}, 1e-2, 1)")
     stub(code % "", MG_TUNE_CACHE="/nonexistent/tune")
 
 
@@ -242,4 +242,31 @@ B.mg_autotune(lanes, 1e-2)                  # a fixed schedule stays what it is
 assert refused(far, new) and refused(far, lanes) and refused(near, lanes) and refused(lanes, near)
 assert refused(far, pools) and refused(near, pools, far)
 B.mg_batch_create([lanes, make(0, schedule=B.MG_SCHED_LANES)])
+""")
+
+
+def test_when_an_automatic_set_is_tuned(stub):
+    """By the call that brings the work of a graph's untuned sets at a dt to 20
+    times the probes' particle-steps: short calls together, or one long one."""
+    stub("""
+def probed(p, k, dt=1e-2):
+    log()
+    B.mg_simulate(p, k, dt, 1)
+    return any("probe" in x for x in log())
+due = 20 * (10 * 1024 + 2 * 2048)
+def new(n=100, G=None, **kw):
+    return B.mg_particles_init(G or B.mg_graph_create(workloads.star_graph(5)), n, 2,
+                               precision=1, **kw)
+p = new()
+assert not probed(p, due - 1) and probed(p, 1) and not probed(p, due)
+assert probed(new(), due)                   # one call
+p = new()                                   # each dt by itself
+assert not probed(p, due - 1, 1e-2) and not probed(p, due - 1, 1e-3)
+assert probed(p, 1, 1e-3) and probed(p, 1, 1e-2)
+G = B.mg_graph_create(workloads.star_graph(5))
+p, q = new(100, G), new(50, G)              # the sets of a graph together
+assert not probed(p, due // 4) and not probed(q, 1) and probed(q, due // 2)
+assert not probed(p, 1)                     # known
+assert not probed(new(schedule=B.MG_SCHED_POOLS_W8), due)
+assert not probed(new(100, B.mg_graph_create(workloads.double_well_star(3))), due)
 """)
