@@ -535,8 +535,9 @@ void mg_batch_destroy(mg_batch *b);
  * mg_simulate call that brings the steps of untuned sets on the graph at its
  * dt to 20 times the probes' particle-steps (at once where a result is known,
  * or MG_TUNE_CACHE names a file); until then (and in a batch built from untuned
- * sets) they use MG_SCHED_POOLS_W8 (a set alone MG_SCHED_LANES where the
- * drift towards an end takes most steps to a vertex on every edge).  Fixed
+ * sets) they use MG_SCHED_POOLS_W8 (a set alone MG_SCHED_LANES where drifts
+ * towards the edges' ends, or edges shorter than a step's noise, are expected
+ * to use up 0.45 of max_splits in each step).  Fixed
  * pool schedules start a partial pass at 16 idle lanes.  FP64 sets have nothing to probe (their set's FP64
  * schedule).  `out` (may be NULL) receives the choice and the probe times.  A
  * probe allocates scratch device memory and synchronises the stream; a

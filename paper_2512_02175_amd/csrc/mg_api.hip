@@ -179,8 +179,14 @@ struct mg_graph {
   mutable std::vector<std::pair<double, mg_tuning>> tune_cache;
   // particle-steps that untuned automatic sets have run, per dt (due_tuning)
   mutable std::vector<std::pair<double, double>> tune_work;
-  // least over the edges of the drift towards an end, there, over sigma
-  double pull = 0.0;
+  // what expected_hits reads: per edge the drift towards an end, there, over
+  // sigma, the noise of unit time over the length, and the weight of the time
+  // spent on it; and the hits without a cap, hit_dt dt + hit_sqrt sqrt(dt)
+  struct HitEdge {
+    double pull, noise, weight;
+  };
+  std::vector<HitEdge> hit_edge;
+  double hit_dt = 0.0, hit_sqrt = 0.0;
   std::vector<double> length;  // host copy for readback conversion
   std::vector<double> span;    // length binned by the uniform histograms
   std::vector<int32_t> vinit_host, vterm_host;  // end vertices of each edge
@@ -202,6 +208,52 @@ struct mg_graph {
   void *dev = nullptr;         // one allocation holding every table
   GraphDev gd{};
 };
+
+// The vertex hits of a step at dt, by the edge's end or both ends within reach.
+static double edge_hits(const mg_graph::HitEdge &h, double dt) {
+  const double r = h.pull * std::sqrt(dt);
+  return std::max(r * (0.9 * r + 0.55), 0.8 * h.noise * std::sqrt(dt));
+}
+
+static void set_hits(mg_graph *g, std::vector<mg_graph::HitEdge> edges) {
+  double w = 0.0, a = 0.0, b = 0.0;
+  for (const mg_graph::HitEdge &h : edges) {
+    w += h.weight;
+    if (std::isinf(w)) return;  // a particle leaves along that edge for good
+    a += h.weight * 0.9 * h.pull * h.pull;
+    b += h.weight * (0.55 * h.pull + 0.8 * h.noise);
+  }
+  g->hit_edge = std::move(edges);
+  g->hit_dt = a / w;
+  g->hit_sqrt = b / w;
+}
+
+// Whether a step at dt is expected to make 0.45 of the M hits that it may, in
+// the mean over the edges, weighted by the time spent on each: with a drift of
+// r times a step's noise towards an end a step makes about 0.9 r^2 + 0.55 r
+// hits, on an edge that is q times shorter than the noise 0.8 q (measured: r
+// 0.5 to 3, q 1 to 16, within 8 %), and a particle stays on an edge for its
+// length or the scale sigma^2 / 2 mu of the drift.  Pools then run little but
+// split passes, one crossing each, while a lane's M crossings at most bound
+// the divergence of the lane schedule.  Lanes against pools, 100 steps of 1e5 /
+// 1e6 particles, M = 8: estimate 0.18 M (drift of one noise on every edge)
+// 335 / 2660 against 285 / 1810 us, 0.30 M (edges a third of the noise) 798 /
+// 3373 against 750 / 2806, 0.36 M (drift 1.5) 720 / 3800 against 725 / 3330,
+// 0.40 M (edges a quarter) 846 / 3601 against 954 / 3616, 0.49 M (the 5-edge
+// star with drifts of 10 to 50 at dt 7.3 10^-3) 912 / 3943 against 1160 / 4124,
+// 0.80 M (edges an eighth) 837 / 3647 against 1431 / 5578; M = 32: 0.20 M 10393
+// against 7821 for 1e6, 1.0 M 15065 against 32473; M = 1: 0.50 M 1.24 and 0.93
+// times as long on pools, 0.80 M 1.30 and 1.05 times.
+static bool crowded(const mg_graph *g, double dt, int32_t max_splits) {
+  const double limit = 0.45 * max_splits;
+  if (g->hit_edge.empty() || g->hit_dt * dt + g->hit_sqrt * std::sqrt(dt) < limit) return false;
+  double hits = 0.0, w = 0.0;
+  for (const mg_graph::HitEdge &h : g->hit_edge) {
+    hits += h.weight * std::min(edge_hits(h, dt), (double)max_splits);
+    w += h.weight;
+  }
+  return hits >= limit * w;
+}
 
 struct mg_particles {
   const mg_graph *g = nullptr;
@@ -225,6 +277,8 @@ struct mg_particles {
   uint64_t step = 0;
   uint64_t obs_start = 0;  // step counter when the streamed histogram started
   int device = -1;         // where the set's memory is
+  double crowded_dt = 0.0;   // the dt that crowded is known for
+  bool crowded = false;      // vertices take up most of a step (fp32_kernel_at)
   bool ran_default = false;  // automatic FP32 set that has run untuned
   void *ev_mem = nullptr;  // event trace: counter, ids and records
 };
@@ -864,7 +918,7 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
     const bool wz = d->vtx_kind && d->vtx_kind[v] == MG_VTX_WENTZELL;
     return (int32_t)((uint32_t)v | (mirror ? kMirrorEnd : 0u) | (wz ? kWentzellEnd : 0u));
   };
-  double pull = std::numeric_limits<double>::infinity();
+  std::vector<mg_graph::HitEdge> hit_edge(E);
   for (int32_t e = 0; e < E; ++e) {
     const double a = d->drift_a ? d->drift_a[e] : 0.0;
     const double c = d->drift_c ? d->drift_c[e] : 0.0;
@@ -876,8 +930,9 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
               tab_k[e] ? tab_k[e] / d->length[e] : 0.0, tab0[e], tab_k[e]};
     // (a particle never measures from the far end of a semi-infinite edge)
     const double aL = std::isinf(d->length[e]) ? 0.0 : std::fma(c, d->length[e], a);
-    // (the least over the edges of a positive drift towards an end, or 0)
-    pull = std::min(pull, std::max({0.0, -a, aL}) / d->sigma[e]);
+    const double pull = std::max({0.0, -a, aL}) / d->sigma[e];
+    hit_edge[e] = {pull, d->sigma[e] / d->length[e],
+                   std::min(d->length[e] / d->sigma[e], 0.5 / pull) / d->sigma[e]};
     const float scale = (float)(std::isinf(d->length[e]) ? d->bin_span[e] : d->length[e]);
     e32[e] = {(float)d->length[e], (float)a, (float)c, (float)d->sigma[e], (float)aL,
               vi, vt, 1e-6f * scale};
@@ -969,7 +1024,7 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
   g->V = V;
   g->E = E;
   g->nnz = nnz;
-  g->pull = pull;
+  set_hits(g, std::move(hit_edge));
   g->length.assign(d->length, d->length + E);
   g->vinit_host.assign(d->edge_init, d->edge_init + E);
   g->vterm_host.assign(d->edge_term, d->edge_term + E);
@@ -1366,17 +1421,15 @@ static bool tuned_at(const mg_particles *p, double dt) {
 }
 
 // The FP32 kernel of a set at dt: the tuned choice or, for an automatic set
-// that is untuned there, the default.  Where the drift takes a
-// particle to an end of its edge by 0.85 of a step's noise or more, on every
-// edge, most steps make several hits and a pool would run little but split
-// passes: one particle per lane.  500 steps of 3e5 / 1e6 / 3e6 particles on
-// the 5-edge star with drifts of 10 to 50 towards its centre, lanes against
-// pools: dt 10^-2 (1.0 of a step's noise, 4.0 hits a step) 7.2 / 19.4 / 51.9
-// against 9.3 / 23.3 / 65.3 ms, 5 10^-3 (0.71) 7.1 / 19.0 / 51.2 against
-// 6.2 / 14.9 / 41.6.
-static int32_t fp32_kernel_at(const mg_particles *p, double dt) {
+// that is untuned there, MG_SCHED_POOLS_W8, but one particle per lane where
+// vertices take up most of a step (looked at once per dt and set).
+static int32_t fp32_kernel_at(mg_particles *p, double dt) {
   if (p->schedule != MG_SCHED_AUTO || p->g->gen || tuned_at(p, dt)) return fp32_kernel(p);
-  return p->g->pull * std::sqrt(dt) >= 0.85 ? 0 : 3;
+  if (p->crowded_dt != dt) {
+    p->crowded_dt = dt;
+    p->crowded = crowded(p->g, dt, p->max_splits);
+  }
+  return p->crowded ? 0 : 3;
 }
 
 // FP64 step kernel of a set: the lane schedule (MG_SCHED_LANES) or wave

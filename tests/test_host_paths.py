@@ -270,3 +270,39 @@ assert not probed(p, 1)                     # known
 assert not probed(new(schedule=B.MG_SCHED_POOLS_W8), due)
 assert not probed(new(100, B.mg_graph_create(workloads.double_well_star(3))), due)
 """)
+
+
+def test_untuned_kernel_by_expected_hits(stub):
+    """Lanes where a step is expected to make 0.45 of its hits, pools below: the
+    sides that were measured faster, for drifts on every edge, drifts on some,
+    short edges, one long edge among short ones, and other split caps."""
+    stub("""
+def kernel(g, dt=1e-2, M=8):
+    G = B.mg_graph_create(g)
+    p = B.mg_particles_init(G, 1000, 1, vertex=0, precision=1, max_splits=M)
+    out = []
+    for d in (dt, 1e-9, dt):
+        log()
+        B.mg_simulate(p, 5, d, 1)
+        out.append(steps(log())[-1][2]["kernel"])
+    assert out[0] == out[2] and out[1] == 3
+    return out[0]
+star = workloads.star_graph
+for E in (3, 64):
+    for r, k in ((0.85, 3), (1.0, 3), (1.5, 3), (2.1, 0), (3.0, 0), (6.0, 0)):
+        assert kernel(star(E, 2.0, -10 * r)) == k, r
+        g = star(E, 0.5, 10 * r)                     # towards the leaves
+        assert kernel(g) == k, r
+    for q, k in ((1, 3), (3, 3), (5, 0), (16, 0)):
+        assert kernel(star(E, 0.1 / q)) == k, q
+for q in (2, 4, 8):
+    assert kernel(star(5, np.where(np.arange(5) == 0, 1.0, 0.1 / q))) == 3
+assert kernel(star(64, 0.1 / 4 * np.random.default_rng(3).uniform(0.3, 1.0, 64))) == 0
+lin = workloads.paper_star5("linear", np.inf)
+assert [kernel(lin, d) for d in (1e-3, 5e-3, 7.3e-3, 2e-2)] == [3, 3, 0, 0]
+assert kernel(star(5, 0.1 / 8), M=32) == 3 and kernel(star(5, 2.0, -60.0), M=32) == 0
+assert kernel(star(5, 0.1), M=1) == 0 and kernel(star(5, 1.0), M=1) == 3
+# a semi-infinite edge without a drift back, and general coefficients
+assert kernel(star(3, [np.inf, 0.001, 0.001], bin_span=[1.0, 0.001, 0.001])) == 3
+assert kernel(workloads.double_well_star(3), 1.0) == 3
+""")
