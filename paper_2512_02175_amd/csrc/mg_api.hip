@@ -1388,7 +1388,7 @@ static mg_status check_steps(const mg_particles *p, int64_t n_steps, double dt) 
 
 // Step kernel (StepArgs::kernel) of an FP32 schedule: 0 one particle per
 // lane, 1 / 2 wave pools of 128 / 256 particles, 3 pools of 128 with the
-// later refill (set_schedule); and back.
+// later refill (refill_lanes); and back.
 static int32_t kernel_of(int32_t schedule) {
   switch (schedule) {
     case MG_SCHED_LANES: return 0;
@@ -1449,22 +1449,12 @@ static int32_t pool_idle_at(const mg_particles *p, double dt) {
   return tuned_at(p, dt) ? p->tuned_idle : 16;
 }
 
-// Schedule fields of a launch: the kernel, the idle lanes that start a
-// partial split pass, and the lanes without a particle that end a window
-// while there are others for them.  A refill costs about 70 VALU
-// instructions whatever the number of lanes it serves, a group of steps 97:
-// at 1 / 8 / 16 / 24 lanes 2000 steps of 1e7 FP32 particles on the 64-edge
-// star take 32.4 / 32.3 / 31.2 / 31.3 ms at 7.1 % hits a step, 23.1 / 21.2 /
-// 20.7 / 21.9 at 2.1 %, and 1000 steps of 3e7 on the vascular network
-// (0.35 %) 19.3 / 18.6 / 19.2 / 20.4.  Hence 16 lanes where the tables are
-// staged in LDS, and 8 where an FP32 set reads them from global memory: a
-// refill there waits for loads that the other lanes' steps hide, and pays
-// earlier.  (FP64, 16 against 8: 55.2 against 56.2 ms for 2000 steps of 1e7
-// on the 64-edge star.)
-static void set_schedule(StepArgs &a, int32_t kernel, int32_t idle, bool fp64, bool staged) {
+// Schedule fields of a launch: the kernel and the idle lanes that start a
+// partial split pass (the lanes that end a window follow from the launch's LDS
+// plan: refill_lanes).
+static void set_schedule(StepArgs &a, int32_t kernel, int32_t idle) {
   a.kernel = kernel;
   a.idle = idle;
-  a.refill = kernel == 3 && (fp64 || staged) ? 16 : 8;
   a.pool_cap = (uint32_t)pool_per_wave(kernel);
 }
 
@@ -1535,8 +1525,7 @@ mg_status mg_simulate(mg_particles *p, int64_t n_steps, double dt, uint64_t seed
   a.key1 = (uint32_t)(seed >> 32);
   a.dt = dt;
   set_schedule(a, p->prec == MG_FP32 ? fp32_kernel_at(p, dt) : step_kernel(p),
-               pool_idle_at(p, dt), p->prec == MG_FP64,
-               p->g->gd.stage_bytes32 > 0);
+               pool_idle_at(p, dt));
   p->ran_default = p->ran_default || (n_steps > 0 && p->prec == MG_FP32 && !p->g->gen &&
                                       p->schedule == MG_SCHED_AUTO && !tuned_at(p, dt));
   // a set without a fixed launch length takes the tuned one
@@ -2429,6 +2418,7 @@ static hipError_t add_chunk(mg_batch *b, const StepArgs &a0, std::vector<hipGrap
     args[gi].batch_claim = b->d_claim + gi;
     launch[gi] = batch_launch(grp.count, grp.max_nnz, grp.max_stage, args[gi],
                               p0->prec == MG_FP64, p0->trace, b->key_obs, b->gen_level);
+    args[gi].refill = launch[gi].refill;
     persistent = persistent || launch[gi].persistent;
   }
   hipError_t he = hipSuccess;
@@ -2501,7 +2491,7 @@ mg_status mg_batch_simulate(mg_batch *b, int64_t n_steps, double dt, uint64_t se
   a.key0 = (uint32_t)seed;
   a.key1 = (uint32_t)(seed >> 32);
   a.dt = dt;
-  set_schedule(a, b->kernel, pool_idle(b->schedule_of), p0->prec == MG_FP64, true);
+  set_schedule(a, b->kernel, pool_idle(b->schedule_of));
   const uint32_t chunk = chunk_steps(p0->steps_per_launch);
   const int32_t n_sets = (int32_t)b->sets.size();
   // the previous call's upload must have left the pinned buffer
@@ -2638,7 +2628,7 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
     if (he == hipSuccess)
       he = hipMemcpyAsync(sd.y32, p->sd.y32, (size_t)n * 8, hipMemcpyDeviceToDevice, p->stream);
     if (he == hipSuccess) he = hipEventRecord(e0, p->stream);
-    set_schedule(a, cand_kernel[i], cand_idle[i], false, p->g->gd.stage_bytes32 > 0);
+    set_schedule(a, cand_kernel[i], cand_idle[i]);
     if (he == hipSuccess) he = launch_step(p->g->gd, sd, a, false, false, p->stream);
     if (he == hipSuccess) he = hipEventRecord(e1, p->stream);
     if (he == hipSuccess) he = hipEventSynchronize(e1);
@@ -2654,8 +2644,7 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
   // steps per launch for the chosen schedule: 2 x steps as one launch
   // against two launches of `steps` (each launch ends with a tail of partly
   // filled waves; the launch count is the only difference)
-  set_schedule(a, cand_kernel[best_i], cand_idle[best_i], false,
-               p->g->gd.stage_bytes32 > 0);
+  set_schedule(a, cand_kernel[best_i], cand_idle[best_i]);
   for (int i = 0; i < 2 && he == hipSuccess; ++i) {
     he = hipMemcpyAsync(sd.ef, p->sd.ef, (size_t)n * 4, hipMemcpyDeviceToDevice, p->stream);
     if (he == hipSuccess)

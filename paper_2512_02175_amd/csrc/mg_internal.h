@@ -278,6 +278,7 @@ struct KernelLaunch {
   dim3 grid, block;
   size_t shm;
   bool persistent;  // a resident grid over the items: k_batch_reset goes first
+  int32_t refill;   // StepArgs::refill of its plan (wave pools)
 };
 // k_batch_reset(const SetDev *sets, int32_t n_sets, uint32_t *claim, int32_t
 // n_claims): clears the sets' particle counters and the groups' item counters

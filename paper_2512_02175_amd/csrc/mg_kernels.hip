@@ -2957,6 +2957,20 @@ LdsPlan plan_lds(bool fp64, int32_t nnz, int32_t stage, size_t pools, const SetD
   return p;
 }
 
+// Lanes without a particle that end a wave pool's window of groups while there
+// are others for them.  A refill costs about 70 VALU instructions whatever the
+// number of lanes it serves, a group of steps 97: at 1 / 8 / 16 / 24 lanes 2000
+// steps of 1e7 FP32 particles on the 64-edge star take 32.4 / 32.3 / 31.2 /
+// 31.3 ms at 7.1 % hits a step, 23.1 / 21.2 / 20.7 / 21.9 at 2.1 %, and 1000
+// steps of 3e7 on the vascular network (0.35 %) 19.3 / 18.6 / 19.2 / 20.4.
+// Hence 16 lanes where the launch stages its tables in LDS, and 8 where an
+// FP32 set reads them from global memory: a refill there waits for loads that
+// the other lanes' steps hide, and pays earlier.  (FP64, 16 against 8: 55.2
+// against 56.2 ms for 2000 steps of 1e7 on the 64-edge star.)
+int32_t refill_lanes(int32_t kernel, bool fp64, bool staged) {
+  return kernel == 3 && (fp64 || staged) ? 16 : 8;
+}
+
 // Compute units of the current device, looked up once.
 uint32_t device_cus() {
   static std::mutex mu;
@@ -3028,6 +3042,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                                   pool_lds_bytes<kPoolSmall, true, TRACE>(obs) * kWavesPerBlock, &s,
                                   g.E);
       a.obs_lds = lp.obs_lds;
+      a.refill = refill_lanes(a.kernel, true, lp.staged);
       const uint32_t need = set_pool(a, s.n, kPoolSmall, true);
       hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(64), 0, st, s.work);
       with_gen(g.gen, [&](auto Gn) {
@@ -3052,6 +3067,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                                   pool_lds_bytes<PW, false, TRACE>(obs) * kWavesPerBlock,
                                   &s, g.E);
       a.obs_lds = lp.obs_lds;
+      a.refill = refill_lanes(a.kernel, false, lp.staged);
       const uint32_t need = set_pool(a, s.n, PW, false);
       hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(64), 0, st, s.work);
       if (!TRACE && !obs && a.probe) {
@@ -3132,6 +3148,7 @@ KernelLaunch batch_launch_t(int32_t n_items, int32_t max_nnz, int32_t max_stage,
         pool_lds_bytes<FP64 ? kPoolSmall : PW, FP64, TRACE>(obs) * kWavesPerBlock;
     const LdsPlan lp = plan_lds(FP64, max_nnz, max_stage, pools ? pool_bytes : 0, nullptr, 0);
     k.shm = lp.shm;
+    k.refill = refill_lanes(a.kernel, FP64, lp.staged);
     with_gen(gen, [&](auto Gn) {
       constexpr int gn = decltype(Gn)::value;
       with_flags([&](auto L, auto T, auto O) {

@@ -306,3 +306,32 @@ assert kernel(star(5, 0.1), M=1) == 0 and kernel(star(5, 1.0), M=1) == 3
 assert kernel(star(3, [np.inf, 0.001, 0.001], bin_span=[1.0, 0.001, 0.001])) == 3
 assert kernel(workloads.double_well_star(3), 1.0) == 3
 """)
+
+
+def test_refill_follows_the_launch_plan(stub):
+    """Lanes that end a window: 16 of MG_SCHED_POOLS_W8 where the launch stages
+    the graph's tables in LDS, else 8 in FP32; group by group in a batch."""
+    stub("""
+small, large = (B.mg_graph_create(workloads.star_graph(E)) for E in (20, 2000))
+def staged(kernel):                         # <trace, exits in LDS, tables in LDS, ...>
+    return re.search(r"(?:k_pool|k_step)\\w*?I((?:Lb[01]E)+)", kernel)[1][10] == "1"
+n = 1_000_000
+for prec, sched, G, want in ((1, 4, small, 16), (1, 4, large, 8), (1, 2, small, 8),
+                             (1, 2, large, 8), (0, 4, small, 16), (0, 4, large, 16)):
+    p = B.mg_particles_init(G, n, 2, precision=prec, schedule=sched)
+    log()
+    B.mg_simulate(p, 5, 1e-2, 1)
+    (k, _, a), = steps(log())
+    assert a["refill"] == want and staged(k) == (G is small), (k, a)
+for prec in (1, 0):
+    sets = [B.mg_particles_init(G, n, 2, precision=prec, schedule=4, graph_tag=i)
+            for i, G in enumerate((small, large))]
+    S.stub_blocks_per_cu(8)
+    b = B.mg_batch_create(sets)
+    log()
+    B.mg_batch_simulate(b, 5, 1e-2, 1)
+    l = steps(log())
+    assert len({staged(k) for k, _, _ in l}) == 2, l
+    for k, _, a in l:
+        assert a["refill"] == (16 if prec == 0 or staged(k) else 8), (k, a)
+""")
