@@ -511,8 +511,9 @@ void mg_batch_destroy(mg_batch *b);
  * Autotuning of an FP32 set's kernel schedule.  The candidates (one
  * particle per lane; wave pools of 128 particles (2 per lane) that start a
  * partial split pass at 4, 8, 16 or 32 idle lanes; pools of 256 (4 per
- * lane) at 8 or 16; MG_SCHED_POOLS_W8 pools of 128 at 8, 16 or 32) all
- * give identical results, so tuning changes only
+ * lane) at 8 or 16; MG_SCHED_POOLS_W8 pools of 128 at 8, 16 or 32, which
+ * share the times of the pools of 128 where the graph's tables are not staged
+ * and their launches are the same) all give identical results, so tuning changes only
  * speed.  Each candidate advances a scratch copy of the set's first
  * min(n, 2^22) particles by probe_steps steps (<= 0: 1024) of size dt with
  * Philox key seed, timed with HIP events on the set's stream; the set

@@ -2624,6 +2624,18 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
   float best = 0.0f;
   int best_i = -1;
   for (int i = 0; i < kCand && he == hipSuccess; ++i) {
+    // a candidate whose launch is an earlier one's (MG_SCHED_POOLS_W8 on a graph
+    // whose tables are not staged) has its time
+    int same = -1;
+    for (int j = 0; j < i && same < 0; ++j)
+      if (cand_kernel[j] && cand_idle[j] == cand_idle[i] &&
+          pool_per_wave(cand_kernel[j]) == pool_per_wave(cand_kernel[i]) &&
+          pool_refill(p->g->gd, cand_kernel[j]) == pool_refill(p->g->gd, cand_kernel[i]))
+        same = j;
+    if (same >= 0) {
+      res.probe_ms[i] = res.probe_ms[same];
+      continue;
+    }
     he = hipMemcpyAsync(sd.ef, p->sd.ef, (size_t)n * 4, hipMemcpyDeviceToDevice, p->stream);
     if (he == hipSuccess)
       he = hipMemcpyAsync(sd.y32, p->sd.y32, (size_t)n * 8, hipMemcpyDeviceToDevice, p->stream);
@@ -2644,7 +2656,7 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
   // steps per launch for the chosen schedule: 2 x steps as one launch
   // against two launches of `steps` (each launch ends with a tail of partly
   // filled waves; the launch count is the only difference)
-  set_schedule(a, cand_kernel[best_i], cand_idle[best_i]);
+  if (he == hipSuccess) set_schedule(a, cand_kernel[best_i], cand_idle[best_i]);
   for (int i = 0; i < 2 && he == hipSuccess; ++i) {
     he = hipMemcpyAsync(sd.ef, p->sd.ef, (size_t)n * 4, hipMemcpyDeviceToDevice, p->stream);
     if (he == hipSuccess)

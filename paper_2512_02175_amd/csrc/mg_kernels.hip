@@ -3197,6 +3197,15 @@ hipError_t launch_step(const GraphDev &g, const SetDev &s, const StepArgs &a,
                : launch_step_t<false, false>(g, s, a, st);
 }
 
+int32_t pool_refill(const GraphDev &g, int32_t kernel) {
+  bool staged = false;
+  with_pool(kernel, [&](auto PWc) {
+    const size_t pools = pool_lds_bytes<decltype(PWc)::value, false, false>(false);
+    staged = plan_lds(false, g.nnz, g.stage_bytes32, pools * kWavesPerBlock, nullptr, 0).staged;
+  });
+  return refill_lanes(kernel, false, staged);
+}
+
 const void *batch_reset_kernel() { return (const void *)k_batch_reset; }
 
 int32_t batch_blocks_per_cu(int32_t max_nnz, int32_t max_stage, const StepArgs &a, bool fp64,

@@ -335,3 +335,29 @@ for prec in (1, 0):
     for k, _, a in l:
         assert a["refill"] == (16 if prec == 0 or staged(k) else 8), (k, a)
 """)
+
+
+def test_equal_candidates_are_probed_once(stub):
+    """On a graph whose tables are not staged MG_SCHED_POOLS_W8 launches what
+    MG_SCHED_POOLS launches: seven probes, and the times of the other three are
+    those of their equals."""
+    stub("""
+for E, launches in ((20, 10), (2000, 7)):
+    p = B.mg_particles_init(B.mg_graph_create(workloads.star_graph(E)), 1_000_000, 2, precision=1)
+    log()
+    S.stub_fast(3)                          # pools of 128 at 16 idle lanes
+    t = B.mg_autotune(p, 1e-2)
+    l = [(re.search(r"I.*E", k)[0], a["idle"], a["refill"], a["nsteps"]) for k, _, a in steps(log())
+         if a["kernel"]]
+    assert len([x for x in l if x[3] == 1024]) - 2 == launches - 1, l   # (2: the launch length)
+    assert t["schedule"] == B.MG_SCHED_POOLS and t["idle_trigger"] == 16 and t["n_probes"] == 10
+    assert t["probe_ms"][3] == 0.5 and (t["probe_ms"][8] == 0.5) == (launches == 7)
+    fail("hipMemcpyAsync")                  # a probe that cannot run
+    p = B.mg_particles_init(B.mg_graph_create(workloads.star_graph(E)), 100, 2, precision=1)
+    try:
+        B.mg_autotune(p, 1e-2)
+        assert False
+    except B.MgError as e:
+        assert e.status == B.MG_EDEVICE
+    fail("")
+""")
