@@ -249,7 +249,8 @@ constexpr int kLdsStageMax = 24576; // graph tables staged in LDS up to this siz
 constexpr int kLdsHistMax = 32768;  // histogram bins privatised in LDS (128 KiB)
 constexpr int kLdsHistEdges = 512;  // and edges whose binning it keeps beside them
 constexpr int kLdsObsMax = 4096;    // streamed-histogram bins privatised in LDS
-constexpr int kLdsBlockMax = 65536; // LDS bytes a step block may take
+constexpr int kLdsBlockMax = 65536; // LDS bytes a step block may take for counters,
+                                    // staged tables and particles
 
 // Injection sources of init mode 3: vertex ids and cumulative rate
 // thresholds (device arrays of n entries).

@@ -2924,7 +2924,15 @@ void with_pool(int32_t kernel, F &&f) {
 // kernels' offsets: [FP64: Box-Muller tables][exit counters][staged
 // tables][pools][snapshot bins].
 // Within kLdsBlockMax bytes, exit counters come first (they take an atomic
-// per hit-step), staged tables next, snapshot bins last.
+// per hit-step), staged tables next, snapshot bins last.  What a block keeps
+// beside those (the Box-Muller tables, the snapshot counts of its home slots)
+// comes on top: counters that leave LDS cost an atomic on the set's own at
+// every hit, one at a time where few slots take the exits.  50 steps of 3e5
+// particles that leave a star's centre by 4 of its edges, exits counted in LDS
+// against beyond: FP64 pools with 9600 slots 0.53 against 3.9 ms, FP64 lanes
+// with 15200 0.45 against 4.1, FP32 pools with streaming and 10800 1.4 against
+// 4.1 (all slots taking their share: 0.43 against 0.24, 0.34 against 0.23, 0.5
+// against 0.25).
 struct LdsPlan {
   bool lds_exit;
   bool staged;
@@ -2932,8 +2940,11 @@ struct LdsPlan {
   size_t shm;
 };
 
-LdsPlan plan_lds(bool fp64, int32_t nnz, int32_t stage, size_t pools, const SetDev *obs_set,
-                 int32_t n_edges) {
+// pools: bytes of the block's pools; beside: of them and of the tables, those
+// on top of kLdsBlockMax (beside_bytes).
+LdsPlan plan_lds(bool fp64, int32_t nnz, int32_t stage, size_t pools, size_t beside,
+                 const SetDev *obs_set, int32_t n_edges) {
+  const size_t most = (size_t)kLdsBlockMax + beside;
   LdsPlan p{};
   p.lds_exit = nnz <= kLdsExitMax;
   p.staged = stage > 0;
@@ -2943,18 +2954,29 @@ LdsPlan plan_lds(bool fp64, int32_t nnz, int32_t stage, size_t pools, const SetD
                      (size_t)((ex + (p.staged ? stage : 0) + 15) & ~15) + pools;
     return (b + 15) & ~(size_t)15;
   };
-  if (size() > (size_t)kLdsBlockMax) p.staged = false;
-  if (size() > (size_t)kLdsBlockMax) p.lds_exit = false;
+  if (size() > most) p.staged = false;
+  if (size() > most) p.lds_exit = false;
   const size_t base = size();
   p.shm = base;
   if (obs_set && obs_set->obs) {
     const int64_t nbins = (int64_t)n_edges * obs_set->obs_nb;
-    if (nbins <= kLdsObsMax && base + (size_t)nbins * 4 <= (size_t)kLdsBlockMax) {
+    if (nbins <= kLdsObsMax && base + (size_t)nbins * 4 <= most) {
       p.obs_lds = (int32_t)nbins;
       p.shm = base + (size_t)nbins * 4;
     }
   }
   return p;
+}
+
+// The bytes that a block's LDS holds on top of kLdsBlockMax: the FP64 tables
+// and, in pools of PW (0: the lane schedule), the snapshot counts.
+template <int PW, bool FP64, bool TRACE>
+size_t beside_bytes(bool obs) {
+  size_t b = FP64 ? sizeof(BmLds) : 0;
+  if constexpr (PW > 0)
+    b += (pool_lds_bytes<PW, FP64, TRACE>(obs) - pool_lds_bytes<PW, FP64, TRACE>(false)) *
+         kWavesPerBlock;
+  return b;
 }
 
 // Lanes without a particle that end a wave pool's window of groups while there
@@ -3039,8 +3061,8 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
     if (a.kernel == 3) {
       // FP64 wave pools (128 per wave) on a resident grid
       const LdsPlan lp = plan_lds(true, g.nnz, g.stage_bytes64,
-                                  pool_lds_bytes<kPoolSmall, true, TRACE>(obs) * kWavesPerBlock, &s,
-                                  g.E);
+                                  pool_lds_bytes<kPoolSmall, true, TRACE>(obs) * kWavesPerBlock,
+                                  beside_bytes<kPoolSmall, true, TRACE>(obs), &s, g.E);
       a.obs_lds = lp.obs_lds;
       a.refill = refill_lanes(a.kernel, true, lp.staged);
       const uint32_t need = set_pool(a, s.n, kPoolSmall, true);
@@ -3065,7 +3087,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
       const int32_t stage = g.stage_bytes32;
       const LdsPlan lp = plan_lds(false, g.nnz, stage,
                                   pool_lds_bytes<PW, false, TRACE>(obs) * kWavesPerBlock,
-                                  &s, g.E);
+                                  beside_bytes<PW, false, TRACE>(obs), &s, g.E);
       a.obs_lds = lp.obs_lds;
       a.refill = refill_lanes(a.kernel, false, lp.staged);
       const uint32_t need = set_pool(a, s.n, PW, false);
@@ -3110,7 +3132,8 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
     return hipGetLastError();
   }
   const int32_t stage = FP64 ? g.stage_bytes64 : g.stage_bytes32;
-  const LdsPlan lp = plan_lds(FP64, g.nnz, stage, 0, &s, g.E);
+  const LdsPlan lp =
+      plan_lds(FP64, g.nnz, stage, 0, beside_bytes<0, FP64, TRACE>(obs), &s, g.E);
   a.obs_lds = lp.obs_lds;
   const uint32_t blocks = (s.n + kBlock - 1) / kBlock;
   if (!FP64 && !TRACE && !obs && a.probe) {
@@ -3144,9 +3167,11 @@ KernelLaunch batch_launch_t(int32_t n_items, int32_t max_nnz, int32_t max_stage,
   const bool pools = FP64 ? a.kernel == 3 : (a.kernel >= 1 && (!gen || a.kernel == 3));
   with_pool(a.kernel, [&](auto PWc) {
     constexpr int PW = decltype(PWc)::value;
-    const size_t pool_bytes =
-        pool_lds_bytes<FP64 ? kPoolSmall : PW, FP64, TRACE>(obs) * kWavesPerBlock;
-    const LdsPlan lp = plan_lds(FP64, max_nnz, max_stage, pools ? pool_bytes : 0, nullptr, 0);
+    constexpr int P = FP64 ? kPoolSmall : PW;
+    const size_t pool_bytes = pool_lds_bytes<P, FP64, TRACE>(obs) * kWavesPerBlock;
+    const LdsPlan lp = plan_lds(FP64, max_nnz, max_stage, pools ? pool_bytes : 0,
+                                pools ? beside_bytes<P, FP64, TRACE>(obs)
+                                      : beside_bytes<0, FP64, TRACE>(obs), nullptr, 0);
     k.shm = lp.shm;
     k.refill = refill_lanes(a.kernel, FP64, lp.staged);
     with_gen(gen, [&](auto Gn) {
@@ -3201,7 +3226,8 @@ int32_t pool_refill(const GraphDev &g, int32_t kernel) {
   bool staged = false;
   with_pool(kernel, [&](auto PWc) {
     const size_t pools = pool_lds_bytes<decltype(PWc)::value, false, false>(false);
-    staged = plan_lds(false, g.nnz, g.stage_bytes32, pools * kWavesPerBlock, nullptr, 0).staged;
+    staged =
+        plan_lds(false, g.nnz, g.stage_bytes32, pools * kWavesPerBlock, 0, nullptr, 0).staged;
   });
   return refill_lanes(kernel, false, staged);
 }

@@ -361,3 +361,35 @@ for E, launches in ((20, 10), (2000, 7)):
         assert e.status == B.MG_EDEVICE
     fail("")
 """)
+
+
+def test_exit_counters_stay_in_lds(stub):
+    """The most exit slots counted in LDS are those that fit in 64 KiB beside the
+    four pools of a block (44 bytes a particle in FP64, 40 in FP32), whatever the
+    FP64 tables and the snapshot counts of a streaming set need beside them; the
+    lane schedule counts 16384."""
+    stub("""
+def exits_in_lds(kernel):   # <trace, exits, ...>; the lane kernels <fp64, trace, exits, ...>
+    f = re.findall(r"Lb([01])E", re.search(r"I((?:Lb[01]E)+)", kernel)[1])
+    return f[2 if "k_step" in kernel or "7k_batch" in kernel else 1] == "1"
+def counted(edges, prec, sched, obs, batch):
+    p = B.mg_particles_init(B.mg_graph_create(workloads.star_graph(edges)), 1000, 2,
+                            precision=prec, schedule=sched)
+    if obs:
+        B.mg_observe_histogram(p, 4, 5)
+    log()
+    if batch:
+        B.mg_batch_simulate(B.mg_batch_create([p]), 5, 1e-2, 1)
+    else:
+        B.mg_simulate(p, 5, 1e-2, 1)
+    (k, _, _), = steps(log())
+    return exits_in_lds(k)
+KB64 = 65536
+for prec, sched, most in ((0, 1, 16384), (1, 1, 16384), (0, 4, (KB64 - 4 * 128 * 44) // 4),
+                          (1, 4, (KB64 - 4 * 128 * 40) // 4), (1, 2, (KB64 - 4 * 128 * 40) // 4),
+                          (1, 3, (KB64 - 4 * 256 * 40) // 4)):
+    for obs in (False, True):
+        for batch in (False, True):
+            at = [counted(most // 2 + d, prec, sched, obs, batch) for d in (0, 1)]
+            assert at == [True, False], (prec, sched, obs, batch, at)
+""")
