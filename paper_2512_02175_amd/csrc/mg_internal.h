@@ -216,7 +216,8 @@ struct StepArgs {
 };
 
 // Largest particle set.  A persistent pool launch hands out particle ids
-// from a 32-bit counter; every wave overshoots it by at most one
+// from a 32-bit counter (on top of the waves' first reservations, where those
+// are their places in the grid); every wave overshoots n by at most one
 // reservation, a persistent grid has at most kMaxPersistBlocks blocks of
 // four waves, and the host caps a reservation at (2^32 - 1 - n) / 8192 ids
 // (at least 112 at this n), so the counter cannot wrap and ids stay below n.

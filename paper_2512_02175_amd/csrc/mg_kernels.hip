@@ -2082,9 +2082,15 @@ __device__ __forceinline__ void drain_lds(uint32_t *lds, uint64_t *glob, int32_t
 // most one reservation per set and launch (a batched launch lets a block
 // join a set only while its counter is below n, so this holds there too);
 // the host bounds the reservation so that the counter cannot wrap.
+// In a launch that is the set's own (not a batch) a wave's first reservation is
+// its place in the grid, and the counter starts behind those of all waves
+// (own_claims): a set spread over many small pools (set_pool) otherwise updated
+// the one address twice per wave, and a short launch waited for that (1 / 8 / 31
+// steps of 3e4 FP32 particles on the 64-edge star 29 / 40 / 67 -> 14 / 26 / 52
+// us; with full pools 18 / 32 / 61).
 // Q: the particle type (Particle32 or Particle64, each with its pool type
 // in LDS).
-template <bool TRACE, bool LDS, bool OBS, int PW, int GEN, class Ln, class Pool>
+template <bool BATCH, bool TRACE, bool LDS, bool OBS, int PW, int GEN, class Ln, class Pool>
 __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
                          const StepArgs &A, Pool &P, uint32_t *s_exit, Tally &t,
                          unsigned long long *s_tot, int32_t nnz, const ObsSink &sink) {
@@ -2113,6 +2119,13 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
   bool exhausted = false;   // the reservation is used up and the set has run out
   bool last_chunk = false;  // the set ran out with the current reservation
   uint32_t res_next = 0, res_end = 0;  // the wave's reserved ids [res_next, res_end)
+  if constexpr (!BATCH) {
+    const uint32_t wave =
+        blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    res_next = min(wave * A.claim_chunk, lim);
+    res_end = min(res_next + A.claim_chunk, lim);
+    last_chunk = gridDim.x * kWavesPerBlock * A.claim_chunk >= lim;
+  }
   uint32_t iter = 0, iter_lds = 0;
   wave_lds_fence();
 
@@ -2419,7 +2432,9 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
 // set's counter has run out and the block's pools are empty, and adds the
 // block's counts to the set's counters.
 
-template <bool FP64, bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN>
+// BATCH: one of the blocks that work on the set at a time; else the whole grid
+// does.
+template <bool BATCH, bool FP64, bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN>
 __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
                                            const StepArgs &A, unsigned long long *s_tot,
                                            char *smem) {
@@ -2448,8 +2463,8 @@ __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
   __syncthreads();
   Tally t{0, 0, 0, 0};
   const uint32_t wave = threadIdx.x >> 6;
-  run_pool<TRACE, LDS, OBS, PW, GEN, Ln>(view, G.E, S, A, pools[wave], s_exit, t, s_tot,
-                                         G.nnz, o);
+  run_pool<BATCH, TRACE, LDS, OBS, PW, GEN, Ln>(view, G.E, S, A, pools[wave], s_exit, t, s_tot,
+                                                G.nnz, o);
   flush(S, t, s_tot, s_exit, G.nnz, LDS);
   if (OBS && A.obs_lds) flush_obs(S, o.lds, A.obs_lds);
 }
@@ -2465,7 +2480,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL_
 void k_pool32(GraphDev G, SetDev S, StepArgs A) {
   extern __shared__ uint4 smem4[];
   __shared__ unsigned long long s_tot[4];
-  pool_block<false, TRACE, LDS, STAGED, OBS, PW, GEN>(G, S, A, s_tot, (char *)smem4);
+  pool_block<false, false, TRACE, LDS, STAGED, OBS, PW, GEN>(G, S, A, s_tot, (char *)smem4);
 }
 
 // FP64 wave pools: the same schedule over FP64 particles (pools of 128).  Two
@@ -2480,7 +2495,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEN == k
 void k_pool64(GraphDev G, SetDev S, StepArgs A) {
   extern __shared__ uint4 smem4[];
   __shared__ unsigned long long s_tot[4];
-  pool_block<true, TRACE, LDS, STAGED, OBS, kPoolSmall, GEN>(G, S, A, s_tot, (char *)smem4);
+  pool_block<false, true, TRACE, LDS, STAGED, OBS, kPoolSmall, GEN>(G, S, A, s_tot, (char *)smem4);
 }
 
 // Batched form of the wave pools: a resident grid whose blocks take work
@@ -2518,7 +2533,7 @@ void k_pool32_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem 
     SetDev S = sets[set];
     S.n0 += A.n0_offset;  // steps already taken by earlier launches of this call
     const GraphDev G = graphs[set];
-    pool_block<false, TRACE, LDS, STAGED, OBS, PW, GEN>(G, S, A, s_tot, (char *)smem4);
+    pool_block<true, false, TRACE, LDS, STAGED, OBS, PW, GEN>(G, S, A, s_tot, (char *)smem4);
   }
 }
 
@@ -2550,7 +2565,7 @@ void k_pool64_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem 
     SetDev S = sets[set];
     S.n0 += A.n0_offset;
     const GraphDev G = graphs[set];
-    pool_block<true, TRACE, LDS, STAGED, OBS, kPoolSmall, GEN>(G, S, A, s_tot,
+    pool_block<true, true, TRACE, LDS, STAGED, OBS, kPoolSmall, GEN>(G, S, A, s_tot,
                                                                   (char *)smem4);
   }
 }
@@ -2572,7 +2587,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL_
 void k_pool32_probe(GraphDev G, SetDev S, StepArgs A) {
   extern __shared__ uint4 smem4[];
   __shared__ unsigned long long s_tot[4];
-  pool_block<false, false, LDS, STAGED, false, PW, 0>(G, S, A, s_tot, (char *)smem4);
+  pool_block<false, false, false, LDS, STAGED, false, PW, 0>(G, S, A, s_tot, (char *)smem4);
 }
 
 template <bool LDS, bool STAGED>
@@ -2583,10 +2598,10 @@ __global__ __launch_bounds__(kBlock) void k_step32_probe(GraphDev G, SetDev S, S
                                                s_tot, (char *)smem4);
 }
 
-// Clears the particle counter of a persistent pool launch (a kernel rather
-// than a memset, so that launch chains can be captured in HIP graphs).
-__global__ void k_clear_word(uint32_t *w) {
-  if (threadIdx.x == 0) *w = 0u;
+// Sets the particle counter of a persistent pool launch (a kernel rather than
+// a memset, so that launch chains can be captured in HIP graphs).
+__global__ void k_set_word(uint32_t *w, uint32_t v) {
+  if (threadIdx.x == 0) *w = v;
 }
 
 // Blocks of a persistent launch: as many as stay resident at once (CUs x
@@ -3052,6 +3067,16 @@ uint32_t set_pool(StepArgs &a, uint32_t n, int32_t pool, bool fp64) {
   return (n + per_block - 1) / per_block;
 }
 
+// The blocks of a set's own pool launch, whose waves take their places in the
+// grid as first reservations; its counter is set behind them.
+uint32_t own_claims(const void *func, size_t shm, uint32_t need, const SetDev &s,
+                    const StepArgs &a, hipStream_t st) {
+  const uint32_t blocks = resident_blocks(func, shm, need);
+  hipLaunchKernelGGL(k_set_word, dim3(1), dim3(64), 0, st, s.work,
+                     blocks * kWavesPerBlock * a.claim_chunk);
+  return blocks;
+}
+
 template <bool FP64, bool TRACE>
 hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                          hipStream_t st) {
@@ -3066,15 +3091,15 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
       a.obs_lds = lp.obs_lds;
       a.refill = refill_lanes(a.kernel, true, lp.staged);
       const uint32_t need = set_pool(a, s.n, kPoolSmall, true);
-      hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(64), 0, st, s.work);
       with_gen(g.gen, [&](auto Gn) {
         constexpr int gn = decltype(Gn)::value;
         with_flags([&](auto L, auto T, auto O) {
           constexpr bool l = decltype(L)::value, t = decltype(T)::value,
                          o = decltype(O)::value;
           const void *f = (const void *)k_pool64<TRACE, l, t, o, gn>;
+          const uint32_t blocks = own_claims(f, lp.shm, need, s, a, st);
           hipLaunchKernelGGL((k_pool64<TRACE, l, t, o, gn>),
-                             dim3(resident_blocks(f, lp.shm, need)), dim3(kBlock), lp.shm, st,
+                             dim3(blocks), dim3(kBlock), lp.shm, st,
                              g, s, a);
         }, lp.lds_exit, lp.staged, obs);
       });
@@ -3091,13 +3116,13 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
       a.obs_lds = lp.obs_lds;
       a.refill = refill_lanes(a.kernel, false, lp.staged);
       const uint32_t need = set_pool(a, s.n, PW, false);
-      hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(64), 0, st, s.work);
       if (!TRACE && !obs && a.probe) {
         with_flags([&](auto L, auto T) {
           const void *f =
               (const void *)k_pool32_probe<decltype(L)::value, decltype(T)::value, PW>;
+          const uint32_t blocks = own_claims(f, lp.shm, need, s, a, st);
           hipLaunchKernelGGL((k_pool32_probe<decltype(L)::value, decltype(T)::value, PW>),
-                             dim3(resident_blocks(f, lp.shm, need)), dim3(kBlock), lp.shm, st,
+                             dim3(blocks), dim3(kBlock), lp.shm, st,
                              g, s, a);
         }, lp.lds_exit, lp.staged);
         return;
@@ -3111,9 +3136,10 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                 const void *f =
                     (const void *)k_pool32<TRACE, decltype(L)::value, decltype(T)::value,
                                            decltype(O)::value, PW, gn>;
+                const uint32_t blocks = own_claims(f, lp.shm, need, s, a, st);
                 hipLaunchKernelGGL((k_pool32<TRACE, decltype(L)::value, decltype(T)::value,
                                              decltype(O)::value, PW, gn>),
-                                   dim3(resident_blocks(f, lp.shm, need)), dim3(kBlock),
+                                   dim3(blocks), dim3(kBlock),
                                    lp.shm, st, g, s, a);
               }, lp.lds_exit, lp.staged, obs);
           });
@@ -3123,9 +3149,10 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
       with_flags([&](auto L, auto T, auto O) {
         const void *f = (const void *)k_pool32<TRACE, decltype(L)::value, decltype(T)::value,
                                                decltype(O)::value, PW>;
+        const uint32_t blocks = own_claims(f, lp.shm, need, s, a, st);
         hipLaunchKernelGGL((k_pool32<TRACE, decltype(L)::value, decltype(T)::value,
                                      decltype(O)::value, PW>),
-                           dim3(resident_blocks(f, lp.shm, need)), dim3(kBlock), lp.shm, st,
+                           dim3(blocks), dim3(kBlock), lp.shm, st,
                            g, s, a);
       }, lp.lds_exit, lp.staged, obs);
     });
