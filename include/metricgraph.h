@@ -206,7 +206,8 @@ void mg_graph_destroy(mg_graph *g);
  *                 MG_SCHED_POOLS256 (3: the same with 256 particles) or
  *                 MG_SCHED_POOLS_W8 (4: pools of 128 whose lanes run on
  *                 until 16 of them, not 8, lack a particle, where the
- *                 graph's tables are staged in LDS or the set is FP64).
+ *                 graph's tables are staged in LDS, in a batch, or where
+ *                 the set is FP64).
  *                 Results are identical; only the speed differs.  FP64 sets
  *                 run MG_SCHED_LANES or MG_SCHED_POOLS_W8 (FP64 wave pools
  *                 of 128, also the automatic choice;

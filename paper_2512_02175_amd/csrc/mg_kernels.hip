@@ -3007,9 +3007,12 @@ size_t beside_bytes(bool obs) {
 // Hence 16 lanes where the launch stages its tables in LDS, and 8 where an
 // FP32 set reads them from global memory: a refill there waits for loads that
 // the other lanes' steps hide, and pays earlier.  (FP64, 16 against 8: 55.2
-// against 56.2 ms for 2000 steps of 1e7 on the 64-edge star.)
-int32_t refill_lanes(int32_t kernel, bool fp64, bool staged) {
-  return kernel == 3 && (fp64 || staged) ? 16 : 8;
+// against 56.2 ms for 2000 steps of 1e7 on the 64-edge star.)  In a batch 16
+// also where a group reads its tables from global memory: 64 uneven sets, 1000
+// steps, 18.1 against 18.8 ms with 8 in such groups; four trees of 600 to 2500
+// edges, 8e6 particles, 300 steps of 10^-2, 5.0 against 5.4.
+int32_t refill_lanes(int32_t kernel, bool fp64, bool late) {
+  return kernel == 3 && (fp64 || late) ? 16 : 8;
 }
 
 // Compute units of the current device, looked up once.
@@ -3204,7 +3207,7 @@ KernelLaunch batch_launch_t(int32_t n_items, int32_t max_nnz, int32_t max_stage,
                                 pools ? beside_bytes<P, FP64, TRACE>(obs)
                                       : beside_bytes<0, FP64, TRACE>(obs), nullptr, 0);
     k.shm = lp.shm;
-    k.refill = refill_lanes(a.kernel, FP64, lp.staged);
+    k.refill = refill_lanes(a.kernel, FP64, true);
     with_gen(gen, [&](auto Gn) {
       constexpr int gn = decltype(Gn)::value;
       with_flags([&](auto L, auto T, auto O) {

@@ -310,7 +310,7 @@ assert kernel(workloads.double_well_star(3), 1.0) == 3
 
 def test_refill_follows_the_launch_plan(stub):
     """Lanes that end a window: 16 of MG_SCHED_POOLS_W8 where the launch stages
-    the graph's tables in LDS, else 8 in FP32; group by group in a batch."""
+    the graph's tables in LDS, else 8 in FP32; 16 in every group of a batch."""
     stub("""
 small, large = (B.mg_graph_create(workloads.star_graph(E)) for E in (20, 2000))
 def staged(kernel):                         # <trace, exits in LDS, tables in LDS, ...>
@@ -333,7 +333,7 @@ for prec in (1, 0):
     l = steps(log())
     assert len({staged(k) for k, _, _ in l}) == 2, l
     for k, _, a in l:
-        assert a["refill"] == (16 if prec == 0 or staged(k) else 8), (k, a)
+        assert a["refill"] == 16, (k, a)
 """)
 
 
