@@ -297,7 +297,7 @@ KernelLaunch batch_launch(int32_t n_items, int32_t max_nnz, int32_t max_stage,
 int32_t batch_blocks_per_cu(int32_t max_nnz, int32_t max_stage, const StepArgs &a, bool fp64,
                             bool trace, int32_t gen, bool *staged);
 // One LDS copy of the bins per block up to kLdsHistMax of them, else 64-bit
-// global atomics.
+// global atomics behind a table of recent bins.
 hipError_t launch_histogram(const GraphDev &g, const SetDev &s, int32_t nb,
                             uint64_t *out, bool fp64, hipStream_t st);
 // Fills a streamed histogram's table of edges (SetDev::obs_edge).

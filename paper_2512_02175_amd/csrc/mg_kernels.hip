@@ -2815,20 +2815,102 @@ __global__ __launch_bounds__(kHistBlock) void k_hist_lds(GraphDev G, SetDev S, i
   merge_bins(s_bin, nbins, out);
 }
 
-// Uniform bins too many for LDS: 64-bit global atomics, about 2.2e10 a
-// second whatever the number of bins beyond 32768 (1e7 particles 430 us, 1e8
-// 4.55 ms).  Passing over the particles once per range of edges whose bins
-// fit in LDS loses to them: 128000 bins 680 us for 1e7 particles, 262144 bins
-// 1.2 ms, 1.7e6 bins 57 ms for 1e8.
+// Uniform bins too many for LDS: 64-bit global atomics, about 2.2e10 a second
+// whatever the number of bins beyond 32768, but one after another (12 ns) where
+// many particles share a bin.  So a block first counts in a table of recent
+// bins in LDS, buckets of two by the bin's hash: a bin that finds an entry of
+// its own, or an empty one, counts there, any other in global memory; every
+// kHotTurns turns the entries go to the counters and the table starts anew, so
+// that bins of a part of the set are found too; lanes left to global memory add
+// up within the wave.  1e7 FP32 particles, by atomics alone and with the table:
+// 76800 bins, even 455 -> 453 us, all in one bin 120021 -> 105, in ten bins 12048
+// -> 102, the second half in one bin 60064 -> 340 (703 where the table is kept
+// for 8 turns), in 1000 bins 459 -> 307; 1.7e6 bins, even 478 -> 480, at the
+// vascular network's inlets 1228 -> 521; 1e8 particles on the network 4.65 ->
+// 4.55 ms.  (A pass per range of edges whose bins fit in LDS takes 250 us for
+// 76800 bins and 2.5 ms for 1.7e6 where the particles gather, and more than the
+// atomics where they do not.)
+constexpr uint32_t kHotBuckets = 256, kHotTurns = 2, kNoBin = 0xFFFFFFFFu;
 template <bool FP64>
 __global__ __launch_bounds__(kBlock) void k_hist_global(GraphDev G, SetDev S, int32_t nb,
-                                                        uint64_t *out) {
-  for_alive<FP64>(S, [&](const Quad<FP64> &q, uint32_t k) {
+                                                            uint64_t *out) {
+  __shared__ alignas(8) uint32_t s_bin[2 * kHotBuckets];
+  __shared__ uint32_t s_cnt[2 * kHotBuckets];
+  auto add = [&](uint32_t bin, uint32_t n) {
+    atomicAdd((unsigned long long *)&out[bin], (unsigned long long)n);
+  };
+  // the active lanes' bins, one addition for lanes of one bin while that saves
+  // at least three
+  auto add_together = [&](uint32_t bin) {
+    for (;;) {
+      const uint32_t b = __builtin_amdgcn_readfirstlane(bin);
+      const uint64_t same = ballot(bin == b);
+      const uint32_t n = (uint32_t)__popcll(same);
+      if (n < 4u) {
+        add(bin, 1u);
+        return;
+      }
+      if (bin == b) {
+        if (lane_rank(same) == 0u) add(b, n);
+        return;
+      }
+    }
+  };
+  auto bin_of_particle = [&](const Quad<FP64> &q, uint32_t k) {
     const int32_t e = (int32_t)(q.ef[k] & kEdgeMask);
     const EdgeRec64 &r = G.e64[e];
-    const int32_t idx = e * nb + bin_of(q.pos(k, r.L), r.span, nb);
-    atomicAdd((unsigned long long *)&out[idx], 1ull);
-  });
+    return (uint32_t)(e * nb + bin_of(q.pos(k, r.L), r.span, nb));
+  };
+  for (uint32_t i = threadIdx.x; i < 2 * kHotBuckets; i += kBlock)
+    s_bin[i] = kNoBin, s_cnt[i] = 0;
+  __syncthreads();
+  auto flush_table = [&]() {
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < 2 * kHotBuckets; i += kBlock) {
+      if (s_cnt[i]) add(s_bin[i], s_cnt[i]);
+      s_bin[i] = kNoBin, s_cnt[i] = 0;
+    }
+    __syncthreads();
+  };
+  // whether `bin` has (or now has) entry i, which held `held` when last read
+  auto owns = [&](uint32_t i, uint32_t held, uint32_t bin) {
+    if (held == kNoBin) held = atomicCAS(&s_bin[i], kNoBin, bin);
+    return held == bin || held == kNoBin;
+  };
+  const uint32_t quads = S.n / 4u, stride = gridDim.x * kBlock;
+  uint32_t turns = 0;
+  Quad<FP64> q;
+  for (uint32_t first = blockIdx.x * kBlock; first < quads; first += stride) {
+    const uint32_t id = first + threadIdx.x;
+    if (id < quads) {
+      q.load(S, id);
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) {
+        if (q.ef[k] & kDeadBit) continue;
+        const uint32_t bin = bin_of_particle(q, k);
+        const uint32_t i = 2u * ((bin * 2654435769u) >> 24);  // 256 buckets
+        const volatile uint32_t *held = &s_bin[i];
+        const uint32_t h0 = held[0], h1 = held[1];
+        if (h0 == bin || (h1 != bin && owns(i, h0, bin)))
+          atomicAdd(&s_cnt[i], 1u);
+        else if (h1 == bin || owns(i + 1u, h1, bin))
+          atomicAdd(&s_cnt[i + 1u], 1u);
+        else
+          add_together(bin);
+      }
+    }
+    if (++turns == kHotTurns) {
+      turns = 0;
+      flush_table();
+    }
+  }
+  flush_table();
+  if (blockIdx.x == 0 && threadIdx.x == 0 && (S.n & 3u)) {
+    q.load_tail(S, 4u * quads);
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+      if (!(q.ef[k] & kDeadBit)) add(bin_of_particle(q, k), 1u);
+  }
 }
 
 // Histogram over per-edge bins of any widths (the appendix's general
@@ -3375,7 +3457,7 @@ hipError_t launch_histogram(const GraphDev &g, const SetDev &s, int32_t nb,
     }, fp64);
     return hipGetLastError();
   }
-  const uint32_t blocks = std::min((s.n + 4 * kBlock - 1) / (4 * kBlock), 8192u);
+  const uint32_t blocks = std::min((s.n + 4 * kBlock - 1) / (4 * kBlock), 2048u);
   with_flags([&](auto F) {
     hipLaunchKernelGGL((k_hist_global<decltype(F)::value>), dim3(blocks), dim3(kBlock), 0, st, g,
                        s, nb, out);
