@@ -393,3 +393,18 @@ for prec, sched, most in ((0, 1, 16384), (1, 1, 16384), (0, 4, (KB64 - 4 * 128 *
             at = [counted(most // 2 + d, prec, sched, obs, batch) for d in (0, 1)]
             assert at == [True, False], (prec, sched, obs, batch, at)
 """)
+
+
+def test_blocks_of_a_csr_histogram(stub):
+    """At least a block per CU (or a turn of four particles per thread) where each
+    block counts in LDS; never more than the uniform histogram's 512."""
+    stub("""
+for E, nb, n, want in ((64, 256, 1_000_000, 256), (64, 256, 10_000_000, 256), (5, 100, 10_000_000, 512),
+                       (64, 256, 30_000, 30), (5, 2, 1, 1), (64, 512, 300_000, 256)):
+    p = B.mg_particles_init(B.mg_graph_create(workloads.star_graph(E)), n, 2, precision=1)
+    log()
+    B.mg_histogram_csr(p, (np.arange(E + 1) * nb).astype(np.int32),
+                       np.tile(np.arange(1, nb + 1) / nb, E))
+    (grid,) = [int(re.search(r"grid=(\\d+)", x)[1]) for x in log() if "k_hist_csr" in x]
+    assert grid == want, (E, nb, n, grid)
+""")
