@@ -679,16 +679,15 @@ struct Particle64 {
 
   // FP64 positions are always measured from the initial vertex.
   __device__ __forceinline__ void reanchor() {}
-  __device__ __forceinline__ void reanchor_if(bool) {}
   __device__ __forceinline__ bool fast_first(double w) { return fast(w); }
   __device__ __forceinline__ double pos64(double) const { return x; }
 
-  // Window preparation of the wave pools: only a window's first active step
+  // Window preparation of the step loop: only a window's first active step
   // can start on a vertex (every step that stays inside an edge ends
   // strictly inside it), where the normal points into the edge.
   template <int N>
-  __device__ __forceinline__ void prep_window(double (&W)[N], uint32_t jb, bool on = true) const {
-    if (on && (x == 0.0 || x == R.L)) {
+  __device__ __forceinline__ void prep_window(double (&W)[N], uint32_t jb) const {
+    if (x == 0.0 || x == R.L) {
       const bool init = x == 0.0;
 #pragma unroll
       for (int i = 0; i < N; ++i)
@@ -1132,8 +1131,8 @@ struct Particle32 {
   // Window preparation of the step loop: the first active step of a window
   // is the only one that can start on a vertex.
   template <int N>
-  __device__ __forceinline__ void prep_window(float (&W)[N], uint32_t jb, bool on = true) const {
-    if (on && y == 0.0f) {
+  __device__ __forceinline__ void prep_window(float (&W)[N], uint32_t jb) const {
+    if (y == 0.0f) {
 #pragma unroll
       for (int i = 0; i < N; ++i) W[i] = (jb == (uint32_t)i) ? at_vertex(W[i]) : W[i];
     }
@@ -1497,7 +1496,7 @@ __device__ __forceinline__ void step_block(const GraphDev &G, const SetDev &S,
   if (OBS && A.obs_lds) flush_obs(S, o.lds, A.obs_lds);
 }
 
-// GEN: some edge has higher drift or diffusion terms (FP32: lane schedule only).
+// GEN: the method-variant level of the graph (GraphDev::gen).
 template <bool FP64, bool TRACE, bool LDS, bool STAGED, bool OBS, int GEN>
 __global__ __launch_bounds__(kBlock) void k_step(GraphDev G, SetDev S, StepArgs A) {
   extern __shared__ uint4 smem4[];
@@ -2477,8 +2476,7 @@ __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
 #define MG_POOL_WAVES_PER_EU 6
 #endif
 
-// GEN (cubic coefficients) is instantiated for pools of 128 with two
-// Philox groups per window only.
+// The general levels (GEN) are built for pools of 128 only.
 template <bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN = 0>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL_WAVES_PER_EU)))
 void k_pool32(GraphDev G, SetDev S, StepArgs A) {
