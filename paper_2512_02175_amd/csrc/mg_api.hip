@@ -1494,7 +1494,10 @@ static bool due_tuning(const mg_particles *p, int64_t n_steps, double dt) {
     if (w != work.end())
       total = w->second += total;
     else if (work.size() < 1024)
-      work.emplace_back(dt, total);
+      try {
+        work.emplace_back(dt, total);
+      } catch (const std::bad_alloc &) {  // this call's work is not counted
+      }
     due = due || total >= pays;
   }
   // a probe allocates and waits: none inside a capture, which runs the default
@@ -2510,7 +2513,13 @@ mg_status mg_batch_simulate(mg_batch *b, int64_t n_steps, double dt, uint64_t se
         b->key_drain == a.drain && b->key_drain_lds == a.drain_lds)) {
     drop_graph(b);
     b->key_obs = obs;
-    hipError_t he = build_graph(b, n_steps, a, chunk);
+    hipError_t he = hipSuccess;
+    try {
+      he = build_graph(b, n_steps, a, chunk);
+    } catch (const std::bad_alloc &) {
+      drop_graph(b);
+      return fail(MG_ENOMEM, "no host memory for the batch launch graph");
+    }
     if (he != hipSuccess) {
       drop_graph(b);
       return hip_fail(he, "building the batch launch graph");

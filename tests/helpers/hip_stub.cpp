@@ -5,6 +5,7 @@
 // to the host run (their copies, at the time of the launch); the others leave
 // their memory as it is, so sets stay as allocated (zeros: particle on edge 0,
 // position 0).  A call can be made to fail by name.
+#include <dlfcn.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -13,6 +14,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -99,6 +101,20 @@ void run(const std::string &k, void **args) {
   }
 }
 }  // namespace
+
+// The library's own allocations can be made to fail too ("new").
+void *operator new(size_t bytes) {
+  if (g_count > 0 && g_fail == "new") {
+    Dl_info at;
+    if (dladdr(__builtin_return_address(0), &at) && strstr(at.dli_fname, "libmetricgraph") &&
+        fails("new"))
+      throw std::bad_alloc();
+  }
+  if (void *p = malloc(bytes ? bytes : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 extern "C" {
 

@@ -408,3 +408,32 @@ for E, nb, n, want in ((64, 256, 1_000_000, 256), (64, 256, 10_000_000, 256), (5
     (grid,) = [int(re.search(r"grid=(\\d+)", x)[1]) for x in log() if "k_hist_csr" in x]
     assert grid == want, (E, nb, n, grid)
 """)
+
+
+def test_no_exception_leaves_a_step_call(stub):
+    """Host memory that runs out inside mg_simulate or mg_batch_simulate is an
+    error code or costs nothing, not an exception through the C entry."""
+    out = stub("""
+G = B.mg_graph_create(workloads.star_graph(5))
+p = B.mg_particles_init(G, 100, 2, precision=1)
+fail("new", 0, 1)
+for dt in (1e-2, 1e-3, 1e-4):
+    assert L.mg_simulate(p.handle, 5, C.c_double(dt), C.c_uint64(1)) == B.MG_OK
+fail("")
+sets = [B.mg_particles_init(B.mg_graph_create(workloads.star_graph(E)), 1000, 2, precision=1)
+        for E in (5, 2000)]
+S.stub_blocks_per_cu(8)
+b = B.mg_batch_create(sets)
+k = 0
+while True:
+    fail("new", k, 1)
+    r = L.mg_batch_simulate(b.handle, 5, C.c_double(1e-2), C.c_uint64(1))
+    if r == B.MG_OK:
+        break
+    assert r == B.MG_ENOMEM and B.mg_particles_step(sets[0]) == 0, r
+    k += 1
+fail("")
+assert B.mg_particles_step(sets[0]) == 5
+print(k)
+""")
+    assert int(out) > 0
