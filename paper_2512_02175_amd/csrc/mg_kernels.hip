@@ -176,13 +176,17 @@ __device__ __forceinline__ void stage_bm(BmLds *t) {
 // -2 ln u of the Box-Muller uniform u = (a + 1/2) 2^-32: u = 2^k m with m in
 // [45/64, 45/32), m's interval of 128 gives c ~ 1/m, z = m c - 1 (one
 // rounding) lies in [-2^-8, 2^-7), and -2 ln u = -2 (k ln 2 + ln(1/c)) - 2
-// log1p(z), with log1p(z) = z + z^2 q(z), q the degree-5 minimax polynomial
-// (error below 2^-59 of log1p; minimax_fit.py beside this file) and ln 2 in
-// two parts, whose first, times k, adds to the table's constant exactly.  c =
-// 1 and no constant in the two intervals at 1, so the relative error stays
-// small where the logarithm vanishes: within 0.82 ulp (0.29 ulp rms) on 4e6
-// draws.  14 FP64 operations and a table read; the series of atanh with a
-// division that it replaces took 30 (0.80 ulp, 0.30 rms).
+// log1p(z) (the table-driven reduction of P. T. P. Tang, ACM TOMS 16, 1990, with
+// reciprocals of its own), with log1p(z) = z + z^2 q(z), q the degree-5 minimax
+// polynomial (error below 2^-59 of log1p; minimax_fit.py beside this file) and
+// ln 2 in two parts, whose first, times k, adds to the table's constant exactly.
+// c = 1 and no constant in the two intervals at 1, so the relative error stays
+// small where the logarithm vanishes.  Within 0.753 ulp of every u above 0.9
+// (below, 0.55) and 0.29 ulp rms on 4e6 draws; the worst draws lie in the two
+// binades of the result next to those intervals, where the constant's error and
+// z's rounding weigh most (1.06 ulp with constants chosen there as elsewhere).
+// 14 FP64 operations and a table read; the series of atanh with a division that
+// it replaces took 30 (0.80 ulp, 0.30 rms).
 __device__ __forceinline__ double neg2log_unit(uint32_t a, const BmLds *t) {
   const uint64_t bits = (uint64_t)__double_as_longlong(fma((double)a, 0x1p-32, 0x1p-33));
   const uint32_t h = (uint32_t)(bits >> 32), d = h - 0x3fe68000u;

@@ -13,7 +13,12 @@ imports it.
   near the reciprocal of its middle whose logarithm lies closest to a
   multiple of 2^-48, of the 20000 nearest (c = 1 for the intervals at 1), and
   that multiple of -2 log(1/c): its sum with k ln 2's first part, a multiple
-  of 2^-32 below 32, is then exact;
+  of 2^-32 below 32, is then exact.  In the seven intervals before those at 1,
+  where -2 log u is smallest beside the constant and z, 200000 doubles 70001
+  ulps apart are tried (the logarithms of neighbours, of c near 1, fall on few
+  fractions of 2^-48), and in the last of them they lie just below the c that
+  makes z = 2^-9 at its upper end, so that z passes 2^-9, where its rounding
+  error doubles, only where -2 log u has passed 2^-6;
 * the angle's table: for i of 128 the angle a near i/128 turns, a multiple
   of 2^-50, whose cosine and sine both lie within 2^-62 of a double (the
   nearest such a; a = 0 for i = 0), with those doubles.
@@ -79,8 +84,12 @@ def log_table():
         best = (1.0, 0.0)
         if i not in (75, 76):
             mid, err = float(2 / (mp.mpf(lo) + mp.mpf(hi))), mp.inf
-            for k in range(20000):
-                v = mid + (k + 1) // 2 * (1 if k % 2 else -1) * math.ulp(mid)
+            if i == 74:
+                mid = float((1 + mp.mpf(2) ** -9) / mp.mpf(hi) * (1 - mp.mpf("2e-6")))
+            near1 = 68 <= i < 76
+            step = math.ulp(mid) * (70001 if near1 else 1)
+            for k in range(200000 if near1 else 20000):
+                v = mid + (k + 1) // 2 * (1 if k % 2 else -1) * step
                 scaled = -mp.ldexp(mp.log(mp.mpf(v)), 48)
                 e = abs(scaled - mp.nint(scaled))
                 if e < err:
@@ -117,7 +126,8 @@ HEAD = {
     "kLogTab": """// {c, -2 log(1/c)}: c close to the reciprocal of the middle of interval i of
 // the mantissa, [45/64 + i/256, + 1/256) below 1 and steps of 1/128 from 1 (i
 // = 76) on; c is the one among the nearest 20000 doubles whose logarithm is
-// closest to a multiple of 2^-48, and 1 for the two intervals at 1.
+// closest to a multiple of 2^-48 (for i = 68 .. 74 of others, minimax_fit.py),
+// and 1 for the two intervals at 1.
 """,
     "kTurnTab": """// {cos a, sin a, a}: a close to i/128 turns, such that its cosine and sine
 // are within 2^-62 of doubles.
