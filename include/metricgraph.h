@@ -206,8 +206,9 @@ void mg_graph_destroy(mg_graph *g);
  *                 MG_SCHED_POOLS256 (3: the same with 256 particles) or
  *                 MG_SCHED_POOLS_W8 (4: pools of 128 whose lanes run on
  *                 until 16 of them, not 8, lack a particle, where the
- *                 graph's tables are staged in LDS, in a batch, or where
- *                 the set is FP64).
+ *                 graph's tables are staged in LDS, in a batch, where the
+ *                 set is FP64, or where diffusion alone makes 1 % of the
+ *                 steps reach a vertex).
  *                 Results are identical; only the speed differs.  FP64 sets
  *                 run MG_SCHED_LANES or MG_SCHED_POOLS_W8 (FP64 wave pools
  *                 of 128, also the automatic choice;
@@ -513,9 +514,8 @@ void mg_batch_destroy(mg_batch *b);
  * particle per lane; wave pools of 128 particles (2 per lane) that start a
  * partial split pass at 4, 8, 16 or 32 idle lanes; pools of 256 (4 per
  * lane) at 8 or 16; MG_SCHED_POOLS_W8 pools of 128 at 8, 16 or 32, which
- * share the times of the pools of 128 where the graph's tables are not staged
- * and their launches are the same) all give identical results, so tuning changes only
- * speed.  Each candidate advances a scratch copy of the set's first
+ * share the times of the pools of 128 where their launches are the same) all
+ * give identical results, so tuning changes only speed.  Each candidate advances a scratch copy of the set's first
  * min(n, 2^22) particles by probe_steps steps (<= 0: 1024) of size dt with
  * Philox key seed, timed with HIP events on the set's stream; the set
  * keeps the fastest for its later mg_simulate calls at this dt.  The

@@ -187,6 +187,8 @@ struct mg_graph {
   };
   std::vector<HitEdge> hit_edge;
   double hit_dt = 0.0, hit_sqrt = 0.0;
+  // hits of a step at unit dt of particles that diffuse, uniform by time
+  double hit_diffuse = 0.0;
   std::vector<double> length;  // host copy for readback conversion
   std::vector<double> span;    // length binned by the uniform histograms
   std::vector<int32_t> vinit_host, vterm_host;  // end vertices of each edge
@@ -919,6 +921,7 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
     return (int32_t)((uint32_t)v | (mirror ? kMirrorEnd : 0u) | (wz ? kWentzellEnd : 0u));
   };
   std::vector<mg_graph::HitEdge> hit_edge(E);
+  double ends = 0.0, stay = 0.0;
   for (int32_t e = 0; e < E; ++e) {
     const double a = d->drift_a ? d->drift_a[e] : 0.0;
     const double c = d->drift_c ? d->drift_c[e] : 0.0;
@@ -933,6 +936,8 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
     const double pull = std::max({0.0, -a, aL}) / d->sigma[e];
     hit_edge[e] = {pull, d->sigma[e] / d->length[e],
                    std::min(d->length[e] / d->sigma[e], 0.5 / pull) / d->sigma[e]};
+    ends += 1.0 / d->sigma[e];
+    stay += d->length[e] / (d->sigma[e] * d->sigma[e]);
     const float scale = (float)(std::isinf(d->length[e]) ? d->bin_span[e] : d->length[e]);
     e32[e] = {(float)d->length[e], (float)a, (float)c, (float)d->sigma[e], (float)aL,
               vi, vt, 1e-6f * scale};
@@ -1025,6 +1030,7 @@ mg_status mg_graph_create(const mg_graph_desc *d, mg_graph **out) {
   g->E = E;
   g->nnz = nnz;
   set_hits(g, std::move(hit_edge));
+  g->hit_diffuse = 0.8 * ends / stay;
   g->length.assign(d->length, d->length + E);
   g->vinit_host.assign(d->edge_init, d->edge_init + E);
   g->vterm_host.assign(d->edge_term, d->edge_term + E);
@@ -1449,12 +1455,13 @@ static int32_t pool_idle_at(const mg_particles *p, double dt) {
   return tuned_at(p, dt) ? p->tuned_idle : 16;
 }
 
-// Schedule fields of a launch: the kernel and the idle lanes that start a
-// partial split pass (the lanes that end a window follow from the launch's LDS
-// plan: refill_lanes).
-static void set_schedule(StepArgs &a, int32_t kernel, int32_t idle) {
+// Schedule fields of a launch: the kernel, the idle lanes that start a partial
+// split pass and (MG_SCHED_POOLS_W8) the lanes that end a window where the
+// graph's tables are read from global memory (refill_lanes).
+static void set_schedule(StepArgs &a, int32_t kernel, int32_t idle, const mg_graph *g) {
   a.kernel = kernel;
   a.idle = idle;
+  a.refill = far_refill(g->hit_diffuse * std::sqrt(a.dt));
   a.pool_cap = (uint32_t)pool_per_wave(kernel);
 }
 
@@ -1528,7 +1535,7 @@ mg_status mg_simulate(mg_particles *p, int64_t n_steps, double dt, uint64_t seed
   a.key1 = (uint32_t)(seed >> 32);
   a.dt = dt;
   set_schedule(a, p->prec == MG_FP32 ? fp32_kernel_at(p, dt) : step_kernel(p),
-               pool_idle_at(p, dt));
+               pool_idle_at(p, dt), p->g);
   p->ran_default = p->ran_default || (n_steps > 0 && p->prec == MG_FP32 && !p->g->gen &&
                                       p->schedule == MG_SCHED_AUTO && !tuned_at(p, dt));
   // a set without a fixed launch length takes the tuned one
@@ -2494,7 +2501,7 @@ mg_status mg_batch_simulate(mg_batch *b, int64_t n_steps, double dt, uint64_t se
   a.key0 = (uint32_t)seed;
   a.key1 = (uint32_t)(seed >> 32);
   a.dt = dt;
-  set_schedule(a, b->kernel, pool_idle(b->schedule_of));
+  set_schedule(a, b->kernel, pool_idle(b->schedule_of), p0->g);
   const uint32_t chunk = chunk_steps(p0->steps_per_launch);
   const int32_t n_sets = (int32_t)b->sets.size();
   // the previous call's upload must have left the pinned buffer
@@ -2633,13 +2640,15 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
   float best = 0.0f;
   int best_i = -1;
   for (int i = 0; i < kCand && he == hipSuccess; ++i) {
+    set_schedule(a, cand_kernel[i], cand_idle[i], p->g);
     // a candidate whose launch is an earlier one's (MG_SCHED_POOLS_W8 on a graph
-    // whose tables are not staged) has its time
+    // whose tables are not staged and whose hits are few) has its time
     int same = -1;
     for (int j = 0; j < i && same < 0; ++j)
       if (cand_kernel[j] && cand_idle[j] == cand_idle[i] &&
           pool_per_wave(cand_kernel[j]) == pool_per_wave(cand_kernel[i]) &&
-          pool_refill(p->g->gd, cand_kernel[j]) == pool_refill(p->g->gd, cand_kernel[i]))
+          pool_refill(p->g->gd, cand_kernel[j], a.refill) ==
+              pool_refill(p->g->gd, cand_kernel[i], a.refill))
         same = j;
     if (same >= 0) {
       res.probe_ms[i] = res.probe_ms[same];
@@ -2649,7 +2658,6 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
     if (he == hipSuccess)
       he = hipMemcpyAsync(sd.y32, p->sd.y32, (size_t)n * 8, hipMemcpyDeviceToDevice, p->stream);
     if (he == hipSuccess) he = hipEventRecord(e0, p->stream);
-    set_schedule(a, cand_kernel[i], cand_idle[i]);
     if (he == hipSuccess) he = launch_step(p->g->gd, sd, a, false, false, p->stream);
     if (he == hipSuccess) he = hipEventRecord(e1, p->stream);
     if (he == hipSuccess) he = hipEventSynchronize(e1);
@@ -2665,7 +2673,7 @@ mg_status mg_autotune(mg_particles *p, double dt, uint64_t seed, int32_t probe_s
   // steps per launch for the chosen schedule: 2 x steps as one launch
   // against two launches of `steps` (each launch ends with a tail of partly
   // filled waves; the launch count is the only difference)
-  if (he == hipSuccess) set_schedule(a, cand_kernel[best_i], cand_idle[best_i]);
+  if (he == hipSuccess) set_schedule(a, cand_kernel[best_i], cand_idle[best_i], p->g);
   for (int i = 0; i < 2 && he == hipSuccess; ++i) {
     he = hipMemcpyAsync(sd.ef, p->sd.ef, (size_t)n * 4, hipMemcpyDeviceToDevice, p->stream);
     if (he == hipSuccess)

@@ -267,9 +267,11 @@ hipError_t launch_init(const GraphDev &g, const SetDev &s, int mode,
                        const InitSources &src, bool fp64, hipStream_t st);
 hipError_t launch_step(const GraphDev &g, const SetDev &s, const StepArgs &a,
                        bool fp64, bool trace, hipStream_t st);
-// StepArgs::refill of an FP32 wave-pool launch (without trace or streaming) on
-// the graph.
-int32_t pool_refill(const GraphDev &g, int32_t kernel);
+// StepArgs::refill where a set alone reads its tables from global memory, by
+// the hits of a step that diffusion is expected to make; and as it becomes in
+// an FP32 wave-pool launch (without trace or streaming) on the graph.
+int32_t far_refill(double hits);
+int32_t pool_refill(const GraphDev &g, int32_t kernel, int32_t far);
 // Particles per batch work item: eight pools per wave for the FP32
 // wave-pool kernel (a wave refills its pool from them), a plain block
 // otherwise.

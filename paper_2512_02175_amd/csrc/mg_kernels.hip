@@ -2236,7 +2236,8 @@ __device__ void run_pool(const GView &G, int32_t n_edges, const SetDev &S,
       // without a hit (16 of them 64-bit products at half rate, 8
       // transcendentals at a quarter), 24 a step, where windows of eight steps with a
       // select per step took 39; what a hit adds (parking, the refill and
-      // its shorter first group, the split pass) is about 700 lane slots.
+      // its shorter first group, the split pass, lanes that wait for them) is
+      // 650 lane slots at 7.7 % hits a step and 1080 at 2.2 %.
       // FP32, 1000 steps of 3e7 particles on the vascular network (0.35 %
       // hits a step) 23.0 -> 19.3 ms, 2000 steps of 1e7 on the 64-edge star
       // 21.1 -> 20.4 ms (2.1 % hits), 30.7 -> 30.7 (7.1 %); FP64, 1e7 on the
@@ -3088,15 +3089,21 @@ size_t beside_bytes(bool obs) {
 // steps of 1e7 FP32 particles on the 64-edge star take 32.4 / 32.3 / 31.2 /
 // 31.3 ms at 7.1 % hits a step, 23.1 / 21.2 / 20.7 / 21.9 at 2.1 %, and 1000
 // steps of 3e7 on the vascular network (0.35 %) 19.3 / 18.6 / 19.2 / 20.4.
-// Hence 16 lanes where the launch stages its tables in LDS, and 8 where an
-// FP32 set reads them from global memory: a refill there waits for loads that
-// the other lanes' steps hide, and pays earlier.  (FP64, 16 against 8: 55.2
-// against 56.2 ms for 2000 steps of 1e7 on the 64-edge star.)  In a batch 16
-// also where a group reads its tables from global memory: 64 uneven sets, 1000
-// steps, 18.1 against 18.8 ms with 8 in such groups; four trees of 600 to 2500
+// Hence 16 lanes where the launch stages its tables in LDS (FP64, 16 against 8:
+// 55.2 against 56.2 ms for 2000 steps of 1e7 on the 64-edge star).  An FP32
+// refill that reads them from global memory waits for loads that the other
+// lanes' steps hide: it pays earlier where hits are few, later where they are
+// many.  1e7 particles, 300 steps, at 8 / 16 lanes by the hits that diffusion
+// makes: vascular network 0.2 % 1.89 / 1.95 ms; tree of 2000 edges 0.2 % 2.52 /
+// 2.56, 0.4 % 2.71 / 2.74, 1.0 % 3.30 / 3.27, 1.4 % 3.81 / 3.55; star of 2000
+// 0.8 % 3.12 / 3.11, 1.1 % 3.43 / 3.35, 2.5 % 4.77 / 4.44; Langevin star of 1000
+// 0.9 % 2.86 / 2.91, 1.8 % 3.47 / 3.44, 2.9 % 4.48 / 4.02; star of 4000, 500
+// steps, 2.5 % 8.30 / 7.59.  Hence 16 there from 1 % on, and 8 below.
+// In a batch 16 in every group: 64 uneven sets, 1000 steps, 18.1 against 18.8 ms
+// with 8 in the groups that read from global memory; four trees of 600 to 2500
 // edges, 8e6 particles, 300 steps of 10^-2, 5.0 against 5.4.
-int32_t refill_lanes(int32_t kernel, bool fp64, bool late) {
-  return kernel == 3 && (fp64 || late) ? 16 : 8;
+int32_t refill_lanes(int32_t kernel, bool fp64, bool late, int32_t far) {
+  return kernel != 3 ? 8 : fp64 || late ? 16 : far;
 }
 
 // Compute units of the current device, looked up once.
@@ -3180,7 +3187,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                                   pool_lds_bytes<kPoolSmall, true, TRACE>(obs) * kWavesPerBlock,
                                   beside_bytes<kPoolSmall, true, TRACE>(obs), &s, g.E);
       a.obs_lds = lp.obs_lds;
-      a.refill = refill_lanes(a.kernel, true, lp.staged);
+      a.refill = refill_lanes(a.kernel, true, lp.staged, a.refill);
       const uint32_t need = set_pool(a, s.n, kPoolSmall, true);
       with_gen(g.gen, [&](auto Gn) {
         constexpr int gn = decltype(Gn)::value;
@@ -3205,7 +3212,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                                   pool_lds_bytes<PW, false, TRACE>(obs) * kWavesPerBlock,
                                   beside_bytes<PW, false, TRACE>(obs), &s, g.E);
       a.obs_lds = lp.obs_lds;
-      a.refill = refill_lanes(a.kernel, false, lp.staged);
+      a.refill = refill_lanes(a.kernel, false, lp.staged, a.refill);
       const uint32_t need = set_pool(a, s.n, PW, false);
       if (!TRACE && !obs && a.probe) {
         with_flags([&](auto L, auto T) {
@@ -3291,7 +3298,7 @@ KernelLaunch batch_launch_t(int32_t n_items, int32_t max_nnz, int32_t max_stage,
                                 pools ? beside_bytes<P, FP64, TRACE>(obs)
                                       : beside_bytes<0, FP64, TRACE>(obs), nullptr, 0);
     k.shm = lp.shm;
-    k.refill = refill_lanes(a.kernel, FP64, true);
+    k.refill = refill_lanes(a.kernel, FP64, true, a.refill);
     with_gen(gen, [&](auto Gn) {
       constexpr int gn = decltype(Gn)::value;
       with_flags([&](auto L, auto T, auto O) {
@@ -3340,14 +3347,16 @@ hipError_t launch_step(const GraphDev &g, const SetDev &s, const StepArgs &a,
                : launch_step_t<false, false>(g, s, a, st);
 }
 
-int32_t pool_refill(const GraphDev &g, int32_t kernel) {
+int32_t far_refill(double hits) { return hits >= 0.01 ? 16 : 8; }
+
+int32_t pool_refill(const GraphDev &g, int32_t kernel, int32_t far) {
   bool staged = false;
   with_pool(kernel, [&](auto PWc) {
     const size_t pools = pool_lds_bytes<decltype(PWc)::value, false, false>(false);
     staged =
         plan_lds(false, g.nnz, g.stage_bytes32, pools * kWavesPerBlock, 0, nullptr, 0).staged;
   });
-  return refill_lanes(kernel, false, staged);
+  return refill_lanes(kernel, false, staged, far);
 }
 
 const void *batch_reset_kernel() { return (const void *)k_batch_reset; }

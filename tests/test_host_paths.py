@@ -310,17 +310,25 @@ assert kernel(workloads.double_well_star(3), 1.0) == 3
 
 def test_refill_follows_the_launch_plan(stub):
     """Lanes that end a window: 16 of MG_SCHED_POOLS_W8 where the launch stages
-    the graph's tables in LDS, else 8 in FP32; 16 in every group of a batch."""
+    the graph's tables in LDS or diffusion makes a hit in every hundred steps,
+    else 8 in FP32; 16 in every group of a batch."""
     stub("""
 small, large = (B.mg_graph_create(workloads.star_graph(E)) for E in (20, 2000))
+longer = B.mg_graph_create(workloads.star_graph(2000, np.linspace(2.0, 6.0, 2000), sigma=0.5))
+endless = B.mg_graph_create(workloads.star_graph(2000, np.inf, bin_span=1.0))
 def staged(kernel):                         # <trace, exits in LDS, tables in LDS, ...>
     return re.search(r"(?:k_pool|k_step)\\w*?I((?:Lb[01]E)+)", kernel)[1][10] == "1"
 n = 1_000_000
-for prec, sched, G, want in ((1, 4, small, 16), (1, 4, large, 8), (1, 2, small, 8),
-                             (1, 2, large, 8), (0, 4, small, 16), (0, 4, large, 16)):
-    p = B.mg_particles_init(G, n, 2, precision=prec, schedule=sched)
+# 0.8 sigma sqrt(dt) / L hits: at 1.5e-4 of the unit star 0.98 %, at 1.6e-4 1.01 %
+for prec, sched, G, dt, want in (
+        (1, 4, small, 1e-5, 16), (1, 4, large, 1e-5, 8), (1, 4, large, 1.5e-4, 8),
+        (1, 4, large, 1.6e-4, 16), (1, 4, large, 1e-2, 16), (1, 4, longer, 9.8e-3, 8),
+        (1, 4, longer, 1.02e-2, 16), (1, 4, endless, 1.0, 8), (1, 2, small, 1e-2, 8),
+        (1, 2, large, 1e-2, 8), (0, 4, small, 1e-5, 16), (0, 4, large, 1e-5, 16)):
+    p = B.mg_particles_init(G, n, 1 if G is endless else 2, precision=prec,
+                            schedule=sched)
     log()
-    B.mg_simulate(p, 5, 1e-2, 1)
+    B.mg_simulate(p, 5, dt, 1)
     (k, _, a), = steps(log())
     assert a["refill"] == want and staged(k) == (G is small), (k, a)
 for prec in (1, 0):
@@ -338,15 +346,15 @@ for prec in (1, 0):
 
 
 def test_equal_candidates_are_probed_once(stub):
-    """On a graph whose tables are not staged MG_SCHED_POOLS_W8 launches what
-    MG_SCHED_POOLS launches: seven probes, and the times of the other three are
-    those of their equals."""
+    """On a graph whose tables are not staged and whose hits are few
+    MG_SCHED_POOLS_W8 launches what MG_SCHED_POOLS launches: seven probes, and
+    the times of the other three are those of their equals."""
     stub("""
-for E, launches in ((20, 10), (2000, 7)):
+for E, dt, launches in ((20, 1e-5, 10), (2000, 1e-5, 7), (2000, 1e-2, 10)):
     p = B.mg_particles_init(B.mg_graph_create(workloads.star_graph(E)), 1_000_000, 2, precision=1)
     log()
     S.stub_fast(3)                          # pools of 128 at 16 idle lanes
-    t = B.mg_autotune(p, 1e-2)
+    t = B.mg_autotune(p, dt)
     l = [(re.search(r"I.*E", k)[0], a["idle"], a["refill"], a["nsteps"]) for k, _, a in steps(log())
          if a["kernel"]]
     assert len([x for x in l if x[3] == 1024]) - 2 == launches - 1, l   # (2: the launch length)
