@@ -2481,9 +2481,13 @@ __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
 #define MG_POOL_WAVES_PER_EU 6
 #endif
 
-// The general levels (GEN) are built for pools of 128 only.
+// The general levels (GEN) are built for pools of 128 only.  The full one takes
+// 117 to 128 registers: four waves a SIMD.  At six it spilled 53 to 118 of them
+// (2e6 particles on the Wentzell star, 60 steps of 10^-3: 2.32 ms, streaming
+// 2.74, in a batch of six sets of 2e5, 100 steps, 5.5; at five 1.35, 1.77, 3.7; at
+// four 1.32, 1.49, 3.1; 2e6 with 200 tabulated edges 1.32 / 1.17 / 1.16).
 template <bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN = 0>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL_WAVES_PER_EU)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEN == kGenFull ? 4 : MG_POOL_WAVES_PER_EU)))
 void k_pool32(GraphDev G, SetDev S, StepArgs A) {
   extern __shared__ uint4 smem4[];
   __shared__ unsigned long long s_tot[4];
@@ -2514,7 +2518,7 @@ void k_pool64(GraphDev G, SetDev S, StepArgs A) {
 // of one load.  Both counters are cleared by k_batch_reset before each
 // launch.
 template <bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN = 0>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MG_POOL_WAVES_PER_EU)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEN == kGenFull ? 4 : MG_POOL_WAVES_PER_EU)))
 void k_pool32_batch(const GraphDev *graphs, const SetDev *sets, const BatchItem *items,
                     StepArgs A) {
   extern __shared__ uint4 smem4[];
