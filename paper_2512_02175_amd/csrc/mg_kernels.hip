@@ -3149,6 +3149,16 @@ uint32_t device_cus() {
 // steps 0.14 / 0.22 / 0.46 / 0.60 -> 0.12 / 0.17 / 0.29 / 0.44; on the 5-edge
 // star with 2 hits a step 12.4 / 13.8 / 21.3 / 41.3 -> 4.6 / 6.2 / 14.9 / 41.6.
 // Shorter launches are bound by the updates and keep the large reservations.
+// From 96 steps on it is sixteen: the waves start together on their places in
+// the grid, and with eight a SIMD, for its five or six waves, a third of them
+// took a second turn while the others stood idle, by which of them came first.
+// 2e6 FP32 particles, counter alone / places with eight / with sixteen: 400
+// steps on the 64-edge star with trace 1520 / 1580 / 1457 us, streaming 1920 /
+// 1880 to 2560 / 1690, on the star of 4000 edges, streaming, 3475 / 3680 / 3430;
+// 100 steps on the 5-edge star with drifts 2200 / 2110 to 2690 / 2110.  At 60
+// steps eight are the faster (the network 238 against 308 us).  (Reservations
+// of one turn for all, where there are fewer than two, lose up to 26 %: 1000
+// steps of 1e6 on that 5-edge star.)
 uint32_t set_pool(StepArgs &a, uint32_t n, int32_t pool, bool fp64) {
   const uint32_t simds = 4u * device_cus();
   uint32_t cap = (uint32_t)pool;
@@ -3164,7 +3174,8 @@ uint32_t set_pool(StepArgs &a, uint32_t n, int32_t pool, bool fp64) {
   a.refill = std::max(1, a.refill * lanes / 64);
   if (cap < (uint32_t)pool) a.claim_chunk = std::min(a.claim_chunk, cap);
   if (a.nsteps >= 32u)
-    a.claim_chunk = std::min(a.claim_chunk, std::max(cap, (n / (8u * simds)) & ~15u));
+    a.claim_chunk = std::min(a.claim_chunk,
+                             std::max(cap, (n / ((a.nsteps < 96u ? 8u : 16u) * simds)) & ~15u));
   const uint32_t per_block = cap * kWavesPerBlock;
   return (n + per_block - 1) / per_block;
 }

@@ -68,8 +68,8 @@ const Block *find(const void *p) {
 }
 std::string args_of(const mg::StepArgs &a) {
   char b[256];
-  snprintf(b, sizeof b, " nsteps=%u kernel=%d idle=%d refill=%d pool_cap=%u", a.nsteps, a.kernel,
-           a.idle, a.refill, a.pool_cap);
+  snprintf(b, sizeof b, " nsteps=%u kernel=%d idle=%d refill=%d pool_cap=%u claim=%u", a.nsteps,
+           a.kernel, a.idle, a.refill, a.pool_cap, a.claim_chunk);
   return b;
 }
 void run(const std::string &k, void **args) {

@@ -345,6 +345,24 @@ for prec in (1, 0):
 """)
 
 
+def test_reservations_leave_every_simd_several(stub):
+    """Ids that a wave reserves at a time: at most an eighth of a SIMD's share of
+    the set (1024 SIMDs here), a sixteenth from 96 steps on, or a pool's worth."""
+    stub("""
+G = B.mg_graph_create(workloads.star_graph(20))
+for prec, n, k, cap, want in ((1, 2_000_000, 95, 128, 240), (1, 2_000_000, 96, 128, 128),
+                              (1, 3_000_000, 60, 128, 352), (1, 3_000_000, 100, 128, 176),
+                              (1, 1_000_000, 60, 128, 128), (1, 300_000, 400, 64, 64),
+                              (1, 10_000, 400, 16, 16), (1, 20_000_000, 4000, 128, 64),
+                              (0, 2_000_000, 60, 128, 240), (0, 2_000_000, 400, 128, 128)):
+    p = B.mg_particles_init(G, n, 2, precision=prec)
+    log()
+    B.mg_simulate(p, k, 1e-3, 1)
+    (_, _, a), = steps(log())
+    assert a["pool_cap"] == cap and a["claim"] == want, (n, k, a)
+""")
+
+
 def test_equal_candidates_are_probed_once(stub):
     """On a graph whose tables are not staged and whose hits are few
     MG_SCHED_POOLS_W8 launches what MG_SCHED_POOLS launches: seven probes, and
