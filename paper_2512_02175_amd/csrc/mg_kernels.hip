@@ -2485,7 +2485,8 @@ __device__ __forceinline__ void pool_block(const GraphDev &G, const SetDev &S,
 // 117 to 128 registers: four waves a SIMD.  At six it spilled 53 to 118 of them
 // (2e6 particles on the Wentzell star, 60 steps of 10^-3: 2.32 ms, streaming
 // 2.74, in a batch of six sets of 2e5, 100 steps, 5.5; at five 1.35, 1.77, 3.7; at
-// four 1.32, 1.49, 3.1; 2e6 with 200 tabulated edges 1.32 / 1.17 / 1.16).
+// four 1.32, 1.49, 3.1; 2e6 with 200 tabulated edges 1.32 / 1.17 / 1.16; 200
+// steps of 3e6 on the Wentzell star, streaming, 16.3 against 6.9 at four).
 template <bool TRACE, bool LDS, bool STAGED, bool OBS, int PW, int GEN = 0>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEN == kGenFull ? 4 : MG_POOL_WAVES_PER_EU)))
 void k_pool32(GraphDev G, SetDev S, StepArgs A) {
@@ -3140,7 +3141,9 @@ uint32_t device_cus() {
 //
 // The reservations of a launch of 32 steps or more also leave every SIMD
 // eight of them (or a pool's worth each), and in FP32 64 particles a wave last
-// up to six waves a SIMD (FP64 has three or four: 2e5 particles with tabulated
+// up to the six waves a SIMD that are resident, four at the full general level
+// (3e5 particles with 8 tabulated edges, streaming, 200 steps 760 us at 64,
+// 660 at 128; FP64 has three or four: 2e5 particles with tabulated
 // coefficients 3.7 ms at 128, 4.1 at 64).  A reservation is one wave's serial
 // work, and the 240 ids
 // that keep the counter's updates cheap at 500 steps left 3e5 particles to
@@ -3159,14 +3162,14 @@ uint32_t device_cus() {
 // steps eight are the faster (the network 238 against 308 us).  (Reservations
 // of one turn for all, where there are fewer than two, lose up to 26 %: 1000
 // steps of 1e6 on that 5-edge star.)
-uint32_t set_pool(StepArgs &a, uint32_t n, int32_t pool, bool fp64) {
+uint32_t set_pool(StepArgs &a, uint32_t n, int32_t pool, bool fp64, bool full) {
   const uint32_t simds = 4u * device_cus();
   uint32_t cap = (uint32_t)pool;
   if (n <= 16u * simds)
     cap = 16;
   else if (n <= 32u * simds)
     cap = 32;
-  else if (n <= (a.nsteps >= 32u && !fp64 ? 6u : 2u) * 64u * simds)
+  else if (n <= (a.nsteps < 32u || fp64 ? 2u : full ? 4u : 6u) * 64u * simds)
     cap = 64;
   const int32_t lanes = (int32_t)std::min<uint32_t>(cap, 64u);
   a.pool_cap = cap;
@@ -3203,7 +3206,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                                   beside_bytes<kPoolSmall, true, TRACE>(obs), &s, g.E);
       a.obs_lds = lp.obs_lds;
       a.refill = refill_lanes(a.kernel, true, lp.staged, a.refill);
-      const uint32_t need = set_pool(a, s.n, kPoolSmall, true);
+      const uint32_t need = set_pool(a, s.n, kPoolSmall, true, g.gen == kGenFull);
       with_gen(g.gen, [&](auto Gn) {
         constexpr int gn = decltype(Gn)::value;
         with_flags([&](auto L, auto T, auto O) {
@@ -3228,7 +3231,7 @@ hipError_t launch_step_t(const GraphDev &g, const SetDev &s, const StepArgs &a0,
                                   beside_bytes<PW, false, TRACE>(obs), &s, g.E);
       a.obs_lds = lp.obs_lds;
       a.refill = refill_lanes(a.kernel, false, lp.staged, a.refill);
-      const uint32_t need = set_pool(a, s.n, PW, false);
+      const uint32_t need = set_pool(a, s.n, PW, false, g.gen == kGenFull);
       if (!TRACE && !obs && a.probe) {
         with_flags([&](auto L, auto T) {
           const void *f =

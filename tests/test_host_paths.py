@@ -350,6 +350,7 @@ def test_reservations_leave_every_simd_several(stub):
     the set (1024 SIMDs here), a sixteenth from 96 steps on, or a pool's worth."""
     stub("""
 G = B.mg_graph_create(workloads.star_graph(20))
+W = B.mg_graph_create(workloads.wentzell_star())
 for prec, n, k, cap, want in ((1, 2_000_000, 95, 128, 240), (1, 2_000_000, 96, 128, 128),
                               (1, 3_000_000, 60, 128, 352), (1, 3_000_000, 100, 128, 176),
                               (1, 1_000_000, 60, 128, 128), (1, 300_000, 400, 64, 64),
@@ -360,6 +361,12 @@ for prec, n, k, cap, want in ((1, 2_000_000, 95, 128, 240), (1, 2_000_000, 96, 1
     B.mg_simulate(p, k, 1e-3, 1)
     (_, _, a), = steps(log())
     assert a["pool_cap"] == cap and a["claim"] == want, (n, k, a)
+for g, n, cap in ((G, 393_216, 64), (G, 393_217, 128), (W, 262_144, 64), (W, 262_145, 128)):
+    p = B.mg_particles_init(g, n, 2, precision=1)   # (waves that are resident)
+    log()
+    B.mg_simulate(p, 100, 1e-3, 1)
+    (_, _, a), = steps(log())
+    assert a["pool_cap"] == cap and a["claim"] == cap, (n, a)
 """)
 
 
