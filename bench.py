@@ -59,7 +59,7 @@ ALG_FP32_CUBIC = 10.0
 # HBM bytes per k_pool32 launch on this workload from the FETCH_SIZE and
 # WRITE_SIZE counter passes (scaled by a 1 GiB copy), valid for the kernel
 # source whose sha256 prefix is given; reported as null for any other build.
-TRAFFIC = {"kernel_sha256": "ef2cc7cec6d26aa1", "bytes_per_launch": 270.6e6}
+TRAFFIC = {"kernel_sha256": "d8fb24e46d6d6e2a", "bytes_per_launch": 257.6e6}
 
 
 def kernel_traffic():
@@ -123,8 +123,9 @@ def run_pass(B, G, g, run, prec, dt, torch, kernel_times, schedules=None, schedu
         if spl:
             launches = -(-run["n_steps"] // spl)
         if schedules is not None:
-            schedules.append((f"k_pool32 ({t['pool_size']} per wave, {t['window']}-step windows, "
-                              f"idle {t['idle_trigger']})"
+            refill = 16 if t["schedule"] == B.MG_SCHED_POOLS_W8 else 8
+            schedules.append((f"k_pool32 ({t['pool_size']} per wave, refill at {refill} lanes, "
+                              f"partial pass at {t['idle_trigger']})"
                               if t["schedule"] != B.MG_SCHED_LANES else "k_step<fp32>")
                              + (f" x{launches} launches of {spl} steps" if spl else ""))
     e0 = torch.cuda.Event(enable_timing=True)
